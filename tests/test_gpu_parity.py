@@ -257,6 +257,26 @@ def test_deterministic_and_batch_equals_single(sm, ctx):
     assert np.array_equal(o2.cpu().numpy(), single[0])
 
 
+def test_fewer_pairs_than_the_plan_holds(sm):
+    """Nine pairs run as eight and one, and a single frame after a batch of its
+    shape runs in the batch's scratch: fewer pairs than the plan was made for
+    (the shifted pixel copy, read at odd disparities, lies behind all of them)."""
+    say("case: 9 pairs of 200x120 Dmax 40 in one call, then one frame")
+    pairs = [make_pair(200, 120, 40, segments=5, seed=500 + s) for s in range(9)]
+    lefts = [torch.from_numpy(p.left).cuda() for p in pairs]
+    rights = [torch.from_numpy(p.right).cuda() for p in pairs]
+    c = sm.Stereo(0)
+    outs = c.disparity_batch(lefts, rights, 40)
+    one = c.disparity(lefts[3], rights[3], 40)
+    torch.cuda.synchronize()
+    for i, p in enumerate(pairs):
+        exp = oracle.disparity(p.left, p.right, 40)["out"]
+        assert_same(f"pair {i}", outs[i].cpu().numpy(), exp)
+        if i == 3:
+            assert_same("single frame", one.cpu().numpy(), exp)
+    c.close()
+
+
 def test_ten_runs_bit_identical_at_paper_size(sm, ctx):
     """1436x992, Dmax 145: ten frames in flight on two streams at once, then
     ten one after another on the launch stream, all give the bits of the first
