@@ -19,9 +19,9 @@ void free_soft_plans(std::vector<SoftPlan*>& plans);
 }  // namespace stereo_host
 
 namespace stereo_host {
-// d-chunk size (disparities) for groups x D of work over band rows of height
-// rows, from the model of the per-XCD dispatch queues (stereo.hip).
-int best_chunk_size(int groups, int D, int rows, int num_cu);
+// d-chunk size (disparities, at most cap) for groups x D of work over band rows
+// of height rows, from the model of the per-XCD dispatch queues (stereo.hip).
+int best_chunk_size(int groups, int D, int rows, int num_cu, int cap);
 
 // A launch geometry chosen by stereo_autotune for one shape and parameter set.
 struct Tuned {

@@ -25,7 +25,6 @@ namespace {
 constexpr int kTX = 64;           // k_match strip width = one wave
 constexpr int kWaves = 16;        // k_match workgroup = 16 waves
 constexpr int kThreads = kWaves * 64;
-constexpr int kKMax = 34;         // most output rows per k_match thread (band <= 544 rows)
 constexpr int kLdsBytes = 163840; // LDS per workgroup on gfx950
 constexpr int kXcds = 8;          // accelerator complex dies, each with its own L2
 constexpr int kXcdQueues = 4;     // workgroup dispatch queues per XCD (position mod 4)
@@ -58,6 +57,7 @@ __device__ __forceinline__ void chunk_at(int j, int nloc, int nfull, int nchunk,
     }
   }
 }
+constexpr int kWinGroup = 2;      // k_match slot pairs whose window reads go together
 constexpr int kRowBatch = 2;      // k_match rows whose lookups and scans interleave
 
 
@@ -162,10 +162,6 @@ __global__ void __launch_bounds__(256) k_prep(PairPtrs pp, int W, int H, int X, 
 constexpr int kFeatRows = 16;    // output rows per k_feat workgroup (one pixel per thread)
 constexpr int kMaxArm = 127;
 
-// Columns left of a 64-column strip in k_match's row buffer for a horizontal
-// arm cap: arm + 1, rounded up to even (the row pass takes column pairs).
-__host__ __device__ constexpr int row_halo(int arm_cap) { return (arm_cap + 2) & ~1; }
-
 // Length of one arm of a pixel of value c: the number of steps t = 1, 2, ...
 // along the axis, taken without a break, whose pixel satisfies |I - c| < delta,
 // at most lim.  p points at the pixel in an LDS tile and STRIDE is the tile
@@ -236,10 +232,10 @@ __device__ __forceinline__ int arm_len(const uint8_t* p, int c, int delta, int c
 // image), census}, may be NULL) and to the two copies of pk16 (gray | census
 // << 8, may be NULL; the second copy copy16 elements after the first, one
 // pixel to the right); pitch XP, column x at pad + x.
-// xoff (may be NULL) takes, for k_match's row pass, the byte offsets in a
-// wave's row buffer of the row-prefix entries that bound CA_x (Eq. 7) at x:
-// 4 (x mod 64 + h - m - 1) in bits 0..15 and 4 (x mod 64 + h + n) in bits
-// 16..31, h = row_halo(cap) of the image; pitch XA like arms.
+// xoff (may be NULL) takes, for k_match's row pass, the distances in bytes
+// from column x's entry in a wave's row buffer to the row-prefix entries that
+// bound CA_x (Eq. 7) there: 4 (m + 1) down in bits 0..15 and 4 n up in bits
+// 16..31; pitch XA like arms.
 // Two workgroups share a CU only while a wave holds at most 80 SGPRs; the
 // waves-per-EU bound keeps the compiler under that (above it the kernel took
 // a fifth longer).
@@ -337,10 +333,8 @@ k_feat(const uint8_t* __restrict__ half, int X, int Y, int delta, int arm_x_l, i
           make_uint2(__float_as_uint(half_f[((size_t)img * Y + y) * X + x]), (uint32_t)bits);
     arms[((size_t)img * Y + y) * XA + x] =
         (uint32_t)m | ((uint32_t)n << 8) | ((uint32_t)M << 16) | ((uint32_t)N << 24);
-    if (xoff) {
-      const uint32_t lh = (uint32_t)(lx + row_halo(arm_x));
-      xoff[((size_t)img * Y + y) * XA + x] = 4u * (lh - (uint32_t)m - 1u) | 4u * (lh + (uint32_t)n) << 16;
-    }
+    if (xoff)
+      xoff[((size_t)img * Y + y) * XA + x] = 4u * ((uint32_t)m + 1u) | 4u * (uint32_t)n << 16;
     p16 = (uint32_t)c | (uint32_t)bits << 8;
   }
   if (pk16) {
@@ -377,44 +371,66 @@ __device__ __forceinline__ uint32_t wave_scan_incl(uint32_t v) {
 }
 
 
+// The same scan of N values, step by step in turn: each DPP step waits two
+// slots for the value it reads, which the other values' steps fill.
+template <int N>
+__device__ __forceinline__ void wave_scan_incl_n(uint32_t (&v)[N]) {
+#pragma unroll
+  for (int i = 0; i < N; ++i) v[i] += __builtin_amdgcn_update_dpp(0u, v[i], 0x111, 0xf, 0xf, false);
+#pragma unroll
+  for (int i = 0; i < N; ++i) v[i] += __builtin_amdgcn_update_dpp(0u, v[i], 0x112, 0xf, 0xf, false);
+#pragma unroll
+  for (int i = 0; i < N; ++i) v[i] += __builtin_amdgcn_update_dpp(0u, v[i], 0x114, 0xf, 0xf, false);
+#pragma unroll
+  for (int i = 0; i < N; ++i) v[i] += __builtin_amdgcn_update_dpp(0u, v[i], 0x118, 0xf, 0xf, false);
+#pragma unroll
+  for (int i = 0; i < N; ++i) v[i] += __builtin_amdgcn_update_dpp(0u, v[i], 0x142, 0xa, 0xf, false);
+#pragma unroll
+  for (int i = 0; i < N; ++i) v[i] += __builtin_amdgcn_update_dpp(0u, v[i], 0x143, 0xc, 0xf, false);
+}
+
+typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+
+// LDS words by their byte address.
+typedef const __attribute__((address_space(3))) uint32_t* lds_cptr;
+__device__ __forceinline__ uint32_t lds_read(uint32_t addr) { return *(lds_cptr)(uintptr_t)addr; }
+__device__ __forceinline__ void lds_write2(uint32_t addr, uint32_t v0, uint32_t v1) {
+  *(__attribute__((address_space(3))) u32x2*)(uintptr_t)addr = u32x2{v0, v1};
+}
+__device__ __forceinline__ uint32_t lds_addr(const void* p) {
+  return (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) void*)p;
+}
+
 // Keeps the compiler from moving LDS accesses of one wave across this point;
 // the LDS itself serves the accesses of a wave in issue order.
 #define WAVE_LDS_ORDER() __asm__ volatile("" ::: "memory")
-
-typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer_rsrc(const void* p, uint32_t bytes) {
   return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), (short)0, (int)bytes,
                                            0x00020000);
 }
 
-// cost table [h'][signed brightness difference + 256], h' = census distance
-// h (rows 0..6) or h + 7 for a match outside the other image (rows 7..13, all
-// C_max): 14 rows of 511 entries.  The row pitch, 530 entries = 265 words,
-// is 9 banks mod 64: entries of rows 1..6 apart land 9, 18, ..., 54 banks
-// apart, so lookups of neighbouring pixels (census distances a row or two
-// apart, brightness differences a few entries apart) rarely share a bank
-// (bank conflicts of the lookups 8.6 M -> 6.8 M cycles per launch against a
-// pitch of 257 words, 1 bank mod 64)
+// cost table [h][signed brightness difference + 256], h = census distance
+// 0..6: 7 rows of 511 entries.  The row pitch, 530 entries = 265 words, is 9
+// banks mod 64: entries of rows 1..6 apart land 9, 18, ..., 54 banks apart,
+// so lookups of neighbouring pixels (census distances a row or two apart,
+// brightness differences a few entries apart) rarely share a bank.
 constexpr int kTabPitch = 530;
-constexpr int kTabRows = 14;
+constexpr int kTabRows = 7;
 constexpr int kTab = kTabRows * kTabPitch;
-constexpr int kOutBias = 7;       // added to h for a match outside the image
 
 // Values the device cost table is built from: the tables of Eq. 4 (AD) and
-// Eq. 5 (census) in fixed point, computed on the host in double, and C_max.
+// Eq. 5 (census) in fixed point, computed on the host in double.
 struct TabArgs {
   uint16_t ad[256];
   uint16_t mc[7];
-  uint16_t cmax;
 };
 
 // Set-up of a plan's device state, ordered on the plan's stream (no memset
 // node, so it may be captured in a graph): clears nzero words at zero (the
 // padding of the pixel and arm planes must read 0; the kernels write the
-// image part) and writes the cost table, entry (h', 256 + diff) = LUT_AD[|diff|]
-// + LUT_MC[h'] for h' < kOutBias, else C_max; column 0 and the pitch's spare
-// columns 0.
+// image part) and writes the cost table, entry (h, 256 + diff) = LUT_AD[|diff|]
+// + LUT_MC[h]; column 0 and the pitch's spare columns 0.
 // grid: any, block 256.
 __global__ void __launch_bounds__(256) k_plan_init(uint32_t* __restrict__ zero, size_t nzero,
                                                    uint16_t* __restrict__ tab, TabArgs t) {
@@ -426,38 +442,82 @@ __global__ void __launch_bounds__(256) k_plan_init(uint32_t* __restrict__ zero, 
     const int a = col < 256 ? 256 - col : col - 256;
     // columns 1..511 hold differences -255..255; column 0 (a difference of
     // -256) and the spare columns are never read
-    tab[i] = (col == 0 || col > 511) ? (uint16_t)0
-                                     : (h < kOutBias ? (uint16_t)(t.ad[a] + t.mc[h]) : t.cmax);
+    tab[i] = (col == 0 || col > 511) ? (uint16_t)0 : (uint16_t)(t.ad[a] + t.mc[h]);
   }
 }
 
 // Bytes of k_match's static LDS: the cost table.
 constexpr int kMatchTabBytes = ((kTab * 2 + 15) / 16) * 16;
 
-// Bytes of k_match's dynamic LDS block with NS sub-passes and a plane of
-// `rows` rows (plane row 0 is the zero row): row buffers, segment totals and
-// the plane.
-__host__ __device__ constexpr int match_lds_bytes(int ns, int rows) {
-  return kWaves * ns * 128 * 4 + kWaves * 64 * 4 + rows * 64 * 4;
+// Bytes of k_match's dynamic LDS block with NS sub-passes, a plane of NB bases
+// and `rows` rows (plane row 0 is the zero row): row buffers and the plane,
+// whose rows hold 64 words per base.
+__host__ __device__ constexpr int match_lds_bytes(int ns, int nbase, int rows) {
+  return kWaves * ns * 128 * 4 + rows * nbase * 256;
 }
 
-// LDS rows of the k_match plane for NS sub-passes of 128 row-buffer columns.
-__host__ __device__ constexpr int plane_rows(int ns) {
-  return (kLdsBytes - kTab * 2 - kWaves * 64 * 4 - kWaves * ns * 128 * 4) / 256 - 2;
+// Plane rows (zero row included) that fit beside NS sub-passes of 128
+// row-buffer columns.
+__host__ __device__ constexpr int match_plane_rows(int ns, int nbase) {
+  return (kLdsBytes - kMatchTabBytes - kWaves * ns * 128 * 4) / (nbase * 256);
 }
+
+// Rows behind the pixel and arm planes that k_match's row loads may touch: the
+// missing second row of an odd segment and the next batch's two.
+constexpr int kMatchSlackRows = 3;
+
+// Most band rows per wave, and so most rows of a band over 16: what the plane
+// holds with one sub-pass (288 rows of both bases, 576 of one).
+__host__ __device__ constexpr int match_seg_rows(int nbase) { return 36 / nbase; }
+
+// Columns left of a strip in k_match's row buffer: the window's entry
+// x - m - 1, rounded up to even (column pairs).
+__host__ __device__ constexpr int match_halo(int arm_cap) { return (arm_cap + 2) & ~1; }
+
+// How far the right-based strip, moved by d, may lie left (lo) or right (hi)
+// of the left-based one so that the windows of both still fall inside the
+// 128 NS row-buffer columns; arm = the larger horizontal cap.  The d-chunks
+// hold at most lo + hi + 1 disparities.
+__host__ __device__ constexpr int match_slack_lo(int arm) { return match_halo(arm) - (arm + 1); }
+__host__ __device__ constexpr int match_slack_hi(int ns, int arm) {
+  return 128 * ns - match_halo(arm) - 64 - arm;
+}
+
+// Column offset of the right-based strip of a chunk that ends at disparity
+// dlast: right strip start = left strip start - offset, the smallest offset
+// that keeps d - offset <= hi.
+__host__ __device__ constexpr int match_delta(int dlast, int hi) { return dlast > hi ? dlast - hi : 0; }
+
+// The workgroups of a k_match launch: one per (strip, band, base with NB = 1,
+// pair, d-chunk) that has an output column.  Every chunk has the nfull strips
+// that start left of X; a chunk whose right-based strips are moved far enough
+// (delta > x0 - X) has up to kMatchExtra more at the right.  Items are numbered
+// by strip, so that neighbours read the same image rows: first those of the
+// full strips, `units` (bands x bases x pairs) x nfull x nchunk, chunk fastest,
+// then per extra strip units x (chunks it has).  Workgroups are dealt to the 8
+// XCDs in turn (id mod 8); XCD k takes the items k * per .. (k + 1) * per - 1, so
+// that a strip's rows stay in one XCD's L2 and every XCD has as many.
+constexpr int kMatchExtra = 9;  // D <= 512, 64 columns a strip, and the last strip's ragged end
+
+struct MatchGrid {
+  int nfull, units, total, per;
+  int nextra;                  // extra strips in use
+  int first[kMatchExtra];      // first chunk of each extra strip
+};
 
 struct MatchArgs {
   const uint16_t* pk;     // [2][2*npair][Y][XP]  padded: gray | census << 8, two copies
   const uint32_t* arms;   // [2*npair][Y][XA]  zero past column X
-  const uint32_t* xoff;   // [2*npair][Y][XA]  row-buffer offsets (k_feat), zero past column X
+  const uint32_t* xoff;   // [2*npair][Y][XA]  row-buffer distances (k_feat), zero past column X
   const uint16_t* tab;    // [kTabRows][kTabPitch]
   uint32_t* keys;         // [npair][nchunk][2][nk]  (min CA) << dbits | argmin d
-  int X, Y, XP, pad, XA, nk, arm_x, arm_x_r, arm_y;
+  int X, Y, XP, pad, XA, nk, arm, arm_y;  // arm: the larger horizontal cap
+  int cmax;               // cost of a match outside the other image
   int dbits;              // key = CA << dbits | d
   int nbands, dlo, dhi;
-  int csize, nchunk;      // d-chunk size; chunks = ceil((dhi - dlo) / csize), the last the remainder
-  int nstrips, ngroups;   // groups = strips x bands x 2 bases x pairs
-  uint32_t pk_bytes, arms_bytes;  // sizes of the pk (both copies) and arms buffers
+  int nchunk;             // d-chunks, of sizes that differ by one at most
+  MatchGrid grid;
+  uint32_t pk_bytes, arms_bytes;  // sizes of the pk (both copies) and arms buffers, slack rows included
   uint32_t copy_bytes;    // bytes from the first pk copy to the second
   // debug planes (pair 0, the single disparity dlo; used by the DBG variant)
   uint16_t* dbg_cost;
@@ -466,79 +526,138 @@ struct MatchArgs {
   int dbg_base;
 };
 
-// One workgroup = one 64-column strip x one band of rows x one base image
-// x one chunk of disparities; 16 waves.  For each d of the chunk:
-//   row pass   : each wave takes rows of the band; every lane evaluates the
-//                cost (Eq. 3-5, one lookup in a table indexed by census distance
-//                and signed brightness difference) of two adjacent columns of
-//                the strip plus arm_x+1 (rounded up to even) columns on either
-//                side, an inclusive wave scan gives the row prefix P, and
-//                CA_x = P[x+n] - P[x-m-1] (Eq. 7) goes into the LDS plane;
-//   column pass: segmented prefix down each column of the plane, in place, then
-//                CA = Q[y+N] - Q[y-M-1] (Eq. 8) for the band's output rows and
+// f(integral_constant 0), ..., f(integral_constant N - 1)
+template <int N, int I = 0, class F>
+__device__ __forceinline__ void static_for(F&& f) {
+  if constexpr (I < N) {
+    f(std::integral_constant<int, I>{});
+    static_for<N, I + 1>(f);
+  }
+}
+
+// f(integral_constant 0), f(integral_constant 1), ... while f returns true
+template <int N, int I = 0, class F>
+__device__ __forceinline__ void static_while(F&& f) {
+  if constexpr (I < N) {
+    if (f(std::integral_constant<int, I>{})) static_while<N, I + 1>(f);
+  }
+}
+
+// acc + |hi - lo| (hi >= lo): one instruction
+__device__ __forceinline__ uint32_t add_diff(uint32_t hi, uint32_t lo, uint32_t acc) {
+  uint32_t r;
+  __asm__("v_sad_u32 %0, %1, %2, %3" : "=v"(r) : "v"(hi), "v"(lo), "v"(acc));
+  return r;
+}
+
+// One workgroup = one 64-column strip x one band of rows x one chunk of
+// disparities; 16 waves.
+// NB = 2 takes both base images: the cost C(c, d) of left column c against
+// right column c - d serves both (Eq. 6: C^R(x') = C^L(x' + d)), so a row is
+// evaluated and scanned once for 64 left-based columns x = x0 + lane and 64
+// right-based ones x' = x0 - delta + lane; delta (match_delta) keeps the
+// columns x' + d of every d of the chunk inside the row buffer.
+// NB = 1 takes one base (columns x0 + lane; for the right one the images
+// change places: cost(R(x), L(x + d)) is C^L(x + d) term for term): its plane
+// holds twice the rows, for vertical arms so long that the halo rows of the
+// lower bands cost more than the shared evaluation saves.
+// For each d of the chunk:
+//   row pass   : each wave takes a segment of the band's rows; every lane
+//                evaluates the cost (Eq. 3-5, one lookup in a table indexed by
+//                census distance and signed brightness difference) of two
+//                adjacent columns of the 128 NS starting at x0 - hx, an inclusive
+//                wave scan gives the row prefix P, and CA_x = P[x+n] - P[x-m-1]
+//                (Eq. 7) of each base is added to running column sums, which
+//                stay in registers row by row;
+//   column pass: the segments' totals, exchanged through the row buffers, give
+//                each wave its offset, and the column prefix Q of the band
+//                goes to the LDS plane;
+//   window, WTA: CA = Q[y+N] - Q[y-M-1] (Eq. 8) for the band's output rows and
 //                key = min(key, CA << dbits | d): the smallest d wins ties (Step5).
-// The right-based cost is evaluated as cost(R(x), L(x+d)), which is C^L(x+d)
-// of Eq. 6 term for term.  Sums wrap modulo 2^32; every difference taken is a
-// window sum below 2^(32 - dbits) (the parameter check), hence exact and room
-// for d in the key's low dbits.  KMAX (<= kKMax) bounds the output rows
-// per thread: a band has at most 16 * KMAX output rows.
-// grid: ceil(groups / 8) * 8 * nchunk workgroups (1-D), block 1024.
-template <int NS, int KMAX, bool DBG>
+// Two barriers a disparity: the plane is written between them and read after
+// the second, so one wave's window step overlaps another's next row pass.
+// Bound by VALU issue and the LDS together (counters at 8 x 960x540 half-res
+// pixels, D = 128: a VALU instruction in 66% of the SIMDs' issue slots, LDS
+// active 60% of the time).  Against one base a workgroup with the plane
+// written in the row pass and corrected by LDS atomics after a third barrier:
+// 1747 -> 1242 us there, 92.7 -> 77.8 us at 718x496 D = 73, 709 -> 539 us at
+// 1436x992 D = 145, 1159 -> 855 us at 1436x992 D = 145 with arms 41 and 61.
+// Sums wrap modulo 2^32; every difference taken is a window sum below
+// 2^(32 - dbits) (the parameter check), hence exact and room for d in the
+// key's low dbits.  A band has at most 16 KMAX output rows and 16
+// match_seg_rows(NB) rows in all.
+// grid: 8 * grid.per workgroups (1-D), block 1024.
+template <int NS, int NB, int KMAX, bool DBG>
 __global__ void __launch_bounds__(kThreads) k_match(MatchArgs a) {
-  constexpr int PR = plane_rows(NS);
   // The cost table is the kernel's static LDS, at LDS address 0, so table
   // addresses fold into the read's offset field.  The rest is one dynamic
   // block carved at constant offsets, sized by the host to the plane rows the
-  // plan reads (match_lds_bytes), at most PR + 1: LDS the plan does not need
-  // is left to the kernels of other streams (the next frame's), which can
-  // then share the CU.
+  // plan reads (match_lds_bytes): LDS the plan does not need is left to the
+  // kernels of other streams (the next frame's), which can then share the CU.
   constexpr int kOffRow = 0;
-  constexpr int kOffSeg = kOffRow + kWaves * NS * 128 * 4;
-  constexpr int kOffPlane = kOffSeg + kWaves * 64 * 4;
-  static_assert(kMatchTabBytes + kOffPlane + (PR + 1) * 64 * 4 <= kLdsBytes, "LDS block");
+  constexpr int kOffPlane = kOffRow + kWaves * NS * 128 * 4;
+  constexpr int kPitch = NB * 64;  // words of a plane row
+  constexpr int kSegRows = match_seg_rows(NB);
   __shared__ __align__(16) uint16_t s_tab[kMatchTabBytes / 2];
   extern __shared__ __align__(16) uint8_t s_lds[];
   auto s_row = reinterpret_cast<uint32_t(*)[NS * 128]>(s_lds + kOffRow);
-  auto s_seg = reinterpret_cast<uint32_t(*)[64]>(s_lds + kOffSeg);
   uint32_t* s_plane = reinterpret_cast<uint32_t*>(s_lds + kOffPlane);  // row 0 = zeros
 
   const int t = threadIdx.x, lane = t & 63;
   const int wave = __builtin_amdgcn_readfirstlane(t >> 6);  // uniform: row offsets stay scalar
   const int X = a.X, Y = a.Y;
-  // Workgroups are dealt to the 8 XCDs in turn (id mod 8).  All d-chunks of
-  // one (strip, band, base, pair) group read the same image rows, so they are
-  // given ids of one residue mod 8: the group's rows stay in one XCD's L2;
-  // chunk_at orders each XCD's sequence for its dispatch queues.
-  const int wg = blockIdx.x, xcd = wg & (kXcds - 1), j = wg / kXcds;
-  int local, chunk;
-  chunk_at(j, (a.ngroups + kXcds - 1) / kXcds, (a.dhi - a.dlo) / a.csize, a.nchunk, local, chunk);
-  int group = local * kXcds + xcd;
-  if (group >= a.ngroups) return;  // padding workgroup
-  const int strip = group % a.nstrips;
-  group /= a.nstrips;
-  const int band = group % a.nbands;
-  group /= a.nbands;
-  const int base = group & 1, pair = group >> 1;
-  const int x0 = strip * kTX;
+  int item = (blockIdx.x & (kXcds - 1)) * a.grid.per + blockIdx.x / kXcds;
+  if (blockIdx.x / kXcds >= a.grid.per || item >= a.grid.total) return;  // padding workgroup
+  int strip, unit, chunk;
+  if (item < a.grid.nfull * a.grid.units * a.nchunk) {
+    chunk = item % a.nchunk;
+    item /= a.nchunk;
+    strip = item % a.grid.nfull;
+    unit = item / a.grid.nfull;
+  } else {
+    item -= a.grid.nfull * a.grid.units * a.nchunk;
+    int e = 0, n = a.nchunk - a.grid.first[0];
+    while (item >= a.grid.units * n) {
+      item -= a.grid.units * n;
+      ++e;
+      n = a.nchunk - a.grid.first[e];
+    }
+    strip = a.grid.nfull + e;
+    unit = item / n;
+    chunk = a.grid.first[e] + item - unit * n;
+  }
+  const int band = unit % a.nbands;
+  unit /= a.nbands;
+  const int base = NB == 2 ? 0 : unit & 1, pair = NB == 2 ? unit : unit >> 1;
+  const int nd = a.dhi - a.dlo;
+  const int d0 = a.dlo + chunk * nd / a.nchunk, d1 = a.dlo + (chunk + 1) * nd / a.nchunk;
+  const int x0 = strip * kTX, delta = NB == 2 ? match_delta(d1 - 1, match_slack_hi(NS, a.arm)) : 0;
   const int ob = (Y + a.nbands - 1) / a.nbands;
   const int y0 = band * ob, y1 = min(Y, y0 + ob);
   const int ya = max(0, y0 - a.arm_y), yb = min(Y, y1 + a.arm_y);
   const int nb = yb - ya, o0 = y0 - ya, o1 = y1 - ya;
-  const int d0 = a.dlo + chunk * a.csize, d1 = min(a.dhi, d0 + a.csize);
-  // row buffer starts at column x0 - hx (even); hx covers this base's arms
-  const int hx = row_halo(base ? a.arm_x_r : a.arm_x);
-  const int sgn = base ? 1 : -1;       // other-image column is x + sgn * d
+  const int hx = match_halo(a.arm), e0 = x0 - hx;  // the row buffer starts at column e0 (even)
+  // columns c of image img[0] against columns c + sgn d of the other one
+  const int sgn = base ? 1 : -1;
   const __amdgpu_buffer_rsrc_t rb = buffer_rsrc(a.pk, a.pk_bytes);
   const __amdgpu_buffer_rsrc_t ra = buffer_rsrc(a.xoff, a.arms_bytes);
-  const uint32_t img_b = (uint32_t)(2 * pair + base), img_o = (uint32_t)(2 * pair + (base ^ 1));
+  const uint32_t img[2] = {(uint32_t)(2 * pair + base), (uint32_t)(2 * pair + (base ^ 1))};
   const uint32_t pkrow = (uint32_t)a.XP * 2u, armrow = (uint32_t)a.XA * 4u;
-  const bool dbg = DBG && pair == 0 && base == a.dbg_base;
+  const bool dbg = DBG && pair == 0 && (NB == 2 || base == a.dbg_base);
   (void)dbg;
 
   for (int i = t; i < kTab; i += kThreads) s_tab[i] = a.tab[i];
-  if (t < 64) s_plane[t] = 0u;
+  if (t < kPitch) s_plane[t] = 0u;
 
-  const int c = lane, x = x0 + lane;
+  // output columns of the lane, per base: outside the image a clamped column
+  // is read and nothing stored
+  int xo[NB];
+  uint32_t vx[NB];
+#pragma unroll
+  for (int h = 0; h < NB; ++h) {
+    xo[h] = x0 + lane - (h ? delta : 0);
+    vx[h] = (uint32_t)min(max(xo[h], 0), a.XA - 1) * 4u;
+  }
   // rows of the band in segments of whole row pairs (the row pass takes its
   // rows in pairs), one per wave in order, the pairs split as evenly as
   // possible: the waves of each SIMD (wave mod 4) then share the rows evenly
@@ -546,227 +665,314 @@ __global__ void __launch_bounds__(kThreads) k_match(MatchArgs a) {
   const int r0 = min(nb, 2 * (wave * bq + min(wave, br)));
   const int r1 = min(nb, r0 + 2 * (bq + (wave < br)));
 
-  // Output rows of this thread: r = o0 + wave + 16 k.  marm[k / 2] packs the
-  // vertical arms (M, N) of two such rows, one byte each.  Rows outside the
-  // band or columns outside the image get M = N = 0; their keys are never
+  // Output rows of this thread: r = o0 + wave + 16 k, k < KMAX; slot k NB + h
+  // is row k of base h.  marm packs per slot NB times the vertical arms M, N
+  // (<= 127), one byte each, two slots a word: a plane row is 256 NB bytes,
+  // so such an arm in bits 8..15 of a 16-bit half is its offset.  Rows outside
+  // the band or columns outside the image get M = N = 0; their keys are never
   // stored.
-  static_assert(KMAX % 2 == 0, "KMAX must be even");
-  uint32_t key[KMAX], marm[KMAX / 2];
+  constexpr int kSlots = KMAX * NB;
+  static_assert(kSlots % 2 == 0, "slots go in pairs");
+  uint32_t key[kSlots], marm[kSlots / 2];
 #pragma unroll
-  for (int k = 0; k < KMAX; ++k) {
-    key[k] = 0xffffffffu;
+  for (int u = 0; u < kSlots; ++u) {
+    const int k = u / NB, h = u % NB;
+    key[u] = 0xffffffffu;
     const int r = o0 + wave + k * kWaves;
     // no branch around the load (a branch made every load wait for the one
     // before): rows past the band read its last row and are masked by a
     // wave-uniform select; columns past X read the plane's zero padding
-    const uint32_t v = a.arms[((size_t)img_b * Y + ya + min(r, o1 - 1)) * a.XA + x] >> 16;
-    const uint32_t mn = r < o1 ? v : 0u;
-    if (k & 1) marm[k / 2] |= mn << 16;
-    else marm[k / 2] = mn;
+    const uint32_t v = a.arms[((size_t)img[h] * Y + ya + min(r, o1 - 1)) * a.XA + vx[h] / 4u] >> 16;
+    const uint32_t mn = r < o1 ? v * NB : 0u;  // arms <= 127: no bit crosses a byte
+    if (u & 1) marm[u / 2] |= mn << 16;
+    else marm[u / 2] = mn;
   }
-  // byte offset in the plane of (band row o0 + wave, column c); plane row =
-  // band row + 1
-  const uint32_t fin_b = (uint32_t)((o0 + wave + 1) * 64 + c) * 4u;
-  // the key shift lives in a VGPR, so that shift-and-or with the scalar d
-  // is one instruction (one scalar operand per vector instruction)
-  uint32_t vdbits = (uint32_t)a.dbits;
-  __asm__ volatile("" : "+v"(vdbits));
-  // byte selector of v_perm: bytes 0 and 2 of marm (M of two rows) to bytes
-  // 1 and 3, zeros to bytes 0 and 2
-  uint32_t kpermM = 0x020c000cu;
-  __asm__ volatile("" : "+v"(kpermM));
-  // byte offset of this lane's first column pair inside a padded pk row
-  const uint32_t vb = (uint32_t)(a.pad + x0 - hx + 2 * lane) * 2u;
   __syncthreads();
 
   const char* tb = reinterpret_cast<const char*>(s_tab) + 512;
-  // cost of pixel J of a pair word: entry (h + bias, 256 + diff) at byte
-  // offset (h + bias) * 2 * kTabPitch + 2 * diff + 512; the census distance h
-  // is the popcount of the xor of the census bytes (one SDWA xor), and the
-  // popcount instruction adds the bias
-  auto cost = [&](uint32_t b, uint32_t o, uint32_t bias, auto J) -> uint32_t {
-    uint32_t hx;
+  // cost of pixel J of a pair word: entry (h, 256 + diff) at byte offset
+  // h * 2 * kTabPitch + 2 * diff + 512; the census distance h is the popcount
+  // of the xor of the census bytes (one SDWA xor)
+  auto cost = [&](uint32_t b, uint32_t o, auto J) -> uint32_t {
+    uint32_t hw;
     if constexpr (decltype(J)::value == 0)
       __asm__("v_xor_b32_sdwa %0, %1, %2 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:BYTE_1 "
-              "src1_sel:BYTE_1" : "=v"(hx) : "v"(b), "v"(o));
+              "src1_sel:BYTE_1" : "=v"(hw) : "v"(b), "v"(o));
     else
       __asm__("v_xor_b32_sdwa %0, %1, %2 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:BYTE_3 "
-              "src1_sel:BYTE_3" : "=v"(hx) : "v"(b), "v"(o));
+              "src1_sel:BYTE_3" : "=v"(hw) : "v"(b), "v"(o));
     constexpr int sh = decltype(J)::value * 16;
-    const uint32_t h = __builtin_popcount(hx) + bias;
+    const uint32_t h = __builtin_popcount(hw);
     const int df = (int)((b >> sh) & 255u) - (int)((o >> sh) & 255u);
     const int e = (int)h * (2 * kTabPitch) + df + df;
     return *reinterpret_cast<const uint16_t*>(tb + e);
   };
   using J0 = std::integral_constant<int, 0>;
   using J1 = std::integral_constant<int, 1>;
-  const uint32_t vx = (uint32_t)x * 4u;
 
   for (int d = d0; d < d1; ++d) {
+    // Per-lane addresses are formed anew for each disparity from the lane
+    // number, one instruction each: held over the loop they would take the
+    // registers of the row sums (the asm statement hides that they are the same).
+    uint32_t ln = (uint32_t)lane;
+    __asm__ volatile("" : "+v"(ln));
+    // byte offset of this lane's first column pair inside a padded pk row
+    const uint32_t vb = (uint32_t)(a.pad + e0) * 2u + ln * 4u;
+    // LDS addresses of the lane's pair in the wave's row buffer and of the
+    // entry of column x0 + lane
+    uint32_t wrow = lds_addr(s_row[wave]) + ln * 8u;
+    const uint32_t ent0 = lds_addr(s_row[wave]) + (uint32_t)hx * 4u + ln * 4u;
     // a pair of other-image pixels starting at an odd column is an aligned
     // word of the second copy (the parity of the column is that of d)
     const uint32_t odd = (uint32_t)d & 1u;
     const uint32_t vo = vb + (uint32_t)(sgn * d * 2) + 2u * odd;
     const uint32_t ocopy = odd ? a.copy_bytes : 0u;
-    // where the match oc of a column falls outside the other image, its cost
-    // is C_max (the x - d < 0 / x + d >= X convention): the lookup takes the
-    // table rows kOutBias.., which hold C_max, by a bias on the census distance
-    uint32_t bias[NS][2];
+    // the entry of each base's output column: the right-based column x' is
+    // left column x' + d
+    uint32_t ent[NB];
+    ent[0] = ent0;
+    if constexpr (NB == 2) ent[1] = ent0 + (uint32_t)((d - delta) * 4);
+    // held as they are: taken apart again, they would cost an add at each use
+    __asm__ volatile("" : "+v"(ent[0]), "+v"(ent[NB - 1]), "+v"(wrow));
+    // columns without a match cost C_max (the x - d < 0 / x + d >= X
+    // convention): selected after the lookup, in the strips that hold such
+    // columns only (wave-uniform).  Both bases: c < d and c >= X; one base:
+    // the other image's column outside it.
+    const int lo = NB == 2 ? d : (base ? -d : d), hi = NB == 2 ? X : (base ? X - d : X + d);
+    const bool edge = e0 < lo || e0 + 128 * NS > hi;
+    bool out[NS][2];
 #pragma unroll
     for (int s = 0; s < NS; ++s)
 #pragma unroll
-      for (int j = 0; j < 2; ++j) {
-        const int oc = x0 - hx + s * 128 + 2 * lane + j + sgn * d;
-        bias[s][j] = (unsigned)oc < (unsigned)X ? 0u : (uint32_t)kOutBias;
+      for (int jj = 0; jj < 2; ++jj) {
+        const int c = e0 + s * 128 + 2 * (int)ln + jj;
+        out[s][jj] = c < lo || c >= hi;
       }
     // ---- row pass over this wave's rows r0..r1-1, kRowBatch rows at a time
     // (their lookups and scans interleave), the loads of the next batch in flight.
-    // CA_x of a row is added to a running column sum, so the plane receives
-    // the column prefix within the wave's segment of rows.
-    struct RowIn { uint32_t b[NS], o[NS]; uint32_t am; };
-    auto load_row = [&](int r, RowIn& in) {
-      const uint32_t y = (uint32_t)(ya + r);
-      const uint32_t sb = (img_b * (uint32_t)Y + y) * pkrow;
-      const uint32_t so = (img_o * (uint32_t)Y + y) * pkrow + ocopy;
+    struct RowIn { uint32_t b[NS], o[NS], am[NB]; };
+    // scalar byte offsets of the row to load next, stepped row by row (rows
+    // past the segment's end belong to the next one, or to the kMatchSlackRows
+    // rows behind the planes; their sums are not stored).  The asm statement
+    // keeps the compiler from holding the offsets of all rows over the d loop.
+    const uint32_t yi[2] = {img[0] * (uint32_t)Y + (uint32_t)(ya + r0), img[1] * (uint32_t)Y + (uint32_t)(ya + r0)};
+    uint32_t sb = yi[0] * pkrow, so = yi[1] * pkrow + ocopy;
+    uint32_t sa[2] = {yi[0] * armrow, yi[1] * armrow};
+    __asm__ volatile("" : "+s"(sb), "+s"(so), "+s"(sa[0]), "+s"(sa[1]));
+    auto load_batch = [&](RowIn (&in)[kRowBatch]) {
 #pragma unroll
-      for (int s = 0; s < NS; ++s) {
-        in.b[s] = __builtin_amdgcn_raw_buffer_load_b32(rb, vb + s * 256, sb, 0);
-        in.o[s] = __builtin_amdgcn_raw_buffer_load_b32(rb, vo + s * 256, so, 0);
-      }
-      in.am = __builtin_amdgcn_raw_buffer_load_b32(ra, vx, (img_b * (uint32_t)Y + y) * armrow, 0);
-    };
-    // row prefix of one row (cost pairs c0, c1 per lane and sub-pass) into the
-    // row buffer, then CA_x of the lane's output column
-    auto finish_row = [&](int r, const uint32_t (&c0)[NS], const uint32_t (&c1)[NS],
-                          const uint32_t (&p1)[NS], uint32_t am) -> uint32_t {
-      const int y = ya + r;
-      uint32_t carry = 0;
+      for (int i = 0; i < kRowBatch; ++i) {
 #pragma unroll
-      for (int s = 0; s < NS; ++s) {
-        const uint32_t p = p1[s] + carry;
-        if (NS > 1) carry = __builtin_amdgcn_readlane(p, 63);
-        *reinterpret_cast<u32x2*>(&s_row[wave][s * 128 + 2 * lane]) = u32x2{p - c1[s], p};
-        if (DBG && dbg && d == a.dlo && y >= y0 && y < y1) {
-          const int xc = x0 - hx + s * 128 + 2 * lane;
-          if (xc >= x0 && xc < x0 + kTX && xc < X) a.dbg_cost[(size_t)y * X + xc] = (uint16_t)c0[s];
-          if (xc + 1 >= x0 && xc + 1 < x0 + kTX && xc + 1 < X)
-            a.dbg_cost[(size_t)y * X + xc + 1] = (uint16_t)c1[s];
+        for (int s = 0; s < NS; ++s) {
+          in[i].b[s] = __builtin_amdgcn_raw_buffer_load_b32(rb, vb + s * 256, sb, 0);
+          in[i].o[s] = __builtin_amdgcn_raw_buffer_load_b32(rb, vo + s * 256, so, 0);
         }
-      }
-      WAVE_LDS_ORDER();
-      // am: byte offsets of entries x + n and x - m - 1 in the row buffer
-      const uint8_t* rw = reinterpret_cast<const uint8_t*>(s_row[wave]);
-      const uint32_t cax = *reinterpret_cast<const uint32_t*>(rw + (am >> 16)) -
-                           *reinterpret_cast<const uint32_t*>(rw + (am & 0xffffu));
-      WAVE_LDS_ORDER();
-      if (DBG && dbg && d == a.dlo && x < X && y >= y0 && y < y1) a.dbg_cax[(size_t)y * X + x] = cax;
-      return cax;
-    };
-    uint32_t run = 0;
-    // Rows go in batches of kRowBatch: their lookups and scans interleave.  A
-    // batch running past the segment end loads its last row again in place
-    // of the missing ones and never stores them.
-    auto row_of = [&](int r, int i) { return r + i < r1 ? r + i : r1 - 1; };
-    auto load_batch = [&](int r, RowIn (&in)[kRowBatch]) {
 #pragma unroll
-      for (int i = 0; i < kRowBatch; ++i) load_row(row_of(r, i), in[i]);
+        for (int h = 0; h < NB; ++h)
+          in[i].am[h] = __builtin_amdgcn_raw_buffer_load_b32(ra, vx[h], sa[h], 0);
+        sb += pkrow;
+        so += pkrow;
+        sa[0] += armrow;
+        if constexpr (NB == 2) sa[1] += armrow;
+      }
     };
-    auto process_batch = [&](int r, const RowIn (&in)[kRowBatch]) {
-      uint32_t c0[kRowBatch][NS], c1[kRowBatch][NS], pr[kRowBatch][NS];
+    uint32_t run[kSegRows][NB], tot[NB] = {};
+    RowIn in[2][kRowBatch];  // two buffer sets, used in turn
+    if (r0 < r1) load_batch(in[0]);
+    auto batch = [&](auto Q) {
+      constexpr int q = decltype(Q)::value;
+      const int r = r0 + q * kRowBatch;
+      if (r >= r1) return false;
+      // the waves of a SIMD issue oldest first: a falling priority keeps them
+      // abreast, so that the last one does not run its rows alone
+      if constexpr (q == 0) __builtin_amdgcn_s_setprio(2);
+      if constexpr (q == kSegRows / 6) __builtin_amdgcn_s_setprio(1);
+      if constexpr (q == kSegRows / 3) __builtin_amdgcn_s_setprio(0);
+      // loaded unconditionally, so that the waits for this batch do not depend
+      // on the next one's loads
+      load_batch(in[(q + 1) & 1]);
+      const RowIn (&cur)[kRowBatch] = in[q & 1];
+      uint32_t c0[kRowBatch][NS], c1[kRowBatch][NS], pr[kRowBatch * NS];
 #pragma unroll
       for (int i = 0; i < kRowBatch; ++i)
 #pragma unroll
         for (int s = 0; s < NS; ++s) {
-          c0[i][s] = cost(in[i].b[s], in[i].o[s], bias[s][0], J0{});
-          c1[i][s] = cost(in[i].b[s], in[i].o[s], bias[s][1], J1{});
+          c0[i][s] = cost(cur[i].b[s], cur[i].o[s], J0{});
+          c1[i][s] = cost(cur[i].b[s], cur[i].o[s], J1{});
         }
+      if (edge) {
+#pragma unroll
+        for (int i = 0; i < kRowBatch; ++i)
+#pragma unroll
+          for (int s = 0; s < NS; ++s) {
+            c0[i][s] = out[s][0] ? (uint32_t)a.cmax : c0[i][s];
+            c1[i][s] = out[s][1] ? (uint32_t)a.cmax : c1[i][s];
+          }
+      }
 #pragma unroll
       for (int i = 0; i < kRowBatch; ++i)
 #pragma unroll
-        for (int s = 0; s < NS; ++s) pr[i][s] = wave_scan_incl(c0[i][s] + c1[i][s]);
+        for (int s = 0; s < NS; ++s) pr[i * NS + s] = c0[i][s] + c1[i][s];
+      wave_scan_incl_n(pr);
 #pragma unroll
       for (int i = 0; i < kRowBatch; ++i) {
-        // a row past the segment end (its last row again) is evaluated but
-        // neither added nor stored: the plane row belongs to the next segment
-        const uint32_t cax = finish_row(r + i, c0[i], c1[i], pr[i], in[i].am);
-        if (i == 0 || r + i < r1) {
-          run += cax;
-          s_plane[(r + i + 1) * 64 + lane] = run;
+        uint32_t carry = 0;
+#pragma unroll
+        for (int s = 0; s < NS; ++s) {
+          const uint32_t p = pr[i * NS + s] + carry;
+          if (NS > 1) carry = __builtin_amdgcn_readlane(p, 63);
+          lds_write2(wrow + s * 512, p - c1[i][s], p);
+        }
+        WAVE_LDS_ORDER();
+        // CA_x of each base; am: byte distances of the entries x + n (high
+        // half, up) and x - m - 1 (low half, down) from the column's own entry
+        uint32_t ph[NB], pl[NB];
+#pragma unroll
+        for (int h = 0; h < NB; ++h) {
+          ph[h] = lds_read(ent[h] + (cur[i].am[h] >> 16));
+          pl[h] = lds_read(ent[h] - (cur[i].am[h] & 0xffffu));
+        }
+        WAVE_LDS_ORDER();
+#pragma unroll
+        for (int h = 0; h < NB; ++h) {
+          tot[h] = add_diff(ph[h], pl[h], tot[h]);
+          run[q * kRowBatch + i][h] = tot[h];
+        }
+        if constexpr (DBG) {
+          const int y = ya + r + i;
+          if (dbg && r + i < r1 && y >= y0 && y < y1) {
+#pragma unroll
+            for (int h = 0; h < NB; ++h)
+              if ((NB == 1 || h == a.dbg_base) && xo[h] >= 0 && xo[h] < X)
+                a.dbg_cax[(size_t)y * X + xo[h]] = ph[h] - pl[h];
+            // the strip's columns of the wanted base: left column c is column
+            // c - d of the right base
+            const bool rb2 = NB == 2 && a.dbg_base;
+            const int s0 = rb2 ? x0 - delta : x0;
+#pragma unroll
+            for (int s = 0; s < NS; ++s)
+#pragma unroll
+              for (int jj = 0; jj < 2; ++jj) {
+                const int c = e0 + s * 128 + 2 * lane + jj - (rb2 ? d : 0);
+                if (c >= max(s0, 0) && c < min(s0 + kTX, X))
+                  a.dbg_cost[(size_t)y * X + c] = (uint16_t)(jj ? c1[i][s] : c0[i][s]);
+              }
+          }
+        }
+      }
+      return true;
+    };
+    static_while<kSegRows / kRowBatch>(batch);
+    // ---- column pass.  The wave's totals go to its own row buffer (its rows
+    // are done, and no other wave reads it before the barrier).  Only the
+    // band's last rows can be an odd segment, whose total holds a row past the
+    // end: no segment follows it, so that total is not used.
+#pragma unroll
+    for (int h = 0; h < NB; ++h) s_row[wave][NB * ln + h] = tot[h];
+    __syncthreads();
+    __builtin_amdgcn_s_setprio(3);
+    uint32_t off[NB] = {};
+    // the wave's own number as 8 + 4 + 2 + 1: groups of reads in flight together
+    int s0 = 0;
+#pragma unroll
+    for (int n = kWaves / 2; n > 0; n >>= 1)
+      if (wave & n) {
+        uint32_t v[8][NB];
+#pragma unroll
+        for (int s = 0; s < n; ++s)
+#pragma unroll
+          for (int h = 0; h < NB; ++h) v[s][h] = s_row[s0 + s][NB * ln + h];
+#pragma unroll
+        for (int s = 0; s < n; ++s)
+#pragma unroll
+          for (int h = 0; h < NB; ++h) off[h] += v[s][h];
+        s0 += n;
+      }
+    uint32_t* pw = s_plane + (r0 + 1) * kPitch + ln;
+    // counted anew: the row pass's tests are not kept for these
+    int nrows = r1 - r0;
+    __asm__ volatile("" : "+s"(nrows));
+    static_while<kSegRows>([&](auto K) {
+      constexpr int k = decltype(K)::value;
+      if (k >= nrows) return false;
+#pragma unroll
+      for (int h = 0; h < NB; ++h) pw[k * kPitch + h * 64] = run[k][h] + off[h];
+      return true;
+    });
+    __syncthreads();
+    // ---- vertical window and WTA for this wave's output rows, kWinGroup slot
+    // pairs at a time, the reads of the next group in flight
+    // byte offset in the plane of (band row o0 + wave, lane); plane row = band
+    // row + 1
+    const uint32_t fin_b = (uint32_t)((o0 + wave + 1) * kPitch) * 4u + ln * 4u;
+    // the key shift lives in a VGPR, so that shift-and-or with the scalar d
+    // is one instruction (one scalar operand per vector instruction)
+    uint32_t vdbits = (uint32_t)a.dbits;
+    // byte selector of v_perm: bytes 0 and 2 of marm (M of two slots) to bytes
+    // 1 and 3, zeros to bytes 0 and 2
+    uint32_t kpermM = 0x020c000cu;
+    __asm__ volatile("" : "+v"(vdbits), "+v"(kpermM));
+    uint32_t wh[2][kWinGroup][2], wl[2][kWinGroup][2];
+    auto window_reads = [&](auto G) {
+      constexpr int g = decltype(G)::value;
+#pragma unroll
+      for (int i = 0; i < kWinGroup; ++i) {
+        constexpr int jp0 = g * kWinGroup;
+        const int jp = jp0 + i;
+        if (jp >= kSlots / 2) continue;
+        // byte offsets of plane rows +N and -(M+1) from the output rows of two
+        // slots (16-bit halves): nw holds N, mw holds M; each read address is
+        // then one SDWA add or subtract.  Volatile asm keeps them inside the d
+        // loop (hoisted, they would need kSlots VGPRs).
+        uint32_t nw, mw;
+        __asm__ volatile("v_and_b32 %0, 0xff00ff00, %1" : "=v"(nw) : "v"(marm[jp]));
+        __asm__ volatile("v_perm_b32 %0, 0, %1, %2" : "=v"(mw) : "v"(marm[jp]), "v"(kpermM));
+#pragma unroll
+        for (int e = 0; e < 2; ++e) {
+          // rows +N and -(M+1) of the slot's output row (plane row 0 at least:
+          // M never reaches above the band); the slot's constant part becomes
+          // the reads' immediate offset
+          const int u = 2 * jp + e, k = u / NB, h = u % NB;
+          const uint8_t* row = s_lds + kOffPlane + k * kWaves * kPitch * 4 + h * 256 + fin_b;
+          const uint32_t on = e ? nw >> 16 : nw & 0xffffu, om = e ? mw >> 16 : mw & 0xffffu;
+          wh[g & 1][i][e] = *reinterpret_cast<const uint32_t*>(row + on);
+          wl[g & 1][i][e] = *reinterpret_cast<const uint32_t*>(row - kPitch * 4 - om);
         }
       }
     };
-    // The next batch is loaded unconditionally (past the segment end it
-    // reloads the last row): with the loads behind a branch, the waits at the
-    // join must hold for the path with them in flight and the path without,
-    // and the compiler then waited for the next batch too.
-    RowIn in0[kRowBatch], in1[kRowBatch];  // two buffer sets, used in turn
-    if (r0 < r1) load_batch(r0, in0);
-    for (int r = r0; r < r1; r += 2 * kRowBatch) {
-      load_batch(r + kRowBatch, in1);
-      process_batch(r, in0);
-      if (r + kRowBatch >= r1) break;
-      load_batch(r + 2 * kRowBatch, in0);
-      process_batch(r + kRowBatch, in1);
-    }
-    s_seg[wave][c] = run;
-    __syncthreads();
-    // ---- column pass: add the sum of the segments above to this segment.
-    // Each plane entry belongs to one thread; the add is an LDS atomic without
-    // return (ds_add_u32), one instruction per row and no read-add-write
-    // latency chain.
-    uint32_t off = 0;
+    constexpr int kWinGroups = (kSlots / 2 + kWinGroup - 1) / kWinGroup;
+    window_reads(std::integral_constant<int, 0>{});
+    static_for<kWinGroups>([&](auto G) {
+      constexpr int g = decltype(G)::value;
+      if constexpr (g + 1 < kWinGroups) window_reads(std::integral_constant<int, g + 1>{});
+      WAVE_LDS_ORDER();  // those reads are issued before this group is waited for
 #pragma unroll
-    for (int s = 0; s < kWaves; ++s) {
-      const uint32_t v = s_seg[s][c];
-      off += s < wave ? v : 0u;
-    }
-    if (wave > 0) {
-#pragma unroll 8
-      for (int r = r0; r < r1; ++r)
-        __hip_atomic_fetch_add(&s_plane[(r + 1) * 64 + c], off, __ATOMIC_RELAXED,
-                               __HIP_MEMORY_SCOPE_WORKGROUP);
-    }
-    __syncthreads();
-    // ---- vertical window and WTA for this wave's output rows
+      for (int i = 0; i < kWinGroup; ++i)
 #pragma unroll
-    for (int j = 0; j < KMAX / 2; ++j) {
-      // byte offsets of plane rows +N and -(M+1) from the output rows 2j and
-      // 2j+1: a plane row is 256 bytes, so an offset is an arm byte in bits
-      // 8..15 of a 16-bit half: nw holds N of both rows in its halves, mw
-      // holds M; each read address is then one SDWA add or subtract.
-      // Volatile asm keeps them inside the d loop (hoisted, they would need
-      // 32 VGPRs).
-      uint32_t nw, mw;
-      __asm__ volatile("v_and_b32 %0, 0xff00ff00, %1" : "=v"(nw) : "v"(marm[j]));
-      __asm__ volatile("v_perm_b32 %0, 0, %1, %2" : "=v"(mw) : "v"(marm[j]), "v"(kpermM));
-#pragma unroll
-      for (int h = 0; h < 2; ++h) {
-        const int k = 2 * j + h;
-        // rows +N and -(M+1) of output row k (plane row 0 at least: M never
-        // reaches above the band); the per-row part k * 4096 bytes becomes
-        // the reads' immediate offset
-        const uint8_t* row = s_lds + kOffPlane + k * kWaves * 256 + fin_b;
-        const uint32_t on = h ? nw >> 16 : nw & 0xffffu, om = h ? mw >> 16 : mw & 0xffffu;
-        const uint32_t ca = *reinterpret_cast<const uint32_t*>(row + on) -
-                            *reinterpret_cast<const uint32_t*>(row - 256 - om);
-        const uint32_t kv = (ca << vdbits) | (uint32_t)d;
-        key[k] = kv < key[k] ? kv : key[k];
-      }
-    }
-    __syncthreads();
+        for (int e = 0; e < 2; ++e) {
+          const int u = 2 * (g * kWinGroup + i) + e;
+          if (u >= kSlots) continue;
+          const uint32_t kv = ((wh[g & 1][i][e] - wl[g & 1][i][e]) << vdbits) | (uint32_t)d;
+          key[u] = kv < key[u] ? kv : key[u];
+        }
+    });
   }
 
   int nout = o1 - o0 - wave;  // output rows left for this wave, from row k = 0
   __asm__ volatile("" : "+v"(nout));  // recompute the row tests here
-  if (x < X) {
-    uint32_t* out = a.keys + ((size_t)(pair * a.nchunk + chunk) * 2 + base) * a.nk;
+#pragma unroll
+  for (int h = 0; h < NB; ++h) {
+    const int x = xo[h];
+    if (x < 0 || x >= X) continue;
+    uint32_t* kp = a.keys + ((size_t)(pair * a.nchunk + chunk) * 2 + (NB == 2 ? h : base)) * a.nk;
 #pragma unroll
     for (int k = 0; k < KMAX; ++k) {
       const int r = o0 + wave + k * kWaves;
       if (k * kWaves < nout) {
-        out[(size_t)(ya + r) * X + x] = key[k];
+        kp[(size_t)(ya + r) * X + x] = key[k * NB + h];
         // a debug run covers the single disparity dlo, so the key holds CA
-        if (DBG && dbg) a.dbg_ca[(size_t)(ya + r) * X + x] = key[k] >> a.dbits;
+        if (DBG && dbg && (NB == 1 || h == a.dbg_base))
+          a.dbg_ca[(size_t)(ya + r) * X + x] = key[k * NB + h] >> a.dbits;
       }
     }
   }

@@ -17,8 +17,11 @@ struct Plan {
   uint16_t lut_ad[256]{}, lut_mc[7]{};
   int cmax = 0;
   int dbits = 8;                // bits of d in the WTA keys
-  int ns = 1, kmax = 8, nstrips = 0, nbands = 0;
-  int csize = 1, nchunk = 0;    // k_match d-chunk size and chunk count ceil(D / csize)
+  // k_match: 128-column sub-passes, bases a workgroup, output rows per thread
+  // and base, row bands and the most rows of a band
+  int ns = 1, nbase = 2, kmax = 8, nbands = 0, brows = 0;
+  int csize = 1, nchunk = 0;    // largest d-chunk and chunk count
+  int ccap = 1;                 // largest chunk size the strips of both bases allow
   int XP = 0, pad = 0, XA = 0;  // padded pitches of pk and arms
   int nk = 0;                   // padded plane stride of keys, disp and mincost
   size_t bytes = 0;
@@ -28,7 +31,7 @@ struct Plan {
   uint16_t* pk = nullptr;     // [2][2*npair][Y][XP]  gray | census<<8, zero padding; the
                               // second copy one column to the right
   uint32_t* arms = nullptr;   // [2*npair][Y][XA]  zero padding
-  uint32_t* xoff = nullptr;   // [2*npair][Y][XA]  k_match row-buffer offsets of the
+  uint32_t* xoff = nullptr;   // [2*npair][Y][XA]  k_match row-buffer distances of the
                               // horizontal arm ends, zero padding
   uint16_t* tab = nullptr;    // [7][kTabPitch]
   uint32_t* keys = nullptr;   // [npair][nchunk][2][Y][X]

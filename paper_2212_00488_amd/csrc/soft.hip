@@ -134,7 +134,7 @@ int make_soft_plan(stereo_ctx* c, int n, int W, int H, int Dmax, const stereo_so
   pl->XS = pl->pads + pl->XA + 128 * pl->ns + 2;
   pl->XS = (pl->XS + 1) & ~1;
   const int groups = pl->nstrips * pl->nbands * n;
-  pl->csize = best_chunk_size(groups, D, pl->rows, c->num_cu);
+  pl->csize = best_chunk_size(groups, D, pl->rows, c->num_cu, D);
   pl->nchunk = (D + pl->csize - 1) / pl->csize;
   const size_t npix = (size_t)X * Y;
   // at most 128 disparities per slab (k_soft_tr's LDS rows of right gradients)
@@ -414,7 +414,7 @@ int stereo_soft_backward(stereo_ctx* c, const float* left, const float* right, i
                          (uint32_t)((size_t)pl->D * pl->n * npix * 4), pl->pc, pl->arms, X, Y,
                          pl->XA, pl->p.arm_y, pl->n, pl->D, ndg, pl->gcax);
     } else {
-      const int cs = best_chunk_size(groups, nds, pl->rows, c->num_cu);
+      const int cs = best_chunk_size(groups, nds, pl->rows, c->num_cu, nds);
       launch_soft_agg<true>(*pl, soft_args(*pl, lambdas, dlo, dhi, cs), stream);
       hipLaunchKernelGGL(k_soft_tcol, dim3((X + 63) / 64, (Y + tb - 1) / tb, nds * pl->n),
                          dim3(256), 0, stream, pl->gca, pl->arms, X, Y, pl->XA, pl->p.arm_y,

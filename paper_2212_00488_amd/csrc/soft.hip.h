@@ -205,6 +205,12 @@ __device__ __forceinline__ float wave_scan_incl_f(float v) {
   return v;
 }
 
+// LDS rows of the k_soft_agg plane for NS sub-passes of 128 row-buffer columns
+// (the row buffers, the segment totals, eight floats and a zero row beside it).
+__host__ __device__ constexpr int plane_rows(int ns) {
+  return (kLdsBytes - 32 - kWaves * 64 * 4 - kWaves * ns * 128 * 4) / 256 - 1;
+}
+
 // One workgroup = one 64-column strip x one band of rows x one pair x one
 // chunk of disparities; 16 waves, the layout of k_match (row pass with a DPP
 // wave scan, running column sums into the LDS plane, segment offsets, window

@@ -169,13 +169,14 @@ double match_makespan(int groups, int D, int cs, int cus_per_xcd, double ovh) {
 // the fastest size or one within 6% of it.
 constexpr double kSetupRows = 300.0;
 
-int best_chunk_size(int groups, int D, int rows, int num_cu) {
+int best_chunk_size(int groups, int D, int rows, int num_cu, int cap) {
   const int cus = std::max(1, num_cu / kXcds);
   const double ovh = kSetupRows / std::max(1, rows);
-  int best = D;
+  int best = std::min(D, cap);
   double best_t = 1e300;
   for (int n = 1; n <= std::min(D, 64); ++n) {
     const int cs = (D + n - 1) / n;
+    if (cs > cap) continue;
     if ((long)groups * ((D + cs - 1) / cs) > 16L * num_cu) break;
     const double t = match_makespan(groups, D, cs, cus, ovh);
     if (t < best_t - 1e-9) {  // ties keep the larger chunks (fewer workgroups)
@@ -186,46 +187,149 @@ int best_chunk_size(int groups, int D, int rows, int num_cu) {
   return best;
 }
 
-// Launch geometry: bands keep the k_match LDS plane and the per-thread key
-// registers within bounds; d-chunks raise the workgroup count to fill the CUs.
-void plan_geometry(Plan& pl, int num_cu, int forced_csize) {
-  // the row buffer spans x0 - hx .. x0 + 63 + arm_x, hx = arm_x + 1 rounded up to even
-  pl.ns = (66 + 2 * std::max(pl.p.arm_x, pl.p.arm_x_r) + 127) / 128;
-  const int pr = plane_rows(pl.ns);
-  // Output rows of a band are spread over the 16 waves, KMAX per thread
-  // (template steps 8..36).  The finalize of a band reads plane rows up to
-  // o0 + 16 KMAX (padding rows included, o0 <= arm_y is the top halo), and
-  // the band itself must fit the plane.
-  auto kstep = [](int rows_per_thread) {
-    for (int s : {8, 16, 24, 32, kKMax})  // kKMax = 34
-      if (rows_per_thread <= s) return s;
-    return -1;
-  };
-  int nb = 1, km = 8;
-  for (;; ++nb) {
-    const int ob = (pl.Y + nb - 1) / nb;
-    km = kstep((ob + kWaves - 1) / kWaves);
-    if (km < 0) continue;
-    const int rows = nb == 1 ? pl.Y : ob + 2 * pl.p.arm_y;
-    const int o0max = nb == 1 ? 0 : pl.p.arm_y;
-    if (rows <= pr && o0max + kWaves * km <= pr) break;
+// KMAX (output rows per k_match thread and base) of the instance for `rows`
+// of them with nbase bases; -1 when there is none.
+int match_kmax(int rows, int nbase) {
+  if (nbase == 2) {
+    for (int s : {4, 8, 12, 16, 18})
+      if (rows <= s) return s;
+  } else {
+    for (int s : {16, 36})
+      if (rows <= s) return s;
   }
-  pl.kmax = km;
-  pl.nbands = nb;
-  pl.nstrips = (pl.X + kTX - 1) / kTX;
+  return -1;
+}
+
+// Row bands of k_match with nbase bases a workgroup, nb at least.  The rows of
+// a band (halos included; the first and the last band have one) fit the plane
+// and the segment sums, and its window step, which reads plane rows up to
+// o0 + 16 KMAX (padding rows included, o0 <= arm_y is the top halo), stays in
+// the plane.
+struct Bands {
+  int n, kmax, rows, out;  // bands, KMAX, most rows of a band, its output rows
+  long total;              // rows of all bands
+};
+
+Bands match_bands(int Y, int arm_y, int ns, int nbase, int nb) {
+  const int pr = match_plane_rows(ns, nbase);
+  for (;; ++nb) {
+    const int ob = (Y + nb - 1) / nb, km = match_kmax((ob + kWaves - 1) / kWaves, nbase);
+    if (km < 0 || ob * (nb - 1) >= Y) continue;
+    int rows = 0;
+    long total = 0;
+    for (int b = 0; b < nb; ++b) {
+      const int r = std::min(Y, std::min(Y, (b + 1) * ob) + arm_y) - std::max(0, b * ob - arm_y);
+      rows = std::max(rows, r);
+      total += r;
+    }
+    const int o0max = nb == 1 ? 0 : arm_y;
+    if (rows <= kWaves * match_seg_rows(nbase) && rows + 1 <= pr && o0max + kWaves * km + 1 <= pr)
+      return Bands{nb, km, rows, ob, total};
+  }
+}
+
+// Whether bands of both bases exist at all: one output row between two halos,
+// and the window step of the smallest instance below one.
+bool bands_exist(int arm_y, int ns) {
+  const int pr = match_plane_rows(ns, 2);
+  return arm_y + kWaves * match_kmax(1, 2) + 1 <= pr && 2 * arm_y + 2 <= pr &&
+         2 * arm_y + 1 <= kWaves * match_seg_rows(2);
+}
+
+// The workgroups of D disparities in nchunk chunks (kernels.hip.h, MatchGrid).
+MatchGrid match_grid(const Plan& pl, int npair, int D0, int D1, int nchunk) {
+  MatchGrid g{};
+  g.nfull = (pl.X + kTX - 1) / kTX;
+  g.units = pl.nbands * npair * (3 - pl.nbase);
+  g.total = g.nfull * g.units * nchunk;
+  if (pl.nbase == 2) {
+    const int hi = match_slack_hi(pl.ns, std::max(pl.p.arm_x, pl.p.arm_x_r)), nd = D1 - D0;
+    for (int s = g.nfull; g.nextra < kMatchExtra; ++s) {
+      int c = 0;  // first chunk whose right-based strip s starts left of X
+      while (c < nchunk && s * kTX - match_delta(D0 + (c + 1) * nd / nchunk - 1, hi) >= pl.X) ++c;
+      if (c == nchunk) break;
+      g.first[g.nextra++] = c;
+      g.total += g.units * (nchunk - c);
+    }
+  }
+  g.per = (g.total + kXcds - 1) / kXcds;
+  return g;
+}
+
+// Modelled k_match time, in units of one band row of one disparity: every XCD
+// has g.per workgroups for its CUs (in rounds, since they are nearly equal),
+// each its set-up and drain (cost table, arms, key stores), and per disparity
+// the rows and the output rows' window step; then k_wta's pass over the keys.
+// The weights are fitted to timings of every chunk count with 1 to 8 bands at
+// 320x240, 640x480, 800x600, 1237x823, 1436x992 (also at full resolution with
+// arms 41 and 61), 2872x1984 and 4 x 1920x1080: the pick is within 4% of the
+// fastest k_match at each (a unit is about 19 ns).
+double match_time(const Plan& pl, const Bands& b, const MatchGrid& g, int nchunk, int num_cu) {
+  constexpr double kSetup = 300.0, kWindow = 0.7, kKeys = 0.85e-4;
+  const int cus = std::max(1, num_cu / kXcds), size = (pl.D + nchunk - 1) / nchunk;
+  const int rounds = (g.per + cus - 1) / cus;
+  return rounds * (kSetup + size * (b.rows + kWindow * b.out)) +
+         kKeys * nchunk * pl.npair * pl.X * pl.Y;
+}
+
+// Launch geometry: bands keep the k_match LDS plane, the segment sums and the
+// key registers within bounds; d-chunks, and more bands than needed, raise
+// the workgroup count to fill the CUs.  nbase: 2 both bases a workgroup where
+// that is the better form, 1 one base.
+void plan_geometry(Plan& pl, int num_cu, int forced_csize, int nbase) {
+  const int arm = std::max(pl.p.arm_x, pl.p.arm_x_r), arm_y = pl.p.arm_y;
+  // Both bases in one workgroup, with the fewest 128-column sub-passes that
+  // leave their strips room for chunks of kMinChunk disparities, unless the
+  // halo rows of the lower bands outweigh the shared evaluation: the two
+  // forms' instructions per band row are about 26 and 2 x 23
+  constexpr int kMinChunk = 6;
+  constexpr double kBothRows = 1.7;  // rows of both bases that cost as much as two of one base
+  const int ns1 = (66 + 2 * arm + 127) / 128;
+  auto cap_of = [&](int ns) { return match_slack_lo(arm) + match_slack_hi(ns, arm) + 1; };
+  int ns2 = 1;
+  while (ns2 < 3 && (match_slack_hi(ns2, arm) < 0 || cap_of(ns2) < std::min(kMinChunk, pl.D))) ++ns2;
+  pl.nbase = 1;
+  pl.ns = ns1;
+  pl.ccap = pl.D;
+  const Bands one = match_bands(pl.Y, arm_y, ns1, 1, 1);
+  if (nbase == 2 && bands_exist(arm_y, ns2) &&
+      (double)match_bands(pl.Y, arm_y, ns2, 2, 1).total * ns2 <= kBothRows * one.total * ns1) {
+    pl.nbase = 2;
+    pl.ns = ns2;
+    pl.ccap = cap_of(ns2);
+  }
+  // bands and d-chunks with the shortest modelled time (ties keep the fewer
+  // bands and the larger chunks), or the chunk size stereo_autotune chose
+  double best_t = 1e300;
+  constexpr int kMoreBands = 6;
+  int nb = 1, best_nb = 1;
+  for (int k = 0; k < kMoreBands && nb <= pl.Y; ++k, ++nb) {
+    const Bands b = match_bands(pl.Y, arm_y, pl.ns, pl.nbase, nb);
+    nb = pl.nbands = b.n;
+    int n0 = (pl.D + pl.ccap - 1) / pl.ccap, n1 = std::min(pl.D, std::max(n0, 64));
+    if (forced_csize > 0) n0 = n1 = std::max(n0, (pl.D + forced_csize - 1) / forced_csize);
+    for (int n = n0; n <= n1; ++n) {
+      const MatchGrid g = match_grid(pl, pl.npair, 0, pl.D, n);
+      if (g.total > 16L * num_cu && best_t < 1e300) break;
+      const double t = match_time(pl, b, g, n, num_cu);
+      if (t < best_t - 1e-9) {
+        best_t = t;
+        best_nb = b.n;
+        pl.kmax = b.kmax;
+        pl.brows = b.rows;
+        pl.nchunk = n;
+      }
+    }
+  }
+  pl.nbands = best_nb;
+  pl.csize = (pl.D + pl.nchunk - 1) / pl.nchunk;
   // pk padding covers every column a k_match lane loads: x0 - hx - D at the
-  // left, x0 - hx + 128 NS - 1 + D < X + 128 NS + D at the right (one more in
-  // the shifted copy); pad and the pitch are even, so the pair of columns
-  // from an even column is an aligned 32-bit word
+  // left, x0 - hx + 128 NS + D (one base; both: x0 - hx + 128 NS with x0 <
+  // X + D) at the right, one more in the shifted copy; pad and the pitch are
+  // even, so the pair of columns from an even column is an aligned 32-bit word
   pl.pad = ((128 * pl.ns + pl.D + 2) + 3) & ~3;
   pl.XP = (pl.X + 2 * pl.pad + 63) & ~63;
-  pl.XA = pl.nstrips * kTX;
-  const int groups = pl.nstrips * pl.nbands * 2 * pl.npair;
-  // d-chunks of csize disparities (the last one the remainder): the size
-  // with the shortest modelled k_match time, or the one stereo_autotune chose
-  const int rows = pl.nbands == 1 ? pl.Y : std::min(pl.Y, (pl.Y + pl.nbands - 1) / pl.nbands + 2 * pl.p.arm_y);
-  pl.csize = forced_csize > 0 ? std::min(forced_csize, pl.D) : best_chunk_size(groups, pl.D, rows, num_cu);
-  pl.nchunk = (pl.D + pl.csize - 1) / pl.csize;
+  pl.XA = (pl.X + kTX - 1) / kTX * kTX;
 }
 
 // The d-chunk size stereo_autotune chose for this shape and parameters, or 0.
@@ -245,7 +349,8 @@ struct PlanBytes {
 PlanBytes plan_bytes(const Plan& pl) {
   auto al = [](size_t b) { return (b + 255) & ~size_t(255); };
   const size_t n = (size_t)pl.X * pl.Y, npair = pl.npair;
-  const size_t npk = (size_t)2 * npair * pl.Y * pl.XP, nar = (size_t)2 * npair * pl.Y * pl.XA;
+  const size_t npk = (size_t)2 * npair * pl.Y * pl.XP;
+  const size_t nar = (size_t)2 * npair * pl.Y * pl.XA;
   const size_t nk = pl.nk;
   PlanBytes b;
   b.pk = 2 * npk * 2;
@@ -256,11 +361,20 @@ PlanBytes plan_bytes(const Plan& pl) {
   return b;
 }
 
+// Launch geometries of a shape, the first the preferred one: where scratch is
+// bounded, the later ones need less of it (fewer chunk keys; one base a
+// workgroup, whose chunks may hold all disparities).
+struct Form {
+  int nbase;
+  bool fewest_chunks;
+};
+constexpr Form kForms[] = {{2, false}, {2, true}, {1, false}, {1, true}};
+
 // Shape, tables and launch geometry of a plan (host side only, no device
 // memory); rejects shapes whose pixel or arm planes the kernels' 32-bit
 // buffer offsets cannot address.
 int plan_setup(stereo_ctx* c, Plan& pl, int W, int H, int Dmax, const stereo_params& p,
-               int npair, int forced_csize) {
+               int npair, const Form& form) {
   pl.W = W; pl.H = H; pl.Dmax = Dmax; pl.npair = npair;
   if (full_res(p)) {
     pl.X = W; pl.Y = H; pl.D = Dmax;
@@ -271,7 +385,8 @@ int plan_setup(stereo_ctx* c, Plan& pl, int W, int H, int Dmax, const stereo_par
   pl.p = p;
   build_tables(p, pl.lut_ad, pl.lut_mc);
   pl.cmax = pl.lut_ad[255] + pl.lut_mc[6];
-  plan_geometry(pl, c->num_cu, forced_csize);
+  plan_geometry(pl, c->num_cu,
+                form.fewest_chunks ? pl.D : tuned_csize(c, W, H, Dmax, npair, p), form.nbase);
   pl.nk = (int)(((size_t)pl.X * pl.Y + 63) & ~size_t(63));
   const PlanBytes b = plan_bytes(pl);
   if (b.pk >= (size_t(1) << 32) || b.arms >= (size_t(1) << 32))
@@ -300,7 +415,6 @@ void plan_carve_and_init(Plan& pl, void* base, hipStream_t s) {
   TabArgs t{};
   for (int i = 0; i < 256; ++i) t.ad[i] = pl.lut_ad[i];
   for (int i = 0; i < 7; ++i) t.mc[i] = pl.lut_mc[i];
-  t.cmax = (uint16_t)pl.cmax;
   // pk, arms and xoff are adjacent in the block: one cleared range covers them
   const size_t nzero = (size_t)(reinterpret_cast<char*>(pl.xoff) + b.arms -
                                 reinterpret_cast<char*>(pl.pk)) / 4;
@@ -311,24 +425,32 @@ void plan_carve_and_init(Plan& pl, void* base, hipStream_t s) {
 
 int make_plan(stereo_ctx* c, int W, int H, int Dmax, const stereo_params& p, int npair,
               hipStream_t s, Plan** out) {
-  Plan* pl = new Plan();
-  int rc = plan_setup(c, *pl, W, H, Dmax, p, npair, tuned_csize(c, W, H, Dmax, npair, p));
+  // the first form whose scratch the cap and the device allow
+  Plan* pl = nullptr;
+  size_t bytes = 0;
+  hipError_t e = hipSuccess;
+  int rc = 0;
+  for (const Form& form : kForms) {
+    delete pl;
+    pl = new Plan();
+    rc = plan_setup(c, *pl, W, H, Dmax, p, npair, form);
+    if (rc) break;
+    bytes = plan_bytes(*pl).total;
+    if (c->mem_cap && c->used + bytes > c->mem_cap) {
+      rc = fail(c, STEREO_ENOMEM, "plan needs %zu bytes, cap %zu, in use %zu", bytes, c->mem_cap,
+                c->used);
+      continue;
+    }
+    e = hipMalloc(&pl->block, bytes);
+    if (e == hipSuccess) break;
+    (void)hipGetLastError();
+    rc = fail(c, STEREO_ENOMEM, "hipMalloc(%zu): %s", bytes, hipGetErrorString(e));
+  }
   if (rc) {
     delete pl;
     return rc;
   }
-  const size_t bytes = plan_bytes(*pl).total;
-  if (c->mem_cap && c->used + bytes > c->mem_cap) {
-    delete pl;
-    return fail(c, STEREO_ENOMEM, "plan needs %zu bytes, cap %zu, in use %zu", bytes, c->mem_cap,
-                c->used);
-  }
-  hipError_t e = hipMalloc(&pl->block, bytes);
-  if (e != hipSuccess) {
-    delete pl;
-    (void)hipGetLastError();
-    return fail(c, STEREO_ENOMEM, "hipMalloc(%zu): %s", bytes, hipGetErrorString(e));
-  }
+  c->err.clear();
   pl->bytes = bytes;
   // set-up on the stream the plan serves: later work on that stream follows
   // it, and no other stream or slot is stalled
@@ -431,59 +553,71 @@ void set_tuned(stereo_ctx* c, int W, int H, int Dmax, int npair, const stereo_pa
   c->tuned.push_back(Tuned{W, H, Dmax, npair, p, csize});
 }
 
-MatchArgs match_args(const Plan& pl, int dlo, int dhi, int csize) {
+MatchArgs match_args(const Plan& pl, int npair, int dlo, int dhi, int nchunk) {
   MatchArgs a{};
   a.pk = pl.pk; a.arms = pl.arms; a.xoff = pl.xoff; a.tab = pl.tab; a.keys = pl.keys;
   a.X = pl.X; a.Y = pl.Y; a.XP = pl.XP; a.pad = pl.pad; a.XA = pl.XA; a.nk = pl.nk;
-  a.arm_x = pl.p.arm_x; a.arm_x_r = pl.p.arm_x_r; a.arm_y = pl.p.arm_y; a.dbits = pl.dbits;
+  a.arm = std::max(pl.p.arm_x, pl.p.arm_x_r); a.arm_y = pl.p.arm_y; a.dbits = pl.dbits;
+  a.cmax = pl.cmax;
   a.copy_bytes = (uint32_t)((size_t)2 * pl.npair * pl.Y * pl.XP * 2);
-  a.pk_bytes = 2 * a.copy_bytes;
-  a.arms_bytes = (uint32_t)((size_t)2 * pl.npair * pl.Y * pl.XA * 4);
+  // the slack rows are the planes that follow in the plan's block, which are
+  // always longer (carved in this order: pk, arms, xoff, tab, keys, ...)
+  const PlanBytes b = plan_bytes(pl);
+  auto bound = [](size_t n) { return (uint32_t)std::min(n, (size_t(1) << 32) - 1); };
+  a.pk_bytes = bound(b.pk + (size_t)kMatchSlackRows * pl.XP * 2);
+  a.arms_bytes = bound(b.arms + (size_t)kMatchSlackRows * pl.XA * 4);
   a.nbands = pl.nbands; a.dlo = dlo; a.dhi = dhi;
-  a.csize = std::max(1, std::min(csize, dhi - dlo));
-  a.nchunk = (dhi - dlo + a.csize - 1) / a.csize;
+  a.nchunk = nchunk;
+  a.grid = match_grid(pl, npair, dlo, dhi, nchunk);
   return a;
 }
 
 // k_match with KMAX = KM: its LDS block holds the plane rows the plan's
 // bands write (band rows + 1) or its window step reads (o0 + 16 KMAX + 1),
 // whichever is more; the rest of the CU's LDS stays free for other streams.
-template <int NS, int KM, bool DBG>
+template <int NS, int NB, int KM>
 void launch_match_km(const Plan& pl, const MatchArgs& a, dim3 grid, hipStream_t s) {
-  const int brows = pl.nbands == 1 ? pl.Y : std::min(pl.Y, (pl.Y + pl.nbands - 1) / pl.nbands + 2 * pl.p.arm_y);
   const int o0max = pl.nbands == 1 ? 0 : pl.p.arm_y;
-  const int rows = std::max(brows, o0max + kWaves * KM) + 1;
+  const size_t lds = (size_t)match_lds_bytes(NS, NB, std::max(pl.brows, o0max + kWaves * KM) + 1);
   // dynamic LDS beyond the default limit needs the attribute (set once per
   // instance); were it refused, the launch below fails and run() reports
   // that launch's error
-  static const hipError_t attr = hipFuncSetAttribute(
-      reinterpret_cast<const void*>(&k_match<NS, KM, DBG>),
-      hipFuncAttributeMaxDynamicSharedMemorySize, kLdsBytes - kMatchTabBytes);
-  (void)attr;
-  hipLaunchKernelGGL((k_match<NS, KM, DBG>), grid, dim3(kThreads),
-                     (size_t)match_lds_bytes(NS, rows), s, a);
-}
-
-template <int NS, bool DBG>
-void launch_match_k(const Plan& pl, const MatchArgs& a, dim3 grid, hipStream_t s) {
-  switch (pl.kmax) {
-    case 8: launch_match_km<NS, 8, DBG>(pl, a, grid, s); break;
-    case 16: launch_match_km<NS, 16, DBG>(pl, a, grid, s); break;
-    case 24: launch_match_km<NS, 24, DBG>(pl, a, grid, s); break;
-    case 32: launch_match_km<NS, 32, DBG>(pl, a, grid, s); break;
-    default: launch_match_km<NS, kKMax, DBG>(pl, a, grid, s); break;
+  auto allow = [](const void* f) {
+    return hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, kLdsBytes - kMatchTabBytes);
+  };
+  if (a.dbg_cost) {
+    static const hipError_t attr = allow(reinterpret_cast<const void*>(&k_match<NS, NB, KM, true>));
+    (void)attr;
+    hipLaunchKernelGGL((k_match<NS, NB, KM, true>), grid, dim3(kThreads), lds, s, a);
+  } else {
+    static const hipError_t attr = allow(reinterpret_cast<const void*>(&k_match<NS, NB, KM, false>));
+    (void)attr;
+    hipLaunchKernelGGL((k_match<NS, NB, KM, false>), grid, dim3(kThreads), lds, s, a);
   }
 }
 
-void launch_match(const Plan& pl, MatchArgs a, int npair, hipStream_t s) {
-  a.nstrips = pl.nstrips;
-  a.ngroups = pl.nstrips * pl.nbands * 2 * npair;
-  dim3 grid((unsigned)(((a.ngroups + kXcds - 1) / kXcds) * kXcds * a.nchunk));
-  const bool dbg = a.dbg_cost != nullptr;
+template <int NS>
+void launch_match_k(const Plan& pl, const MatchArgs& a, dim3 grid, hipStream_t s) {
+  if (pl.nbase == 1) {
+    if (pl.kmax == 16) launch_match_km<NS, 1, 16>(pl, a, grid, s);
+    else launch_match_km<NS, 1, 36>(pl, a, grid, s);
+    return;
+  }
+  switch (pl.kmax) {
+    case 4: launch_match_km<NS, 2, 4>(pl, a, grid, s); break;
+    case 8: launch_match_km<NS, 2, 8>(pl, a, grid, s); break;
+    case 12: launch_match_km<NS, 2, 12>(pl, a, grid, s); break;
+    case 16: launch_match_km<NS, 2, 16>(pl, a, grid, s); break;
+    default: launch_match_km<NS, 2, 18>(pl, a, grid, s); break;
+  }
+}
+
+void launch_match(const Plan& pl, const MatchArgs& a, hipStream_t s) {
+  dim3 grid((unsigned)(kXcds * a.grid.per));
   switch (pl.ns) {
-    case 1: dbg ? launch_match_k<1, true>(pl, a, grid, s) : launch_match_k<1, false>(pl, a, grid, s); break;
-    case 2: dbg ? launch_match_k<2, true>(pl, a, grid, s) : launch_match_k<2, false>(pl, a, grid, s); break;
-    default: dbg ? launch_match_k<3, true>(pl, a, grid, s) : launch_match_k<3, false>(pl, a, grid, s); break;
+    case 1: launch_match_k<1>(pl, a, grid, s); break;
+    case 2: launch_match_k<2>(pl, a, grid, s); break;
+    default: launch_match_k<3>(pl, a, grid, s); break;
   }
 }
 
@@ -525,7 +659,7 @@ int run(stereo_ctx* c, Plan& pl, const PairPtrs& pp, int npair, bool keep, bool 
                      pl.XP, pl.pad, pl.XA, nullptr, nullptr, pl.arms, pl.xoff, pl.pk,
                      (size_t)2 * pl.npair * Y * pl.XP);
   mark(2);
-  launch_match(pl, match_args(pl, 0, pl.D, pl.csize), npair, s);
+  launch_match(pl, match_args(pl, npair, 0, pl.D, pl.nchunk), s);
   mark(3);
   hipLaunchKernelGGL(k_wta, dim3((pl.nk + 1023) / 1024, npair), dim3(256), 0, s, pl.keys,
                      pl.nchunk, pl.nk, pl.dbits, pl.disp, keep ? pl.mincost : nullptr);
@@ -680,7 +814,7 @@ int stereo_autotune(stereo_ctx* c, const uint8_t* const* left, const uint8_t* co
   probe.X = full_res(p) ? W : (W + 1) / 2;
   probe.Y = full_res(p) ? H : (H + 1) / 2;
   probe.D = full_res(p) ? Dmax : (Dmax + 1) / 2;
-  plan_geometry(probe, c->num_cu, 0);
+  plan_geometry(probe, c->num_cu, 0, 2);
   std::vector<int> cand{probe.csize};
   for (int k = 1; k <= std::min(probe.D, 32); ++k) {
     const int cs = (probe.D + k - 1) / k;
@@ -765,9 +899,14 @@ int stereo_disparity_noalloc(stereo_ctx* c, const uint8_t* left, const uint8_t* 
   // and tables are host arithmetic, the set-up (padding cleared, cost table
   // written) is a kernel on the caller's stream
   Plan pl{};
-  rc = plan_setup(c, pl, W, H, Dmax, p, 1, tuned_csize(c, W, H, Dmax, 1, p));
-  if (rc) return rc;
-  const size_t bytes = plan_bytes(pl).total;
+  size_t bytes = 0;
+  for (const Form& form : kForms) {
+    pl = Plan{};
+    rc = plan_setup(c, pl, W, H, Dmax, p, 1, form);
+    if (rc) return rc;
+    bytes = plan_bytes(pl).total;
+    if (bytes <= kNoallocBytes) break;
+  }
   if (bytes > kNoallocBytes)
     return fail(c, STEREO_EINVAL, "%dx%d Dmax %d needs %zu bytes of scratch; the fixed array "
                 "holds %zu (use stereo_disparity)", W, H, Dmax, bytes, kNoallocBytes);
@@ -859,11 +998,11 @@ int stereo_get_intermediate(stereo_ctx* c, int which, int d, void* dst, size_t b
       }
       // one-disparity run of the fused kernel on pair 0 with the debug planes
       // of the wanted base on; it overwrites the first d-chunk keys only
-      MatchArgs a = match_args(*pl, d, d + 1, 1);
+      MatchArgs a = match_args(*pl, 1, d, d + 1, 1);
       a.dbg_cost = pl->dbg_cost; a.dbg_cax = pl->dbg_cax; a.dbg_ca = pl->dbg_ca;
       a.dbg_base = (which == STEREO_I_COST_R_D || which == STEREO_I_CAX_R_D ||
                     which == STEREO_I_CA_R_D) ? 1 : 0;
-      launch_match(*pl, a, 1, stream);
+      launch_match(*pl, a, stream);
       HIP_TRY(c, hipGetLastError());
       HIP_TRY(c, hipStreamSynchronize(stream));
       const void* src = cost ? (const void*)pl->dbg_cost

@@ -186,6 +186,48 @@ def test_maximum_sides(sm, ctx, W, H, dmax, full):
     full_parity(sm, ctx, pair.left, pair.right, dmax, p, label=f"max {W}x{H}")
 
 
+@pytest.mark.parametrize("W,H,dmax,kw", [
+    (70, 128, 20, {}), (70, 130, 20, {}), (66, 256, 24, {}), (66, 384, 24, {}),   # output rows
+    (66, 514, 24, {}),                                                            # per thread
+    (90, 576, 20, {}), (90, 578, 20, {}), (90, 1158, 16, {}),   # one band of 288 rows, two, three
+    (126, 60, 120, {}), (128, 61, 127, {}), (130, 60, 44, {}), (254, 40, 250, {}),  # extra strips
+    (150, 80, 40, dict(arm_x=29)), (150, 80, 40, dict(arm_x=30)), (150, 80, 40, dict(arm_x=31)),
+    (150, 80, 40, dict(arm_x=9, arm_x_r=26)),
+    (150, 80, 40, dict(arm_x=93, arm_y=9, cost_scale=256)),     # two sub-passes, then three
+    (150, 80, 40, dict(arm_x=94, arm_y=9, cost_scale=256)),
+    (90, 700, 16, dict(arm_x=5, arm_y=64, cost_scale=512)),     # both bases a workgroup
+    (90, 700, 16, dict(arm_x=5, arm_y=127, cost_scale=256)),    # one base
+    (90, 1100, 16, dict(arm_x=40, arm_y=127, cost_scale=64)),   # one base, two sub-passes
+])
+def test_match_launch_forms(sm, ctx, W, H, dmax, kw):
+    """Both sides of every edge at which k_match's launch changes: output rows
+    per thread, rows of a band, strips of the two bases, sub-passes, bases."""
+    pair = make_pair(W, H, dmax, segments=4, seed=W + H + dmax)
+    full_parity(sm, ctx, pair.left, pair.right, dmax, keep_params(sm, **kw), label=str(kw))
+
+
+def test_scratch_cap_keeps_the_map(sm):
+    """A context whose cap holds less and less scratch falls back to forms with
+    fewer chunk keys and gives the same map until it refuses."""
+    pair = make_pair(640, 480, 64, segments=6, seed=77)
+    lt, rt = torch.from_numpy(pair.left).cuda(), torch.from_numpy(pair.right).cuda()
+    exp = oracle.disparity(pair.left, pair.right, 64)["out"]
+    cap, served = 32 << 20, 0
+    while True:
+        c = sm.Stereo(0, mem_cap=cap)
+        try:
+            assert_same(f"cap {cap}", c.disparity(lt, rt, 64).cpu().numpy(), exp)
+        except sm.StereoError as e:
+            assert e.code == sm.binding.ENOMEM
+            break
+        finally:
+            c.close()
+        served = cap
+        cap = cap * 9 // 10
+    # one chunk's keys, the planes and the cost table: 240 x 320 pixels
+    assert 0 < served < 5 << 20
+
+
 def test_largest_arms(sm, ctx):
     """Both arms at their cap of 127 (three 128-column sub-passes of the row
     pass; cost scale small enough for the 2^24 window-sum bound)."""

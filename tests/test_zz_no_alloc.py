@@ -108,6 +108,21 @@ def test_noalloc_makes_no_device_allocation_and_refuses_oversize(sm):
     ctx.close()
 
 
+def test_noalloc_shape_that_fits_with_fewer_chunks_only(sm):
+    """2000x1200 Dmax 300: the planes with the preferred number of chunk keys
+    exceed the fixed array, those with fewer fit; the map is the same."""
+    say("[noalloc] 2000x1200 Dmax 300")
+    pair = make_pair(2000, 1200, 300, segments=20, seed=45)
+    lt, rt = dev(pair.left), dev(pair.right)
+    out = torch.empty((1200, 2000), dtype=torch.int16, device="cuda")
+    ctx = sm.Stereo(0)
+    assert call_noalloc(sm, ctx, lt, rt, 300, out) == 0, ctx.last_error()
+    ref = ctx.disparity(lt, rt, 300)
+    torch.cuda.synchronize()
+    assert np.array_equal(out.cpu().numpy(), ref.cpu().numpy())
+    ctx.close()
+
+
 def test_noalloc_under_graph_capture(sm):
     """The caller this entry point is for: code under graph capture.  The call
     is captured in a HIP graph and replayed three times; between replays an
