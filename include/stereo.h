@@ -231,7 +231,7 @@ typedef struct stereo_soft_params {
   int32_t color_delta;  /* delta of the frozen arms (Sec. III-C), 0..256             */
   int32_t arm_x;        /* per-side cap of m, n; 0..31                               */
   int32_t arm_y;        /* per-side cap of M, N; 0..63                               */
-  int32_t slab;         /* disparities recomputed per backward slab; 0 = automatic   */
+  int32_t slab;         /* disparities per backward slab; 0 = automatic              */
   uint32_t flags;       /* STEREO_SOFT_F_*                                           */
 } stereo_soft_params;
 
@@ -246,10 +246,10 @@ typedef struct stereo_soft_params {
  * forward also saved its weights (SAVE_WEIGHTS) for the same left, right and
  * lambdas pointers, the backward forms dL/dCA from them instead of
  * recomputing the aggregate; lambdas must then hold the forward's values too.
- * SAVE_WEIGHTS, for stereo_soft_forward: keep the softmax weight of every
- * pixel and disparity (n * X * Y * D floats of the context's scratch, in the
- * planes the backward's slabs use; ignored when one slab cannot hold all D)
- * for a following backward with REUSE_FEATURES.  Any later forward or
+ * SAVE_WEIGHTS, for stereo_soft_forward: keep the softmax weight, or the
+ * aggregate, of every pixel and disparity (n * X * Y * D floats of the
+ * context's scratch; ignored when a slab is given that does not hold all D,
+ * or the scratch or 4 GiB do not) for a following backward with REUSE_FEATURES.  Any later forward or
  * backward with other inputs on the same context, stream and parameters
  * replaces or drops them. */
 #define STEREO_SOFT_F_REUSE_FEATURES 1u
@@ -269,10 +269,12 @@ int stereo_soft_forward(stereo_ctx* ctx, const float* left, const float* right, 
  * writes g_left, g_right (device float [n][H][W][3]) and g_lambdas (device
  * float[2]: dL/dlambda_AD, dL/dlambda_census), all overwritten, not
  * accumulated.  d_hat and lse2 are the forward's outputs for the same
- * inputs.  The adjoint recomputes the aggregate for slabs of disparities
- * and runs the window sums backward (difference arrays and prefix sums over
- * the frozen arms); no cost volume is stored.  Scratch grows with the slab:
- * 2 * n * X * Y * 4 bytes per disparity of a slab. */
+ * inputs.  The adjoint takes the aggregate that the forward saved, or computes
+ * it again, and runs the window sums backward over slabs of disparities
+ * (difference arrays and prefix sums over the frozen arms); no cost volume is
+ * stored.  Scratch: n * X * Y * 4 bytes per disparity, and as much again per
+ * disparity of a slab; where that does not fit, the planes shrink to a slab's
+ * and then the slabs. */
 int stereo_soft_backward(stereo_ctx* ctx, const float* left, const float* right, int n, int W,
                          int H, int Dmax, const float* lambdas, const stereo_soft_params* params,
                          const float* d_hat, const float* lse2, const float* g_dhat,

@@ -17,7 +17,11 @@ using namespace stereo_dev;
 namespace stereo_host {
 
 constexpr int kSoftMaxPairs = 64;
-constexpr size_t kSlabBudget = size_t(1) << 30;  // dL/dCA + dL/dCA_x planes of a slab
+// The weight and dL/dCA_x planes of a plan: at most this many bytes each, so
+// that 32-bit offsets reach every weight (k_soft_tcolw).
+constexpr size_t kPlanesMost = (size_t(1) << 32) - 1;
+// A slab's weight and dL/dCA_x planes, where the caller sets no slab.
+constexpr size_t kSlabBudget = size_t(1) << 30;
 
 struct SoftPlan {
   int n = 0, W = 0, H = 0, Dmax = 0, X = 0, Y = 0, D = 0;
@@ -26,8 +30,9 @@ struct SoftPlan {
   int csize = 1, nchunk = 0;   // k_soft_agg d-chunk size and forward chunk count
   int XS = 0, pads = 0, XA = 0;
   int fxk = 18;        // fixed-point bits of the costs
+  int nw = 1;          // disparities the weight planes hold: all D, or a slab's
   int nds = 1;         // disparities per backward slab
-  int nbands_tr = 0;   // k_soft_tr bands of kSoftBR rows
+  bool ca = false;     // a forward saves CA, not e_d (several slabs)
   size_t lam_count = 0;
   size_t bytes = 0;
   void* block = nullptr;
@@ -38,7 +43,7 @@ struct SoftPlan {
   float* inv_size = nullptr;   // [n][Y][X]
   float2* part = nullptr;      // [n][nchunk][Y][X]
   float4* pc = nullptr;        // [n][Y][X]
-  float* gca = nullptr;        // [nds][n][Y][X]
+  float* wts = nullptr;        // [nw][n][Y][X] e_d or CA
   float* gcax = nullptr;       // [nds][n][Y][X] dL/dCA_x
   float* gr_part = nullptr;    // [n][nstrips][Y][WP] right-gradient partials of a slab
   int WP = 0;                  // 64 + nds - 1 columns per partial row
@@ -47,9 +52,9 @@ struct SoftPlan {
   // images of the last feature pass on this plan (STEREO_SOFT_F_REUSE_FEATURES)
   const float* feat_left = nullptr;
   const float* feat_right = nullptr;
-  // inputs of the last forward, when it saved its weights e_d in the gca
-  // planes (STEREO_SOFT_F_SAVE_WEIGHTS, all D in one slab); any other
-  // forward, and a backward that recomputes the slabs, clears wts_valid
+  // inputs of the last forward, when it saved its weights e_d in the weight
+  // planes (STEREO_SOFT_F_SAVE_WEIGHTS, planes of all D); any other forward,
+  // and a backward that recomputes the weights, clears wts_valid
   bool wts_valid = false;
   const float* wts_left = nullptr;
   const float* wts_right = nullptr;
@@ -100,20 +105,18 @@ int soft_checks(stereo_ctx* c, int n, int W, int H, int Dmax, const stereo_soft_
   return 0;
 }
 
-int make_soft_plan(stereo_ctx* c, int n, int W, int H, int Dmax, const stereo_soft_params& p,
-                   hipStream_t s, SoftPlan** out) {
-  SoftPlan* pl = new SoftPlan();
-  pl->n = n; pl->W = W; pl->H = H; pl->Dmax = Dmax; pl->p = p;
-  pl->X = (W + 1) / 2; pl->Y = (H + 1) / 2; pl->D = (Dmax + 1) / 2;
-  const int X = pl->X, Y = pl->Y, D = pl->D;
+// Shape and launch geometry of a plan (host side only), for weight planes of nw
+// disparities and backward slabs of nds.
+void soft_geometry(SoftPlan& pl, int num_cu) {
+  const stereo_soft_params& p = pl.p;
+  pl.X = (pl.W + 1) / 2; pl.Y = (pl.H + 1) / 2; pl.D = (pl.Dmax + 1) / 2;
+  const int X = pl.X, Y = pl.Y, D = pl.D;
   // fixed point: (2 arm_x + 1)(2 arm_y + 1) costs of at most 2 stay below 2^31
   const double cells = (2.0 * p.arm_x + 1) * (2.0 * p.arm_y + 1);
-  pl->fxk = (int)std::floor(std::log2(2147483648.0 / (2.0 * cells + 1.0)));
-  pl->fxk = std::min(pl->fxk, 22);
+  pl.fxk = (int)std::floor(std::log2(2147483648.0 / (2.0 * cells + 1.0)));
+  pl.fxk = std::min(pl.fxk, 22);
   // k_soft_agg: one row-buffer pass (arm_x <= 31), bands whose output rows
   // fit 16 per thread and whose rows fit the plane
-  pl->ns = 1;
-  const int pr = plane_rows(1);
   int nb = 1, km = 8;
   for (;; ++nb) {
     const int ob = (Y + nb - 1) / nb;
@@ -122,32 +125,40 @@ int make_soft_plan(stereo_ctx* c, int n, int W, int H, int Dmax, const stereo_so
     km = per <= 8 ? 8 : 16;
     const int rows = nb == 1 ? Y : ob + 2 * p.arm_y;
     const int o0max = nb == 1 ? 0 : p.arm_y;
-    if (rows <= pr && o0max + kWaves * km <= pr) break;
+    if (rows <= kAggRows && o0max + kWaves * km <= kAggRows) break;
   }
-  pl->nbands = nb;
-  pl->kmax = km;
-  pl->rows = nb == 1 ? Y : std::min(Y, (Y + nb - 1) / nb + 2 * p.arm_y);
-  pl->nstrips = (X + kTX - 1) / kTX;
-  pl->XA = pl->nstrips * kTX;
+  pl.nbands = nb;
+  pl.kmax = km;
+  pl.rows = nb == 1 ? Y : std::min(Y, (Y + nb - 1) / nb + 2 * p.arm_y);
+  pl.nstrips = (X + kTX - 1) / kTX;
+  pl.XA = pl.nstrips * kTX;
   // row loads reach x0 - hx - d .. x0 - hx + 127 for every strip x0
-  pl->pads = ((128 * pl->ns + D + 2) + 1) & ~1;
-  pl->XS = pl->pads + pl->XA + 128 * pl->ns + 2;
-  pl->XS = (pl->XS + 1) & ~1;
-  const int groups = pl->nstrips * pl->nbands * n;
-  pl->csize = best_chunk_size(groups, D, pl->rows, c->num_cu, D);
-  pl->nchunk = (D + pl->csize - 1) / pl->csize;
-  const size_t npix = (size_t)X * Y;
-  // at most 128 disparities per slab (k_soft_tr's LDS rows of right gradients)
-  pl->nds = p.slab > 0 ? std::min(p.slab, D)
-                       : (int)std::max<size_t>(1, std::min<size_t>(D, kSlabBudget / (2 * n * npix * 4)));
-  pl->nds = std::min(pl->nds, kTrMaxWP - 63);
-  pl->WP = 64 + pl->nds - 1;
-  pl->nbands_tr = (Y + kSoftBR - 1) / kSoftBR;
-  const int nslab = (D + pl->nds - 1) / pl->nds;
-  pl->lam_count = (size_t)nslab * n * pl->nstrips * pl->nbands_tr;
+  pl.pads = ((128 + D + 2) + 1) & ~1;
+  pl.XS = (pl.pads + pl.XA + 128 + 2 + 1) & ~1;
+  const int groups = pl.nstrips * pl.nbands * pl.n;
+  pl.csize = best_chunk_size(groups, D, pl.rows, num_cu, D);
+  pl.nchunk = (D + pl.csize - 1) / pl.csize;
+}
 
+// Device bytes of a plan with weight planes of nw disparities and slabs of nds.
+size_t soft_bytes(const SoftPlan& pl, int nw, int nds) {
   auto al = [](size_t b) { return (b + 255) & ~size_t(255); };
-  const size_t nimg = 2 * (size_t)n;
+  const size_t n = pl.n, nimg = 2 * n, Y = pl.Y, npix = (size_t)pl.X * Y;
+  const size_t nslab = (pl.D + nds - 1) / nds;
+  return al(nimg * npix * 4) + al(nimg * npix) + al(nimg * Y * pl.XA * 4) +
+         al(nimg * Y * pl.XS * 8) + al(n * npix * 4) + al(n * pl.nchunk * npix * 8) +
+         al(n * npix * 16) + al(nw * n * npix * 4) + al(nds * n * npix * 4) +
+         al(nimg * npix * 4) + al(nslab * n * pl.nstrips * ((Y + kSoftBR - 1) / kSoftBR) * 8) +
+         al(n * pl.nstrips * Y * (64 + nds - 1) * 4);
+}
+
+int make_soft_plan(stereo_ctx* c, int n, int W, int H, int Dmax, const stereo_soft_params& p,
+                   hipStream_t s, SoftPlan** out) {
+  SoftPlan* pl = new SoftPlan();
+  pl->n = n; pl->W = W; pl->H = H; pl->Dmax = Dmax; pl->p = p;
+  soft_geometry(*pl, c->num_cu);
+  const int X = pl->X, Y = pl->Y, D = pl->D;
+  const size_t npix = (size_t)X * Y, nimg = 2 * (size_t)n;
   // k_soft_agg addresses the pixel and arm planes through 32-bit buffer
   // offsets
   if (nimg * Y * pl->XS * 8 >= (size_t(1) << 32) || nimg * Y * pl->XA * 4 >= (size_t(1) << 32)) {
@@ -155,22 +166,45 @@ int make_soft_plan(stereo_ctx* c, int n, int W, int H, int Dmax, const stereo_so
     return fail(c, STEREO_EINVAL, "%d pairs of %dx%d exceed the 4 GiB pixel or arm planes of the "
                 "soft head; pass fewer pairs per call", n, W, H);
   }
-  size_t bytes = al(nimg * npix * 4) + al(nimg * npix) +
-                 al(nimg * Y * pl->XA * 4) + al(nimg * Y * pl->XS * 8) + al(n * npix * 4) +
-                 al((size_t)n * pl->nchunk * npix * 8) + al(n * npix * 16) +
-                 2 * al((size_t)pl->nds * n * npix * 4) + al(nimg * npix * 4) +
-                 al(pl->lam_count * 8) + al((size_t)n * pl->nstrips * Y * pl->WP * 4);
-  if (c->mem_cap && c->used + bytes > c->mem_cap) {
-    delete pl;
-    return fail(c, STEREO_ENOMEM, "soft plan needs %zu bytes, cap %zu, in use %zu", bytes,
+  // the slab of kSlabBudget, or the caller's (at most 128 disparities: k_soft_tr's
+  // LDS rows of right gradients), and weight planes of all D when they can be
+  // addressed and the caller sets no slab: the backward then computes no CA
+  // again.  One slab saves e_d; the terms of several are formed from CA itself,
+  // p_d = 2^{-CA w - log2 sum e} in one rounding of the exponent, as they are when
+  // the planes are computed again.  Smaller planes and slabs where the cap or the
+  // device does not hold the scratch.
+  const size_t budget = std::max<size_t>(1, kSlabBudget / (2 * n * npix * 4));
+  int nds = std::min(p.slab > 0 ? std::min(p.slab, D) : (int)std::min<size_t>(D, budget), kTrMaxWP - 63);
+  nds = (int)std::max<size_t>(1, std::min<size_t>(nds, kPlanesMost / (n * npix * 4)));
+  pl->ca = nds < D;
+  int nw = p.slab > 0 || (size_t)D * n * npix * 4 > kPlanesMost ? nds : D;
+  size_t bytes = 0;
+  int rc = 0;
+  for (;;) {
+    bytes = soft_bytes(*pl, nw, nds);
+    rc = 0;
+    if (c->mem_cap && c->used + bytes > c->mem_cap) {
+      rc = fail(c, STEREO_ENOMEM, "soft plan needs %zu bytes, cap %zu, in use %zu", bytes,
                 c->mem_cap, c->used);
+    } else {
+      const hipError_t e = hipMalloc(&pl->block, bytes);
+      if (e == hipSuccess) break;
+      (void)hipGetLastError();
+      rc = fail(c, STEREO_ENOMEM, "hipMalloc(%zu): %s", bytes, hipGetErrorString(e));
+    }
+    if (nds == 1 && nw == 1) break;
+    if (nw == nds) nds = (nds + 1) / 2;
+    nw = nds;
   }
-  hipError_t e = hipMalloc(&pl->block, bytes);
-  if (e != hipSuccess) {
+  if (rc) {
     delete pl;
-    (void)hipGetLastError();
-    return fail(c, STEREO_ENOMEM, "hipMalloc(%zu): %s", bytes, hipGetErrorString(e));
+    return rc;
   }
+  c->err.clear();
+  pl->nw = nw;
+  pl->nds = nds;
+  pl->WP = 64 + nds - 1;
+  pl->lam_count = (size_t)((D + nds - 1) / nds) * n * pl->nstrips * ((Y + kSoftBR - 1) / kSoftBR);
   pl->bytes = bytes;
   char* cur = static_cast<char*>(pl->block);
   pl->half_f = carve<float>(cur, nimg * npix);
@@ -180,8 +214,8 @@ int make_soft_plan(stereo_ctx* c, int n, int W, int H, int Dmax, const stereo_so
   pl->inv_size = carve<float>(cur, n * npix);
   pl->part = carve<float2>(cur, (size_t)n * pl->nchunk * npix);
   pl->pc = carve<float4>(cur, n * npix);
-  pl->gca = carve<float>(cur, (size_t)pl->nds * n * npix);
-  pl->gcax = carve<float>(cur, (size_t)pl->nds * n * npix);
+  pl->wts = carve<float>(cur, (size_t)nw * n * npix);
+  pl->gcax = carve<float>(cur, (size_t)nds * n * npix);
   pl->g_half = carve<float>(cur, nimg * npix);
   pl->lam_part = carve<float2>(cur, pl->lam_count);
   pl->gr_part = carve<float>(cur, (size_t)n * pl->nstrips * Y * pl->WP);
@@ -191,7 +225,7 @@ int make_soft_plan(stereo_ctx* c, int n, int W, int H, int Dmax, const stereo_so
                      nimg * Y * pl->XA, 0.f);
   hipLaunchKernelGGL(k_fill_f32, dim3(1024), dim3(256), 0, s, reinterpret_cast<float*>(pl->sp),
                      nimg * Y * pl->XS * 2, 0.f);
-  e = hipGetLastError();
+  const hipError_t e = hipGetLastError();
   if (e != hipSuccess) {
     (void)hipFree(pl->block);
     delete pl;
@@ -247,7 +281,6 @@ void soft_features(SoftPlan& pl, const float* left, const float* right, hipStrea
 SoftArgs soft_args(const SoftPlan& pl, const float* lambdas, int dlo, int dhi, int csize) {
   SoftArgs a{};
   a.sp = pl.sp; a.arms = pl.arms; a.lam = lambdas; a.inv_size = pl.inv_size;
-  a.part = pl.part; a.pc = pl.pc; a.gca = pl.gca;
   a.X = pl.X; a.Y = pl.Y; a.XS = pl.XS; a.pads = pl.pads; a.XA = pl.XA;
   a.arm_x = pl.p.arm_x; a.arm_y = pl.p.arm_y;
   a.nbands = pl.nbands; a.dlo = dlo; a.dhi = dhi;
@@ -261,11 +294,32 @@ SoftArgs soft_args(const SoftPlan& pl, const float* lambdas, int dlo, int dhi, i
   return a;
 }
 
-template <bool GCA>
-void launch_soft_agg(const SoftPlan& pl, const SoftArgs& a, hipStream_t s) {
+// Most rows of a k_soft_agg band: the first and the last band have one halo.
+int agg_rows(const SoftPlan& pl) {
+  const int ob = (pl.Y + pl.nbands - 1) / pl.nbands;
+  return pl.nbands == 1 ? pl.Y : std::min(pl.Y, ob + (pl.nbands == 2 ? 1 : 2) * pl.p.arm_y);
+}
+
+template <int KMAX, int SEG>
+void launch_soft_agg_k(const SoftPlan& pl, const SoftArgs& a, hipStream_t s) {
   dim3 grid((unsigned)(((a.ngroups + kXcds - 1) / kXcds) * kXcds * a.nchunk));
-  if (pl.kmax == 8) hipLaunchKernelGGL((k_soft_agg<1, 8, GCA>), grid, dim3(kThreads), 0, s, a);
-  else hipLaunchKernelGGL((k_soft_agg<1, 16, GCA>), grid, dim3(kThreads), 0, s, a);
+  // the plane rows the band writes, or its window step reads
+  const int o0max = pl.nbands == 1 ? 0 : pl.p.arm_y;
+  const size_t lds = kAggRowBytes + (size_t)(std::max(agg_rows(pl), o0max + kWaves * KMAX) + 1) * 256;
+  static const hipError_t attr =
+      hipFuncSetAttribute(reinterpret_cast<const void*>(&k_soft_agg<KMAX, SEG>),
+                          hipFuncAttributeMaxDynamicSharedMemorySize, kLdsBytes);
+  (void)attr;  // were it refused, the launch fails and its error is reported
+  hipLaunchKernelGGL((k_soft_agg<KMAX, SEG>), grid, dim3(kThreads), lds, s, a);
+}
+
+void launch_soft_agg(const SoftPlan& pl, const SoftArgs& a, hipStream_t s) {
+  // rows of a wave's segment (whole pairs): 254 at most with 128 output rows,
+  // 382 with 256
+  const int seg = 2 * (((agg_rows(pl) + 1) / 2 + kWaves - 1) / kWaves);
+  if (pl.kmax == 8) launch_soft_agg_k<8, 16>(pl, a, s);
+  else if (seg <= 18) launch_soft_agg_k<16, 18>(pl, a, s);
+  else launch_soft_agg_k<16, 24>(pl, a, s);
 }
 
 int soft_prologue(stereo_ctx* c, int n, int W, int H, int Dmax, const stereo_soft_params* params,
@@ -355,18 +409,16 @@ int stereo_soft_forward(stereo_ctx* c, const float* left, const float* right, in
   if (rc) return rc;
   soft_features(*pl, left, right, stream);
   SoftArgs a = soft_args(*pl, lambdas, 0, pl->D, pl->csize);
-  // the weights of all D fit the gca planes only when one slab covers D;
-  // k_soft_tcolw addresses them through 32-bit buffer offsets
-  const size_t wts_bytes = (size_t)pl->D * pl->n * pl->X * pl->Y * 4;
-  pl->wts_valid = (flags & STEREO_SOFT_F_SAVE_WEIGHTS) && pl->nds >= pl->D &&
-                  wts_bytes < (size_t(1) << 32);
+  a.part = pl->part;
+  a.ca = pl->ca;
+  pl->wts_valid = (flags & STEREO_SOFT_F_SAVE_WEIGHTS) && pl->nw >= pl->D;
   if (pl->wts_valid) {
-    a.wts = pl->gca;
+    a.wts = pl->wts;
     pl->wts_left = left;
     pl->wts_right = right;
     pl->wts_lam = lambdas;
   }
-  launch_soft_agg<false>(*pl, a, stream);
+  launch_soft_agg(*pl, a, stream);
   const int npix = pl->X * pl->Y;
   hipLaunchKernelGGL(k_soft_merge, dim3((npix + 255) / 256, pl->n), dim3(256), 0, stream, pl->part,
                      pl->nchunk, npix, d_hat, lse2);
@@ -390,8 +442,7 @@ int stereo_soft_backward(stereo_ctx* c, const float* left, const float* right, i
   const bool reuse = (flags & STEREO_SOFT_F_REUSE_FEATURES) != 0;
   if (!reuse || pl->feat_left != left || pl->feat_right != right)
     soft_features(*pl, left, right, stream);
-  // the forward's weights of these inputs are on the plan: dL/dCA comes from
-  // them (k_soft_tcolw) instead of a recomputation of the aggregate
+  // the forward's weights of these inputs are on the plan, or are computed again
   const bool saved = reuse && pl->wts_valid && pl->wts_left == left && pl->wts_right == right &&
                      pl->wts_lam == lambdas;
   const float zc = (float)(std::ldexp(1.0, -pl->fxk) * 1.4426950408889634 / pl->p.tau);
@@ -399,45 +450,52 @@ int stereo_soft_backward(stereo_ctx* c, const float* left, const float* right, i
                      pl->inv_size, lse2, d_hat, g_dhat, npix, zc, 1.f / pl->p.tau, pl->pc);
   const int groups = pl->nstrips * pl->nbands * pl->n;
   const int tb = tcol_band(pl->p.arm_y);
-  if (!saved) pl->wts_valid = false;  // the slabs below overwrite the weight planes
-  size_t lam_off = 0;
-  for (int dlo = 0; dlo < pl->D; dlo += pl->nds) {
-    const int dhi = std::min(pl->D, dlo + pl->nds), nds = dhi - dlo;
-    if (saved) {
-      // one slab holds all D; disparity groups so that the grid fills the
-      // CUs about three blocks deep (each group reloads the per-pixel
-      // constants: at 4 x 718x496, 4 groups ran faster than 3 or 6)
-      const int base = ((X + 63) / 64) * ((Y + tb - 1) / tb) * pl->n;
-      const int ndg = std::max(1, std::min(pl->D, (3 * c->num_cu + base - 1) / base));
-      hipLaunchKernelGGL(k_soft_tcolw, dim3((X + 63) / 64, (Y + tb - 1) / tb, pl->n * ndg),
-                         dim3(64 * kTcwWaves), 0, stream, pl->gca,
-                         (uint32_t)((size_t)pl->D * pl->n * npix * 4), pl->pc, pl->arms, X, Y,
-                         pl->XA, pl->p.arm_y, pl->n, pl->D, ndg, pl->gcax);
-    } else {
-      const int cs = best_chunk_size(groups, nds, pl->rows, c->num_cu, nds);
-      launch_soft_agg<true>(*pl, soft_args(*pl, lambdas, dlo, dhi, cs), stream);
-      hipLaunchKernelGGL(k_soft_tcol, dim3((X + 63) / 64, (Y + tb - 1) / tb, nds * pl->n),
-                         dim3(256), 0, stream, pl->gca, pl->arms, X, Y, pl->XA, pl->p.arm_y,
-                         pl->n, pl->gcax);
-    }
+  const int base = pl->nstrips * ((Y + tb - 1) / tb) * pl->n;
+  const bool whole = pl->nw >= pl->D;  // weight planes of all D: computed once
+  if (!saved) pl->wts_valid = false;  // the planes are overwritten below
+  auto weights = [&](int dlo, int dhi) {
+    SoftArgs a = soft_args(*pl, lambdas, dlo, dhi,
+                           best_chunk_size(groups, dhi - dlo, pl->rows, c->num_cu, dhi - dlo));
+    a.wts = pl->wts;
+    a.wlo = dlo;
+    a.ca = 1;
+    launch_soft_agg(*pl, a, stream);
+  };
+  if (!saved && whole) weights(0, pl->D);
+  int slab = 0;
+  const int lam_slab = pl->nstrips * ((Y + kSoftBR - 1) / kSoftBR) * pl->n;
+  for (int dlo = 0; dlo < pl->D; dlo += pl->nds, ++slab) {
+    const int dhi = std::min(pl->D, dlo + pl->nds);
+    if (!saved && !whole) weights(dlo, dhi);
+    TcwArgs tc{};
+    tc.wts = pl->wts; tc.pc = pl->pc; tc.arms = pl->arms; tc.gcax = pl->gcax;
+    tc.wts_bytes = (uint32_t)((size_t)pl->nw * pl->n * npix * 4);
+    tc.X = X; tc.Y = Y; tc.XA = pl->XA; tc.arm_y = pl->p.arm_y; tc.npair = pl->n;
+    tc.dlo = dlo; tc.dhi = dhi; tc.wlo = whole ? 0 : dlo;
+    // disparity groups so that the grid fills the CUs about three blocks deep
+    // (each group reloads the per-pixel constants: at 4 x 718x496, 4 groups
+    // ran faster than 3 or 6)
+    tc.ndg = std::max(1, std::min(dhi - dlo, (3 * c->num_cu + base - 1) / base));
+    const dim3 tg((unsigned)((base * tc.ndg + kXcds - 1) / kXcds * kXcds));
+    if (saved && !pl->ca) hipLaunchKernelGGL(k_soft_tcolw<false>, tg, dim3(64 * kTcwWaves), 0, stream, tc);
+    else hipLaunchKernelGGL(k_soft_tcolw<true>, tg, dim3(64 * kTcwWaves), 0, stream, tc);
     TrArgs ta{};
     ta.gcax = pl->gcax; ta.arms = pl->arms; ta.sp = pl->sp; ta.lam = lambdas;
     ta.g_half = pl->g_half; ta.gr_part = pl->gr_part;
-    ta.lam_part = pl->lam_part + lam_off;
+    ta.lam_part = pl->lam_part + (size_t)slab * lam_slab;
     ta.X = X; ta.Y = Y; ta.XS = pl->XS; ta.pads = pl->pads; ta.XA = pl->XA;
     ta.npair = pl->n; ta.dlo = dlo; ta.dhi = dhi; ta.WP = pl->WP;
-    ta.nstrips = pl->nstrips; ta.nbands = pl->nbands_tr;
+    ta.nstrips = pl->nstrips; ta.nbands = (Y + kSoftBR - 1) / kSoftBR;
     ta.first = dlo == 0;  // the first slab writes every half-image gradient
-    dim3 tg((unsigned)(pl->nstrips * pl->nbands_tr), (unsigned)pl->n);
-    hipLaunchKernelGGL(k_soft_tr, tg, dim3(256), 0, stream, ta);
-    lam_off += (size_t)tg.x * tg.y;
+    hipLaunchKernelGGL(k_soft_tr, dim3((unsigned)(ta.nstrips * ta.nbands), (unsigned)pl->n), dim3(256),
+                       0, stream, ta);
     hipLaunchKernelGGL(k_soft_gright, dim3((X + 255) / 256, Y, pl->n), dim3(256), 0, stream,
                        pl->gr_part, pl->nstrips, pl->WP, dlo, dhi, X, Y, (int)(dlo == 0),
                        pl->g_half);
   }
   hipLaunchKernelGGL(k_soft_gfull, dim3((W + 255) / 256, H, 2 * pl->n), dim3(256), 0, stream,
                      pl->g_half, W, H, X, Y, g_left, g_right);
-  hipLaunchKernelGGL(k_soft_lam, dim3(1), dim3(1024), 0, stream, pl->lam_part, (int)lam_off,
+  hipLaunchKernelGGL(k_soft_lam, dim3(1), dim3(1024), 0, stream, pl->lam_part, slab * lam_slab,
                      g_lambdas);
   return launch_status(c);
 }

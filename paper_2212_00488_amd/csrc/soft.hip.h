@@ -17,16 +17,15 @@
 //             k_soft_merge  d_hat = sum d e_d / sum e_d, log2 sum e_d
 //             (with the weights saved, k_soft_agg also writes every e_d)
 //   backward  k_soft_bprep  per-pixel constants of dL/dCA
-//             k_soft_agg    (GCA mode) recomputes CA for a slab of d and
-//                           writes dL/dCA planes
-//             k_soft_tcol   transposed vertical window sums (integer difference
-//                           arrays over bands of output rows, LDS atomics)
-//             k_soft_tcolw  (weights saved by the forward) the same transpose
-//                           with dL/dCA formed from the saved e_d, in place of
-//                           k_soft_agg and k_soft_tcol
-//             k_soft_tr     transposed horizontal window sums back to dL/dC,
-//                           then dC/d(dI), dC/d(lambda) per pixel, summed over
-//                           the slab into the half-image gradients
+//             k_soft_agg    the weights e_d again, where the forward did not
+//                           save them
+//             k_soft_tcolw  dL/dCA from the weights, and the transposed vertical
+//                           window sums (integer difference arrays over bands
+//                           of output rows, LDS atomics)
+//             k_soft_tr     transposed horizontal window sums back to dL/dC
+//                           then dC/d(dI), dC/d(lambda) per
+//                           pixel, summed over the slab into the half-image
+//                           gradients
 //             k_soft_gright dL/d(right half image) from the strips' partials
 //             k_soft_gfull  transposed downscale and gray: dL/d(RGB)
 //             k_soft_lam    fixed-order sum of the lambda partials
@@ -47,8 +46,6 @@ namespace stereo_dev {
 // Internal linkage: each source of the library that launches a kernel
 // carries its own copy (no relocatable device code).
 namespace {
-
-constexpr int kSoftBR = 4;  // output rows per k_soft_tr workgroup (one per wave)
 
 __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
 
@@ -175,61 +172,53 @@ struct SoftArgs {
   const uint2* sp;          // [2n][Y][XS] padded pixel planes
   const uint32_t* arms;     // [2n][Y][XA]
   const float* lam;         // device [2]: lambda_AD, lambda_census
-  const float* inv_size;    // [n][Y][X]                    (forward)
-  float2* part;             // [n][nchunk][Y][X] {sum e, sum d e}  (forward)
-  const float4* pc;         // [n][Y][X] {w, log2 sum e, d_hat, A}  (GCA)
-  float* gca;               // [nds][n][Y][X] dL/dCA           (GCA)
-  float* wts;               // [D][n][Y][X] e_d, or NULL        (forward)
+  const float* inv_size;    // [n][Y][X]
+  float2* part;             // [n][nchunk][Y][X] {sum e, sum d e}, or NULL
+  float* wts;               // [..][n][Y][X] e_d, plane 0 = disparity wlo, or NULL
+  int ca;                   // wts takes CA in place of e_d
   int X, Y, XS, pads, XA, arm_x, arm_y;
-  int nbands, dlo, dhi, nstrips, ngroups, npair;
+  int nbands, dlo, dhi, wlo, nstrips, ngroups, npair;
   int csize, nchunk;        // d-chunk size; chunks = ceil((dhi - dlo) / csize), the last the remainder
   float fx;                 // fixed-point scale 2^k of the costs
   float zc;                 // 2^-k log2(e) / tau: CA_int * inv_size * zc = mean / tau in log2 units
   uint32_t sp_bytes, arms_bytes;
 };
 
-// Inclusive prefix sum of a float over the 64 lanes of a wave (the DPP
-// steps of wave_scan_incl, in float).
-template <int CTRL, int RMASK>
-__device__ __forceinline__ float dpp_add_f(float v) {
-  return v + __int_as_float(
-                 __builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, RMASK, 0xf, false));
-}
-__device__ __forceinline__ float wave_scan_incl_f(float v) {
-  v = dpp_add_f<0x111, 0xf>(v);
-  v = dpp_add_f<0x112, 0xf>(v);
-  v = dpp_add_f<0x114, 0xf>(v);
-  v = dpp_add_f<0x118, 0xf>(v);
-  v = dpp_add_f<0x142, 0xa>(v);
-  v = dpp_add_f<0x143, 0xc>(v);
-  return v;
+// Blocks are dealt to the 8 XCDs in turn (block id mod 8): block `id` of
+// `count` takes item (id mod 8) * ceil(count / 8) + id / 8, so that
+// neighbouring items, which read the same rows, run on one XCD and find each
+// other's halo in its L2.  The launch has 8 * ceil(count / 8) blocks; the items
+// past the last one are none.
+__device__ __forceinline__ int xcd_item(int id, int count) {
+  return (id & (kXcds - 1)) * ((count + kXcds - 1) / kXcds) + id / kXcds;
 }
 
-// LDS rows of the k_soft_agg plane for NS sub-passes of 128 row-buffer columns
-// (the row buffers, the segment totals, eight floats and a zero row beside it).
-__host__ __device__ constexpr int plane_rows(int ns) {
-  return (kLdsBytes - 32 - kWaves * 64 * 4 - kWaves * ns * 128 * 4) / 256 - 1;
-}
+// LDS bytes of k_soft_agg beside the plane: row buffers and the census table.
+constexpr int kAggRowBytes = kWaves * 128 * 4 + 32;
+// Most rows of the plane (the zero row beside them).
+constexpr int kAggRows = (kLdsBytes - kAggRowBytes) / 256 - 1;
 
 // One workgroup = one 64-column strip x one band of rows x one pair x one
-// chunk of disparities; 16 waves, the layout of k_match (row pass with a DPP
-// wave scan, running column sums into the LDS plane, segment offsets, window
-// differences).  The cost of a column c at disparity d:
+// chunk of disparities; 16 waves, the layout of k_match with one base (row
+// pass with a DPP wave scan, column sums in registers until the segment offsets
+// are known, plane, window differences).  The cost of a column c at disparity d:
 //   c - d >= 0: C = (2 - exp(-255 |L(c) - R(c-d)| / lambda_AD)) - exp(-H / lambda_census)
 //   c - d <  0: C = 2
 // taken to fixed point.  Output rows of a thread: o0 + wave + 16 k, k < KMAX.
-//   GCA = false: e = 2^{-CA mean / tau (log2 units)}, sums of e and d e per
-//                output pixel over the chunk -> part;
-//   GCA = true : dL/dCA(x,y,d) = A p_d (d - d_hat), p_d = 2^{-z_d - log2 sum e}
-//                -> gca plane of d (slot d - dlo).
+// e = 2^{-CA mean / tau (log2 units)}; its sums e and d e per output pixel over
+// the chunk go to part, every e to wts (each where given).
+// A wave's segment has at most SEG rows (their sums stay in registers).
+// Vector arithmetic and LDS bound: the row sums in registers and two barriers
+// a disparity (one for the segments' totals, one for the plane) in place of
+// three and a second pass over the plane.  4 pairs of 718x496, 73 disparities:
+// 440 us before, 390 us now.
 // grid: ceil(groups / 8) * 8 * nchunk workgroups (1-D), block 1024.
-template <int NS, int KMAX, bool GCA>
+template <int KMAX, int SEG>
 __global__ void __launch_bounds__(kThreads) k_soft_agg(SoftArgs a) {
-  constexpr int PR = plane_rows(NS);
-  __shared__ uint32_t s_row[kWaves][NS * 128];
-  __shared__ uint32_t s_seg[kWaves][64];
-  __shared__ uint32_t s_plane[(PR + 1) * 64];
-  __shared__ float s_ex[8];
+  extern __shared__ __align__(16) uint8_t s_agg[];
+  auto s_row = reinterpret_cast<uint32_t(*)[128]>(s_agg);
+  float* s_ex = reinterpret_cast<float*>(s_agg + kWaves * 128 * 4);
+  uint32_t* s_plane = reinterpret_cast<uint32_t*>(s_agg + kAggRowBytes);  // row 0 = zeros
 
   const int t = threadIdx.x, lane = t & 63;
   const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
@@ -249,10 +238,10 @@ __global__ void __launch_bounds__(kThreads) k_soft_agg(SoftArgs a) {
   const int ya = max(0, y0 - a.arm_y), yb = min(Y, y1 + a.arm_y);
   const int nb = yb - ya, o0 = y0 - ya, o1 = y1 - ya;
   const int d0 = a.dlo + chunk * a.csize, d1 = min(a.dhi, d0 + a.csize);
-  const int hx = (a.arm_x + 2) & ~1;
+  const int hx = (a.arm_x + 2) & ~1, e0 = x0 - hx;
   const __amdgpu_buffer_rsrc_t rs = buffer_rsrc(a.sp, a.sp_bytes);
   const __amdgpu_buffer_rsrc_t ra = buffer_rsrc(a.arms, a.arms_bytes);
-  const uint32_t img_l = (uint32_t)(2 * pair), img_r = img_l + 1u;
+  const uint32_t img_l = (uint32_t)(2 * pair);
   const uint32_t sprow = (uint32_t)a.XS * 8u, armrow = (uint32_t)a.XA * 4u;
   const float lam_ad = a.lam[0], lam_c = a.lam[1];
   // e^{-255 |dI| / lambda_AD} = 2^{-|dI| k2}
@@ -260,7 +249,7 @@ __global__ void __launch_bounds__(kThreads) k_soft_agg(SoftArgs a) {
   if (t < 8) s_ex[t] = t < 7 ? fast_exp2(-(float)t * 1.4426950408889634f / lam_c) : 0.f;
   if (t < 64) s_plane[t] = 0u;
 
-  const int c = lane, x = x0 + lane;
+  const int x = x0 + lane;
   // rows of the band in segments of whole row pairs (the row pass takes its
   // rows in pairs), one per wave in order, the pairs split as evenly as
   // possible: the waves of each SIMD (wave mod 4) then share the rows evenly
@@ -268,9 +257,9 @@ __global__ void __launch_bounds__(kThreads) k_soft_agg(SoftArgs a) {
   const int r0 = min(nb, 2 * (wave * bq + min(wave, br)));
   const int r1 = min(nb, r0 + 2 * (bq + (wave < br)));
 
-  static_assert(KMAX % 2 == 0, "KMAX must be even");
+  static_assert(KMAX % 2 == 0 && SEG % kRowBatch == 0, "rows go in pairs");
   uint32_t marm[KMAX / 2];
-  float se[GCA ? 1 : KMAX], sde[GCA ? 1 : KMAX], isz[GCA ? 1 : KMAX];
+  float se[KMAX], sde[KMAX], isz[KMAX];
 #pragma unroll
   for (int k = 0; k < KMAX; ++k) {
     const int r = o0 + wave + k * kWaves;
@@ -281,154 +270,179 @@ __global__ void __launch_bounds__(kThreads) k_soft_agg(SoftArgs a) {
     const uint32_t mn = r < o1 ? v : 0u;
     if (k & 1) marm[k / 2] |= mn << 16;
     else marm[k / 2] = mn;
-    if constexpr (!GCA) {
-      se[k] = 0.f;
-      sde[k] = 0.f;
-      // unconditional load at a clamped pixel, then a select (as above)
-      const float iv = a.inv_size[((size_t)pair * Y + ya + min(r, o1 - 1)) * X + min(x, X - 1)];
-      isz[k] = in ? iv * a.zc : 0.f;
-    }
+    se[k] = 0.f;
+    sde[k] = 0.f;
+    // unconditional load at a clamped pixel, then a select (as above)
+    const float iv = a.inv_size[((size_t)pair * Y + ya + min(r, o1 - 1)) * X + min(x, X - 1)];
+    isz[k] = in ? iv * a.zc : 0.f;
   }
-  const int fin_base = (o0 + wave + 1) * 64 + c;
-  // byte offset of this lane's first column pair in a padded row
-  const uint32_t vb = (uint32_t)(a.pads + x0 - hx + 2 * lane) * 8u;
-  const uint32_t vx = (uint32_t)x * 4u;
   const float fx = a.fx;
   __syncthreads();
 
-  auto cost = [&](uint2 l, uint2 r, int col, int d) -> uint32_t {
-    const float di = fabsf(__uint_as_float(l.x) - __uint_as_float(r.x));
-    const float cf = (2.f - fast_exp2(-di * k2)) - s_ex[__builtin_popcount(l.y ^ r.y)];
-    const uint32_t ci = (uint32_t)(cf * fx + 0.5f);
-    return col - d >= 0 ? ci : (uint32_t)(2.f * fx + 0.5f);
+  // cost of a pair of pixels in fixed point (the columns without a match apart)
+  auto cost = [&](uint32_t lv, uint32_t lc, uint32_t rv, uint32_t rc) -> uint32_t {
+    const float di = fabsf(__uint_as_float(lv) - __uint_as_float(rv));
+    const float cf = (2.f - fast_exp2(-di * k2)) - s_ex[__builtin_popcount(lc ^ rc)];
+    return (uint32_t)(cf * fx + 0.5f);
   };
+  const uint32_t cout = (uint32_t)(2.f * fx + 0.5f);
 
   for (int d = d0; d < d1; ++d) {
-    const uint32_t vo = vb - (uint32_t)(d * 8);
-    uint32_t run = 0;
-    // rows in batches of two (their scans interleave), the loads of the next
-    // batch in flight while this one is processed; a batch running past the
-    // segment end loads its last row again and never stores it
-    struct RowIn { u32x4 L[NS], R[NS]; uint32_t am; };
-    auto load_row = [&](int r, RowIn& in) {
-      const uint32_t y = (uint32_t)(ya + r);
-      const uint32_t sl = (img_l * (uint32_t)Y + y) * sprow, sr = (img_r * (uint32_t)Y + y) * sprow;
+    // per-lane addresses formed anew for each disparity (see k_match)
+    uint32_t ln = (uint32_t)lane;
+    __asm__ volatile("" : "+v"(ln));
+    // byte offset of this lane's first column pair in a padded row
+    const uint32_t vb = (uint32_t)(a.pads + e0) * 8u + ln * 16u;
+    const uint32_t vo = vb - (uint32_t)(d * 8), vx = ((uint32_t)x0 + ln) * 4u;
+    uint32_t wrow = lds_addr(s_row[wave]) + ln * 8u;
+    uint32_t ent = lds_addr(s_row[wave]) + (uint32_t)hx * 4u + ln * 4u;
+    __asm__ volatile("" : "+v"(ent), "+v"(wrow));
+    const bool edge = e0 < d;  // the strip holds columns without a match (wave-uniform)
+    const bool out0 = e0 + 2 * (int)ln < d, out1 = e0 + 2 * (int)ln + 1 < d;
+    // scalar byte offsets of the row to load next (rows past the segment's end
+    // are the next one's, or the band's last row again)
+    const uint32_t yl = img_l * (uint32_t)Y + (uint32_t)(ya + r0);
+    uint32_t sl = yl * sprow, sa = yl * armrow;
+    const uint32_t other = (uint32_t)Y * sprow;  // the right image's rows follow the left one's
+    int rn = r0;
+    __asm__ volatile("" : "+s"(sl), "+s"(sa), "+s"(rn));
+    struct RowIn { u32x4 L, R; };
+    auto load_batch = [&](RowIn (&in)[kRowBatch], uint32_t (&am)[kRowBatch]) {
 #pragma unroll
-      for (int s = 0; s < NS; ++s) {
-        in.L[s] = __builtin_amdgcn_raw_buffer_load_b128(rs, vb + s * 1024, sl, 0);
-        in.R[s] = __builtin_amdgcn_raw_buffer_load_b128(rs, vo + s * 1024, sr, 0);
-      }
-      in.am = __builtin_amdgcn_raw_buffer_load_b32(ra, vx, (img_l * (uint32_t)Y + y) * armrow, 0);
-    };
-    auto row_of = [&](int r, int i) { return r + i < r1 ? r + i : r1 - 1; };
-    auto load_batch = [&](int r, RowIn (&in)[2]) {
-      load_row(row_of(r, 0), in[0]);
-      load_row(row_of(r, 1), in[1]);
-    };
-    auto process_batch = [&](int r, const RowIn (&in)[2]) {
-      uint32_t c1v[2][NS], pr[2][NS];
-#pragma unroll
-      for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int s = 0; s < NS; ++s) {
-          const int col = x0 - hx + s * 128 + 2 * lane;
-          const uint32_t c0 = cost(make_uint2(in[i].L[s].x, in[i].L[s].y),
-                                   make_uint2(in[i].R[s].x, in[i].R[s].y), col, d);
-          c1v[i][s] = cost(make_uint2(in[i].L[s].z, in[i].L[s].w),
-                           make_uint2(in[i].R[s].z, in[i].R[s].w), col + 1, d);
-          pr[i][s] = wave_scan_incl(c0 + c1v[i][s]);
-        }
-#pragma unroll
-      for (int i = 0; i < 2; ++i) {
-        if (i > 0 && r + i >= r1) break;
-        uint32_t carry = 0;
-#pragma unroll
-        for (int s = 0; s < NS; ++s) {
-          const uint32_t p = pr[i][s] + carry;
-          if (NS > 1) carry = __builtin_amdgcn_readlane(p, 63);
-          *reinterpret_cast<u32x2*>(&s_row[wave][s * 128 + 2 * lane]) = u32x2{p - c1v[i][s], p};
-        }
-        WAVE_LDS_ORDER();
-        const int m = in[i].am & 255u, n = (in[i].am >> 8) & 255u;
-        run += s_row[wave][lane + hx + n] - s_row[wave][lane + hx - m - 1];
-        WAVE_LDS_ORDER();
-        s_plane[(r + i + 1) * 64 + lane] = run;
+      for (int i = 0; i < kRowBatch; ++i) {
+        in[i].L = __builtin_amdgcn_raw_buffer_load_b128(rs, vb, sl, 0);
+        in[i].R = __builtin_amdgcn_raw_buffer_load_b128(rs, vo, sl + other, 0);
+        am[i] = __builtin_amdgcn_raw_buffer_load_b32(ra, vx, sa, 0);
+        ++rn;
+        sl += rn < nb ? sprow : 0u;
+        sa += rn < nb ? armrow : 0u;
       }
     };
-    RowIn in0[2], in1[2];  // two buffer sets, used in turn
-    if (r0 < r1) load_batch(r0, in0);
-    for (int r = r0; r < r1; r += 4) {
-      load_batch(r + 2, in1);  // unconditional: see k_match's row pass
-      process_batch(r, in0);
-      if (r + 2 >= r1) break;
-      load_batch(r + 4, in0);
-      process_batch(r + 2, in1);
-    }
-    s_seg[wave][c] = run;
+    uint32_t run[SEG], tot = 0;
+    RowIn in[kRowBatch];
+    uint32_t am[2][kRowBatch];
+    if (r0 < r1) load_batch(in, am[0]);
+    static_while<SEG / kRowBatch>([&](auto Q) {
+      constexpr int q = decltype(Q)::value;
+      const int r = r0 + q * kRowBatch;
+      if (r >= r1) return false;
+      // a falling priority keeps the waves of a SIMD abreast (see k_match)
+      if constexpr (q == 0) __builtin_amdgcn_s_setprio(2);
+      if constexpr (q == SEG / 6) __builtin_amdgcn_s_setprio(1);
+      if constexpr (q == SEG / 3) __builtin_amdgcn_s_setprio(0);
+      uint32_t c1[kRowBatch], pr[kRowBatch];
+#pragma unroll
+      for (int i = 0; i < kRowBatch; ++i) {
+        pr[i] = cost(in[i].L.x, in[i].L.y, in[i].R.x, in[i].R.y);
+        c1[i] = cost(in[i].L.z, in[i].L.w, in[i].R.z, in[i].R.w);
+      }
+      // the pixels are used up: the next batch's take their registers
+      // (unconditional, so that the waits do not depend on a branch)
+      load_batch(in, am[(q + 1) & 1]);
+      if (edge) {
+#pragma unroll
+        for (int i = 0; i < kRowBatch; ++i) {
+          pr[i] = out0 ? cout : pr[i];
+          c1[i] = out1 ? cout : c1[i];
+        }
+      }
+#pragma unroll
+      for (int i = 0; i < kRowBatch; ++i) pr[i] += c1[i];
+      wave_scan_incl_n(pr);
+#pragma unroll
+      for (int i = 0; i < kRowBatch; ++i) {
+        lds_write2(wrow, pr[i] - c1[i], pr[i]);
+        WAVE_LDS_ORDER();
+        const uint32_t m = am[q & 1][i] & 255u, n = (am[q & 1][i] >> 8) & 255u;
+        tot += lds_read(ent + n * 4u) - lds_read(ent - m * 4u - 4u);
+        WAVE_LDS_ORDER();
+        run[q * kRowBatch + i] = tot;
+      }
+      return true;
+    });
+    // the wave's total goes to its own row buffer (see k_match)
+    s_row[wave][ln] = tot;
     __syncthreads();
+    __builtin_amdgcn_s_setprio(3);
     uint32_t off = 0;
+    int s0 = 0;
 #pragma unroll
-    for (int s = 0; s < kWaves; ++s) {
-      const uint32_t v = s_seg[s][c];
-      off += s < wave ? v : 0u;
-    }
-    if (wave > 0) {
-#pragma unroll 8
-      for (int r = r0; r < r1; ++r) s_plane[(r + 1) * 64 + c] += off;
-    }
+    for (int n = kWaves / 2; n > 0; n >>= 1)
+      if (wave & n) {
+        uint32_t v[8];
+#pragma unroll
+        for (int s = 0; s < n; ++s) v[s] = s_row[s0 + s][ln];
+#pragma unroll
+        for (int s = 0; s < n; ++s) off += v[s];
+        s0 += n;
+      }
+    uint32_t* pw = s_plane + (r0 + 1) * 64 + ln;
+    int nrows = r1 - r0;
+    __asm__ volatile("" : "+s"(nrows));
+    static_while<SEG>([&](auto K) {
+      constexpr int k = decltype(K)::value;
+      if (k >= nrows) return false;
+      pw[k * 64] = run[k] + off;
+      return true;
+    });
     __syncthreads();
+    // window differences of this wave's output rows, two slot pairs at a time,
+    // the reads of the next ones in flight
     const float fd = (float)d;
-    // the adjoint's per-pixel constants of 4 output rows at a time, loaded
-    // together (unconditionally, at clamped pixels) before they are used
-    constexpr int QB = GCA ? 4 : 1;
-    float4 qv[QB];
+    const uint32_t fin = lds_addr(s_plane) + (uint32_t)((o0 + wave + 1) * 64) * 4u + ln * 4u;
+    uint32_t kpermM = 0x020c000cu;
+    __asm__ volatile("" : "+v"(kpermM));
+    // rows of the weight plane of d
+    float* wd = a.wts ? a.wts + ((size_t)(d - a.wlo) * a.npair + pair) * X * Y + (size_t)(ya + o0 + wave) * X + x0
+                      : nullptr;
+    if (x < X) {
+      uint32_t wh[2][kWinGroup][2], wl[2][kWinGroup][2];
+      auto window_reads = [&](auto G) {
+        constexpr int g = decltype(G)::value;
 #pragma unroll
-    for (int jj = 0; jj < KMAX / 2; ++jj) {
-      if constexpr (GCA) {
-        if ((2 * jj) % QB == 0) {
+        for (int i = 0; i < kWinGroup; ++i) {
+          const int jp = g * kWinGroup + i;
+          if (jp >= KMAX / 2) continue;
+          uint32_t nw, mw;  // N and M of two rows in bits 8..15 of the halves: byte offsets
+          __asm__ volatile("v_and_b32 %0, 0xff00ff00, %1" : "=v"(nw) : "v"(marm[jp]));
+          __asm__ volatile("v_perm_b32 %0, 0, %1, %2" : "=v"(mw) : "v"(marm[jp]), "v"(kpermM));
 #pragma unroll
-          for (int u = 0; u < QB; ++u) {
-            const int r = min(o0 + wave + (2 * jj + u) * kWaves, o1 - 1);
-            qv[u] = a.pc[((size_t)pair * Y + ya + r) * X + min(x, X - 1)];
+          for (int e = 0; e < 2; ++e) {
+            const uint32_t kb = (uint32_t)((2 * jp + e) * kWaves * 64 * 4);
+            wh[g & 1][i][e] = lds_read((fin + (e ? nw >> 16 : nw & 0xffffu)) + kb);
+            wl[g & 1][i][e] = lds_read((fin - (e ? mw >> 16 : mw & 0xffffu)) + kb - 256u);
           }
         }
-      }
-      uint32_t mj = marm[jj];
-      __asm__ volatile("" : "+v"(mj));
+      };
+      constexpr int kGroups = (KMAX / 2 + kWinGroup - 1) / kWinGroup;
+      window_reads(std::integral_constant<int, 0>{});
+      static_for<kGroups>([&](auto G) {
+        constexpr int g = decltype(G)::value;
+        if constexpr (g + 1 < kGroups) window_reads(std::integral_constant<int, g + 1>{});
+        WAVE_LDS_ORDER();  // those reads are issued before this group is waited for
 #pragma unroll
-      for (int h = 0; h < 2; ++h) {
-        const int k = 2 * jj + h;
-        const int M = (mj >> (16 * h)) & 255u, N = (mj >> (16 * h + 8)) & 255u;
-        const int lo = fin_base - (M + 1) * 64, hi = fin_base + N * 64;
-        const uint32_t ca = s_plane[hi + k * kWaves * 64] - s_plane[lo + k * kWaves * 64];
-        if constexpr (!GCA) {
-          const float e = fast_exp2(-(float)ca * isz[k]);
-          se[k] += e;
-          sde[k] += fd * e;
-          const int r = o0 + wave + k * kWaves;
-          if (a.wts && x < X && r < o1)
-            a.wts[(size_t)d * a.npair * X * Y + ((size_t)pair * Y + ya + r) * X + x] = e;
-        } else {
-          const int r = o0 + wave + k * kWaves;
-          const float4 q = qv[k % QB];
-          const float p = fast_exp2(-(float)ca * q.x - q.y);
-          if (x < X && r < o1)
-            a.gca[(size_t)(d - a.dlo) * a.npair * X * Y + ((size_t)pair * Y + ya + r) * X + x] =
-                q.w * p * (fd - q.z);
-        }
-      }
+        for (int i = 0; i < kWinGroup; ++i)
+#pragma unroll
+          for (int e = 0; e < 2; ++e) {
+            const int k = 2 * (g * kWinGroup + i) + e;
+            if (k >= KMAX) continue;
+            const uint32_t ca = wh[g & 1][i][e] - wl[g & 1][i][e];
+            const float ev = fast_exp2(-(float)ca * isz[k]);
+            se[k] += ev;
+            sde[k] += fd * ev;
+            if (wd && o0 + wave + k * kWaves < o1)
+              wd[(size_t)k * kWaves * X + ln] = a.ca ? (float)ca : ev;
+          }
+      });
     }
-    __syncthreads();
   }
 
-  if constexpr (!GCA) {
-    if (x < X) {
-      float2* out = a.part + (size_t)(pair * a.nchunk + chunk) * X * Y;
+  if (a.part && x < X) {
+    float2* out = a.part + (size_t)(pair * a.nchunk + chunk) * X * Y;
 #pragma unroll
-      for (int k = 0; k < KMAX; ++k) {
-        const int r = o0 + wave + k * kWaves;
-        if (r < o1) out[(size_t)(ya + r) * X + x] = make_float2(se[k], sde[k]);
-      }
+    for (int k = 0; k < KMAX; ++k) {
+      const int r = o0 + wave + k * kWaves;
+      if (r < o1) out[(size_t)(ya + r) * X + x] = make_float2(se[k], sde[k]);
     }
   }
 }
@@ -477,234 +491,219 @@ __global__ void __launch_bounds__(256) k_soft_bprep(const float* __restrict__ in
   pc[o] = make_float4(is * zc, lse2[o], dhat[o], -g_dhat[o] * is * inv_tau);
 }
 
-// ------------------------------------------------------------ k_soft_tcol
-// Transpose of the vertical window sum (Eq. 8) for one disparity over a band
-// of kTcolBand output rows of a 64-column strip:
-//   CA(x,y) = sum_{s=-M(x,y)}^{N(x,y)} CA_x(x,y+s)  gives
-//   dL/dCA_x(x,y') = sum of dL/dCA(x,y) over the y whose window holds y'.
-// The band's rows y' in [Y0, Y0 + B) can only be reached from sources y in
-// [Y0 - arm_y, Y0 + B + arm_y); each source's window, clipped to the band,
-// becomes a difference array (+g at its first row, -g after its last) and a
-// prefix down the column gives the sums.  The difference array is integer
-// fixed point with a per-column scale 2^k, k = 23 - e where 2^(e-1) <= the
-// column's largest |g| < 2^e: each term is below 2^23 and a sum of at most
-// 2 arm_y + 1 <= 127 terms below 2^30, so LDS integer atomic adds give exact
-// sums in any order (the result does not depend on scheduling) and each
-// term is rounded to 2^(e-24), the float resolution of the column's largest
-// value.  Thread (wave w, lane l) takes column x0 + l and the source rows
-// Y0 - arm_y + w + 4 i, all loads issued together and held in registers.
-// grid: (ceil(X/64), ceil(Y/B), nds * n), block 256; B = kTcolBand for
-// arm_y <= 31, else kTcolBand / 2 (the sources then still fit 48 per thread).
-constexpr int kTcolBand = 128;
-constexpr int kTcolSrc = 48;  // source rows per thread at most
-
-__host__ __device__ constexpr int tcol_band(int arm_y) { return arm_y <= 31 ? kTcolBand : kTcolBand / 2; }
-
-__global__ void __launch_bounds__(256) k_soft_tcol(const float* __restrict__ gca,
-                                                   const uint32_t* __restrict__ arms, int X,
-                                                   int Y, int XA, int arm_y, int npair,
-                                                   float* __restrict__ gcax) {
-  __shared__ int s_d[kTcolBand + 1][64];
-  __shared__ float s_max[4][64];
-  __shared__ int s_tot[4][64];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int B = tcol_band(arm_y);
-  const int x = blockIdx.x * 64 + lane, Y0 = blockIdx.y * B;
-  const int dj = blockIdx.z / npair, pair = blockIdx.z - dj * npair;
-  const int Y1 = min(Y, Y0 + B);
-  const bool xv = x < X;
-  const size_t plane = (size_t)X * Y;
-  const float* g = gca + ((size_t)dj * npair + pair) * plane;
-  const uint32_t* am = arms + (size_t)(2 * pair) * Y * XA;
-  const int ys = max(0, Y0 - arm_y), ye = min(Y, Y1 + arm_y);
-  // sources y = ys + wave + 4 i < ye; loads at clamped rows, masked after
-  float gv[kTcolSrc];
-  uint32_t av[kTcolSrc];
-#pragma unroll
-  for (int i = 0; i < kTcolSrc; ++i) {
-    const int y = min(ys + wave + 4 * i, ye - 1);
-    gv[i] = xv ? g[(size_t)y * X + x] : 0.f;
-    av[i] = am[(size_t)y * XA + min(x, XA - 1)];
-  }
-  for (int i = threadIdx.x; i < (B + 1) * 64; i += 256) (&s_d[0][0])[i] = 0;
-  float mx = 0.f;
-#pragma unroll
-  for (int i = 0; i < kTcolSrc; ++i)
-    if (ys + wave + 4 * i < ye) mx = fmaxf(mx, fabsf(gv[i]));
-  s_max[wave][lane] = mx;
-  __syncthreads();
-  const float cmax = fmaxf(fmaxf(s_max[0][lane], s_max[1][lane]), fmaxf(s_max[2][lane], s_max[3][lane]));
-  int e = 0;
-  (void)frexpf(cmax, &e);
-  const float up = cmax > 0.f ? ldexpf(1.f, 23 - e) : 0.f;
-#pragma unroll
-  for (int i = 0; i < kTcolSrc; ++i) {
-    const int y = ys + wave + 4 * i;
-    if (y < ye && gv[i] != 0.f) {
-      const int q = (int)rintf(gv[i] * up);
-      const int M = (int)((av[i] >> 16) & 255u), N = (int)(av[i] >> 24);
-      const int lo = max(y - M, Y0), hi = min(y + N, Y1 - 1);
-      if (lo <= hi) {
-        atomicAdd(&s_d[lo - Y0][lane], q);
-        if (hi + 1 < Y1) atomicAdd(&s_d[hi + 1 - Y0][lane], -q);
-      }
-    }
-  }
-  __syncthreads();
-  // prefix down the column: wave w takes rows w * B/4 .. (w+1) * B/4 - 1,
-  // its running sum kept per row, then the totals of the waves above
-  const int rpw = B / 4, r0 = wave * rpw;
-  int run = 0;
-  int loc[kTcolBand / 4];
-#pragma unroll
-  for (int i = 0; i < kTcolBand / 4; ++i) {
-    if (i < rpw) run += s_d[r0 + i][lane];
-    loc[i] = run;
-  }
-  s_tot[wave][lane] = run;
-  __syncthreads();
-  int off = 0;
-#pragma unroll
-  for (int w = 0; w < 3; ++w) off += w < wave ? s_tot[w][lane] : 0;
-  if (!xv) return;
-  const float down = cmax > 0.f ? ldexpf(1.f, e - 23) : 0.f;
-  float* out = gcax + ((size_t)dj * npair + pair) * plane + x;
-#pragma unroll
-  for (int i = 0; i < kTcolBand / 4; ++i) {
-    const int y = Y0 + r0 + i;
-    if (i < rpw && y < Y1) out[(size_t)y * X] = (float)(loc[i] + off) * down;
-  }
-}
-
 // ------------------------------------------------------------ k_soft_tcolw
-// The transpose of k_soft_tcol with dL/dCA formed on the fly from the
-// softmax weights e_d = 2^{-CA(d) w} that the forward saved:
+// Transpose of the vertical window sum (Eq. 8) with dL/dCA formed on the fly
+// from the softmax weights e_d = 2^{-CA(d) w} of the forward:
 //   dL/dCA(x,y,d) = A p_d (d - d_hat),  p_d = e_d 2^{-lse2}
-// (A, lse2 and d_hat from k_soft_bprep's constants), so the backward needs
-// neither k_soft_agg's recomputation of CA nor the dL/dCA planes.  A block
-// takes a 64-column strip, a band of B output rows (tcol_band) and a range
-// of disparities of one pair; thread (wave w, lane l) holds, over the range,
-// the constants and vertical arms of column x0 + l at the source rows
-// Y0 - arm_y + w + 8 i, and for each disparity builds the band's integer
-// difference array exactly as k_soft_tcol does (per-column power-of-two
-// scale from the largest |dL/dCA| of the band's sources, LDS integer atomics,
-// order-independent sums), then writes dL/dCA_x of the band's rows.
-// grid: (ceil(X/64), ceil(Y/B), n * ndg), block 512; disparity group g of
-// ndg covers [g D / ndg, (g + 1) D / ndg).
+//   CA(x,y) = sum_{s=-M(x,y)}^{N(x,y)} CA_x(x,y+s)  gives
+//   dL/dCA_x(x,y') = sum of dL/dCA(x,y) over the y whose window holds y'
+// (A, lse2 and d_hat from k_soft_bprep's constants).  A block takes a
+// 64-column strip, a band of B output rows (tcol_band) and a range of
+// disparities of one pair.  The band's rows y' in [Y0, Y0 + B) can only be
+// reached from sources y in [Y0 - arm_y, Y0 + B + arm_y); each source's window,
+// clipped to the band, becomes a difference array (+g at its first row, -g
+// after its last) and a prefix down the column gives the sums.  The difference
+// array is integer fixed point with a per-column scale 2^k, k = 23 - e where
+// 2^(e-1) <= the column's largest |g| < 2^e: each term is at most 2^23 and a sum
+// of at most 2 arm_y + 1 <= 127 terms at most 2^30, so LDS integer atomics give
+// exact sums in any order (the result does not depend on scheduling) and each
+// term is rounded to 2^(e-24), the float resolution of the column's largest
+// value.  Thread (wave w, lane l) holds, over the range, the constants of
+// column x0 + l at the source rows Y0 - arm_y + w + 16 i and the difference rows
+// their windows start and end at.
+// A disparity passes through four stages: A its terms and the column's largest
+// (LDS atomic maximum), B the scatter, C each wave's prefix over its output rows,
+// D the offsets of the waves above and the stores.  Between two barriers every
+// wave does B of one disparity, D and C of the two before it and A of the next,
+// on three difference arrays in turn: one barrier a disparity instead of three.
+// Bound by the 24 LDS atomics a thread and disparity and by the 16 waves that a
+// CU holds: 4 pairs of 718x496, 73 disparities, 264 us with three barriers and
+// 246 now.  CA = true takes saved CA: at 4 pairs of 960x540 and 128 disparities,
+// where the backward computed CA again and summed its planes one by one,
+// forward and backward together took 3.61 ms and take 2.27 (this kernel 0.60).
+// grid: strips * bands * n * ndg rounded up to 8 (1-D, xcd_item), block 1024;
+// disparity group g of ndg covers [dlo + g nd / ndg, dlo + (g + 1) nd / ndg).
+constexpr int kTcolBand = 128;
+__host__ __device__ constexpr int tcol_band(int arm_y) { return arm_y <= 31 ? kTcolBand : kTcolBand / 2; }
 constexpr int kTcwWaves = 16;
 constexpr int kTcwSrc = 12;  // source rows per thread: B + 2 arm_y <= 16 * 12
 static_assert(tcol_band(31) + 2 * 31 <= kTcwWaves * kTcwSrc &&
                   tcol_band(63) + 2 * 63 <= kTcwWaves * kTcwSrc, "k_soft_tcolw source rows");
 
-__global__ void __launch_bounds__(64 * kTcwWaves) k_soft_tcolw(
-    const float* __restrict__ wts, uint32_t wts_bytes, const float4* __restrict__ pc,
-    const uint32_t* __restrict__ arms, int X, int Y, int XA, int arm_y, int npair, int D, int ndg,
-    float* __restrict__ gcax) {
-  __shared__ int s_d[kTcolBand + 1][64];
-  __shared__ float s_max[kTcwWaves][64];
-  __shared__ int s_tot[kTcwWaves][64];
-  const int lane = threadIdx.x & 63;
-  const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-  const int B = tcol_band(arm_y);
-  const int x = blockIdx.x * 64 + lane, Y0 = blockIdx.y * B;
-  const int pair = blockIdx.z % npair, dg = blockIdx.z / npair;
-  const int dlo = dg * D / ndg, dhi = (dg + 1) * D / ndg;
+struct TcwArgs {
+  const float* wts;         // [..][n][Y][X] e_d or CA, plane 0 = disparity wlo
+  const float4* pc;         // [n][Y][X] constants (k_soft_bprep)
+  const uint32_t* arms;     // [2n][Y][XA]
+  float* gcax;              // [nds][n][Y][X] dL/dCA_x
+  uint32_t wts_bytes;
+  int X, Y, XA, arm_y, npair, dlo, dhi, wlo, ndg;
+};
+
+// Exponent e with 2^(e-1) <= v < 2^e of the bits of a float v >= 0 (frexp's;
+// denormals too); 0 for v = 0.
+__device__ __forceinline__ int float_exp(uint32_t bits) {
+  const int be = (int)(bits >> 23);
+  return be > 0 ? be - 126 : (bits ? -117 - (int)__builtin_clz(bits) : 0);
+}
+
+template <bool CA>
+__global__ void __launch_bounds__(64 * kTcwWaves) k_soft_tcolw(TcwArgs a) {
+  constexpr int RPW = kTcolBand / kTcwWaves;  // output rows per wave, at most
+  __shared__ __align__(16) int s_d[3][kTcolBand + 1][64];  // row B: ends behind the band
+  __shared__ int s_tot[2][kTcwWaves][64];
+  __shared__ uint32_t s_max[3][64];  // largest |g| of the column
+  __shared__ float s_w[CA ? kTcwSrc : 1][64 * kTcwWaves];  // w of the sources (each thread's own)
+  const int t = threadIdx.x, lane = t & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
+  const int X = a.X, Y = a.Y, B = tcol_band(a.arm_y);
+  // the bands of a strip are neighbours (they share their halo rows)
+  const int nstrips = (X + 63) / 64, nbands = (Y + B - 1) / B;
+  const int item = xcd_item(blockIdx.x, nstrips * nbands * a.npair * a.ndg);
+  if (item >= nstrips * nbands * a.npair * a.ndg) return;
+  const int x = item / nbands % nstrips * 64 + lane, Y0 = item % nbands * B;
+  const int pair = item / (nbands * nstrips) % a.npair, dg = item / (nbands * nstrips * a.npair);
+  const int nd = a.dhi - a.dlo;
+  const int d0 = a.dlo + dg * nd / a.ndg, n = a.dlo + (dg + 1) * nd / a.ndg - d0;
   const int Y1 = min(Y, Y0 + B);
   const bool xv = x < X;
   const int xc = min(x, X - 1);
   const size_t plane = (size_t)X * Y;
-  const int ys = max(0, Y0 - arm_y), ye = min(Y, Y1 + arm_y);
+  const int ys = max(0, Y0 - a.arm_y), ye = min(Y, Y1 + a.arm_y);
   // source row of slot i (wave-uniform), clamped into the sources
   auto src_row = [&](int i) { return min(ys + wave + kTcwWaves * i, ye - 1); };
-  // constants of the source rows ys + wave + 8 i (loads at clamped rows; a
-  // row outside the sources or a column past X gets A = 0, so it adds nothing)
+  // constants of the source rows (loads at clamped rows; a row outside the
+  // sources or a column past X gets A = 0, so it adds nothing; one whose window
+  // misses the band counts for the scale and adds q - q to row 0)
   float cA[kTcwSrc], cS[kTcwSrc], cD[kTcwSrc];
-  uint32_t cMN[kTcwSrc / 2];  // M | N << 8 of two rows, one per 16-bit half
+  // byte offsets (256 a row) of the difference rows lo and hi + 1 of two
+  // sources, in the 16-bit halves
+  uint32_t cLo[kTcwSrc / 2], cHi[kTcwSrc / 2];
 #pragma unroll
   for (int i = 0; i < kTcwSrc; ++i) {
     const int y = src_row(i);
-    const float4 q = pc[((size_t)pair * Y + y) * X + xc];
-    const uint32_t am = arms[((size_t)(2 * pair) * Y + y) * XA + xc] >> 16;
+    const float4 q = a.pc[((size_t)pair * Y + y) * X + xc];
+    const uint32_t am = a.arms[((size_t)(2 * pair) * Y + y) * a.XA + xc];
+    const int lo = max(y - (int)((am >> 16) & 255u), Y0), hi = min(y + (int)(am >> 24), Y1 - 1);
     cA[i] = xv && ys + wave + kTcwWaves * i < ye ? q.w : 0.f;
-    cS[i] = fast_exp2(-q.y);
+    cS[i] = CA ? -q.y : fast_exp2(-q.y);
+    if (CA) s_w[i][t] = q.x;
     cD[i] = q.z;
-    if (i & 1) cMN[i / 2] |= am << 16;
-    else cMN[i / 2] = am;
+    const bool in = lo <= hi;
+    const uint32_t el = in ? (uint32_t)(lo - Y0) << 8 : 0u, eh = in ? (uint32_t)(hi + 1 - Y0) << 8 : 0u;
+    if (i & 1) {
+      cLo[i / 2] |= el << 16;
+      cHi[i / 2] |= eh << 16;
+    } else {
+      cLo[i / 2] = el;
+      cHi[i / 2] = eh;
+    }
   }
   // weight loads: the lane's column in the vector offset, the row and plane
   // (wave-uniform) in the scalar one
-  const __amdgpu_buffer_rsrc_t rw = buffer_rsrc(wts, wts_bytes);
+  const __amdgpu_buffer_rsrc_t rw = buffer_rsrc(a.wts, a.wts_bytes);
   const uint32_t vcol = (uint32_t)xc * 4u;
-  const int rpw = B / kTcwWaves, r0 = wave * rpw;
-  // the weights of disparity d into w[]; the next disparity's are loaded
-  // while this one is processed (past the range: the last one again)
-  auto load_w = [&](int d, float (&w)[kTcwSrc]) {
-    const uint32_t sp = (uint32_t)(((size_t)min(d, dhi - 1) * npair + pair) * plane * 4);
+  float w[kTcwSrc], g[kTcwSrc];
+  auto load_w = [&](int k) {  // past the range: the last one again
+    const uint32_t sp =
+        (uint32_t)(((size_t)(d0 + min(k, n - 1) - a.wlo) * a.npair + pair) * plane * 4);
 #pragma unroll
     for (int i = 0; i < kTcwSrc; ++i)
       w[i] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(
           rw, vcol, sp + (uint32_t)src_row(i) * (uint32_t)X * 4u, 0));
   };
-  float wn[kTcwSrc];
-  if (dlo < dhi) load_w(dlo, wn);
-  for (int d = dlo; d < dhi; ++d) {
-    const float fd = (float)d;
-    float g[kTcwSrc];
-#pragma unroll
-    for (int i = 0; i < kTcwSrc; ++i) g[i] = wn[i];
-    load_w(d + 1, wn);
-    float mx = 0.f;
+  auto stage_a = [&](int k, uint32_t* mx) {
+    const float fd = (float)(d0 + k);
+    float m = 0.f;
 #pragma unroll
     for (int i = 0; i < kTcwSrc; ++i) {
-      g[i] = cA[i] * (g[i] * cS[i]) * (fd - cD[i]);
-      mx = fmaxf(mx, fabsf(g[i]));
+      const float p = CA ? fast_exp2(fmaf(-w[i], s_w[i][t], cS[i])) : w[i] * cS[i];
+      g[i] = cA[i] * p * (fd - cD[i]);
+      m = fmaxf(m, fabsf(g[i]));
     }
-    s_max[wave][lane] = mx;
-    for (int i = threadIdx.x; i < (B + 1) * 64; i += 64 * kTcwWaves) (&s_d[0][0])[i] = 0;
-    __syncthreads();
-    float cmax = 0.f;
+    // the bit order of floats >= 0 is that of their values
+    (void)__hip_atomic_fetch_max(mx + lane, __float_as_uint(m), __ATOMIC_RELAXED,
+                                 __HIP_MEMORY_SCOPE_WORKGROUP);
+  };
+  auto zero = [&](int (*dst)[64]) {
+    for (int i = t; i < (B + 1) * 16; i += 64 * kTcwWaves)
+      reinterpret_cast<u32x4*>(&dst[0][0])[i] = u32x4{0u, 0u, 0u, 0u};
+  };
+  // output rows Y0 + r0 .. of this wave, and the lane's place in a row
+  const int rpw = B / kTcwWaves, r0 = wave * rpw;
+  const size_t dstride = (size_t)a.npair * plane;
+  float* gout = a.gcax + ((size_t)(d0 - a.dlo) * a.npair + pair) * plane + (size_t)(Y0 + r0) * X + x;
+  if (n <= 0) return;  // block-uniform
+  load_w(0);
+  if (t < 192) (&s_max[0][0])[t] = 0u;
+  zero(s_d[0]);
+  __syncthreads();
+  stage_a(0, s_max[0]);
+  load_w(1);
+  __syncthreads();
+  int loc[RPW];
+  uint32_t mC = 0, mD = 0;  // column maxima of the disparities in stages C and D
+  int b0 = 0, b1 = 2, b2 = 1;  // difference arrays of stage B, C, and the one to clear
+  for (int k = 0; k < n + 2; ++k) {
+    uint32_t mB = 0;
+    if (k < n) {  // B
+      mB = s_max[b0][lane];
+      const float up = mB ? ldexpf(1.f, 23 - float_exp(mB)) : 0.f;
+      char* col = reinterpret_cast<char*>(&s_d[b0][0][lane]);
 #pragma unroll
-    for (int w = 0; w < kTcwWaves; ++w) cmax = fmaxf(cmax, s_max[w][lane]);
-    int e = 0;
-    (void)frexpf(cmax, &e);
-    const float up = cmax > 0.f ? ldexpf(1.f, 23 - e) : 0.f;
+      for (int i = 0; i < kTcwSrc; ++i) {
+        const int q = (int)rintf(g[i] * up);
+        const uint32_t lo = i & 1 ? cLo[i / 2] >> 16 : cLo[i / 2] & 0xffffu;
+        const uint32_t hi = i & 1 ? cHi[i / 2] >> 16 : cHi[i / 2] & 0xffffu;
+        (void)__hip_atomic_fetch_add(reinterpret_cast<int*>(col + lo), q, __ATOMIC_RELAXED,
+                                     __HIP_MEMORY_SCOPE_WORKGROUP);
+        (void)__hip_atomic_fetch_sub(reinterpret_cast<int*>(col + hi), q, __ATOMIC_RELAXED,
+                                     __HIP_MEMORY_SCOPE_WORKGROUP);
+      }
+    }
+    if (k + 1 < n) {  // A of the next disparity
+      stage_a(k + 1, s_max[b2]);
+      load_w(k + 2);
+      zero(s_d[b2]);
+    }
+    if (k >= 2) {  // D
+      int off = 0, s0 = 0;
+      // the totals above: the wave's number as 8 + 4 + 2 + 1, groups of reads
+      // in flight together
 #pragma unroll
-    for (int i = 0; i < kTcwSrc; ++i) {
-      const int q = (int)rintf(g[i] * up);
-      if (q != 0) {
-        const int y = ys + wave + kTcwWaves * i;
-        const uint32_t mn = cMN[i / 2] >> (16 * (i & 1));
-        const int M = (int)(mn & 255u), N = (int)((mn >> 8) & 255u);
-        const int lo = max(y - M, Y0), hi = min(y + N, Y1 - 1);
-        if (lo <= hi) {
-          atomicAdd(&s_d[lo - Y0][lane], q);
-          if (hi + 1 < Y1) atomicAdd(&s_d[hi + 1 - Y0][lane], -q);
+      for (int m = kTcwWaves / 2; m > 0; m >>= 1)
+        if (wave & m) {
+          int v[8];
+#pragma unroll
+          for (int s = 0; s < m; ++s) v[s] = s_tot[k & 1][s0 + s][lane];
+#pragma unroll
+          for (int s = 0; s < m; ++s) off += v[s];
+          s0 += m;
         }
+      if (xv) {
+        const float down = mD ? ldexpf(1.f, float_exp(mD) - 23) : 0.f;
+        float* o = gout + (size_t)(k - 2) * dstride;
+#pragma unroll
+        for (int i = 0; i < RPW; ++i)
+          if (i < rpw && Y0 + r0 + i < Y1) o[(size_t)i * X] = (float)(loc[i] + off) * down;
       }
     }
-    __syncthreads();
-    // prefix down the column: wave w takes rows w B/8 .. (w+1) B/8 - 1
-    int run = 0;
-    int loc[kTcolBand / kTcwWaves];
+    if (k >= 1 && k <= n) {  // C
+      int run = 0;
 #pragma unroll
-    for (int i = 0; i < kTcolBand / kTcwWaves; ++i) {
-      if (i < rpw) run += s_d[r0 + i][lane];
-      loc[i] = run;
-    }
-    s_tot[wave][lane] = run;
-    __syncthreads();
-    int off = 0;
-#pragma unroll
-    for (int w = 0; w < kTcwWaves - 1; ++w) off += w < wave ? s_tot[w][lane] : 0;
-    if (xv) {
-      const float down = cmax > 0.f ? ldexpf(1.f, e - 23) : 0.f;
-      float* out = gcax + ((size_t)d * npair + pair) * plane + x;
-#pragma unroll
-      for (int i = 0; i < kTcolBand / kTcwWaves; ++i) {
-        const int y = Y0 + r0 + i;
-        if (i < rpw && y < Y1) out[(size_t)y * X] = (float)(loc[i] + off) * down;
+      for (int i = 0; i < RPW; ++i) {
+        if (i < rpw) run += s_d[b1][r0 + i][lane];
+        loc[i] = run;
       }
+      s_tot[(k - 1) & 1][wave][lane] = run;
+      if (t < 64) s_max[b1][t] = 0u;  // for the disparity two further
     }
+    mD = mC;
+    mC = mB;
+    const int nb = b2;
+    b2 = b1;
+    b1 = b0;
+    b0 = nb;
+    __syncthreads();
   }
 }
 
@@ -714,7 +713,7 @@ __global__ void __launch_bounds__(64 * kTcwWaves) k_soft_tcolw(
 // cost derivatives there, summed over the slab into the half-image gradients.
 //   CA_x(x,y) = sum_{t=-m}^{n} C(x+t,y) transposes to a difference array
 //   along the row (+g at x - m, -g at x + n + 1) and a prefix along it,
-//   giving dL/dC from dL/dCA_x (k_soft_tcol's planes).
+//   giving dL/dC from dL/dCA_x (k_soft_tcolw's planes).
 // Then with dI = L(x,y) - R(x-d,y), a = 255 |dI|, E = e^{-a/lambda_AD}:
 //   t = dL/dC * dC/d(dI) = dL/dC * (255 / lambda_AD) E sign(dI)
 //   dL/dL(x,y)        += t       dL/dR(x-d,y) -= t
@@ -732,7 +731,7 @@ __global__ void __launch_bounds__(64 * kTcwWaves) k_soft_tcolw(
 // derivatives at output column x0 + l, so the disparity loop needs no
 // barrier (a wave's LDS
 // accesses are served in order).  The difference arrays are integer fixed
-// point with a per-row scale (as in k_soft_tcol: terms below 2^23, sums of
+// point with a per-row scale (as in k_soft_tcolw: terms below 2^23, sums of
 // at most 63 terms below 2^29), added with LDS integer atomics, so the
 // result does not depend on their order.  The left gradient of a pixel stays
 // in a register over the slab and goes to g_half once (written by the first
@@ -778,6 +777,7 @@ __device__ __forceinline__ uint32_t wave_max_u32(uint32_t v) {
   return (uint32_t)__builtin_amdgcn_readlane((int)v, 63);
 }
 
+constexpr int kSoftBR = 4;  // output rows per k_soft_tr workgroup (one per wave)
 constexpr int kTrMaxWP = 64 + 127;  // 64 columns + a slab of up to 128 disparities
 
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) k_soft_tr(TrArgs a) {

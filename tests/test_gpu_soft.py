@@ -374,3 +374,63 @@ def test_saved_weights_dropped_by_a_later_forward(ctx):
     got = soft_grads(ctx, left, right, lam, 30, p, g, 0, SOFT_F_REUSE_FEATURES)
     for u, v in zip(got, ref):
         assert np.array_equal(u, v)
+
+
+@pytest.mark.parametrize("case", [
+    # 135 disparities: two slabs, whose terms the backward forms from saved CA
+    dict(W=290, H=14, dmax=270, n=1, seed=600),
+    # 768 half rows: three bands of k_soft_agg with 382 rows at most (24 a wave).
+    # 4 columns only: among many pixels some pair of half-image intensities is
+    # nearer than float rounding, and the sign of its difference is not the oracle's
+    dict(W=8, H=1536, dmax=4, n=1, seed=601, arm_y=63),
+    # bands with 17 and 18 rows a wave, two strips, the second of one column
+    dict(W=130, H=440, dmax=10, n=1, seed=602),
+])
+def test_slabs_and_bands_match_oracle(ctx, case):
+    """The largest arrangements of k_soft_agg and the slabs beyond one, saved and
+    computed again, against the oracle."""
+    W, H, dmax, n, seed = case["W"], case["H"], case["dmax"], case["n"], case["seed"]
+    p = osoft.SoftParams(**({"arm_y": case["arm_y"]} if "arm_y" in case else {}))
+    L, R, G, M = float_pairs(n, W, H, dmax, seed, noise=0.002)
+    print(f"[soft] slabs and bands {W}x{H} Dmax={dmax}", flush=True)
+    ref = oracle_dhat(L, R, dmax, p)
+    rloss, rgl, rgr, rglam = osoft.loss_and_grads(list(L), list(R), list(G), list(M), dmax, p)
+    for slab in (0, 7):
+        d_hat, loss, gl, gr, glam = run_gpu(ctx, L, R, G, M, dmax, p, slab=slab)
+        assert float(np.abs(d_hat - ref).max()) <= 1e-3
+        assert_grad_close(gl, rgl, "g_left")
+        assert_grad_close(gr, rgr, "g_right")
+        for k in range(2):
+            assert abs(glam[k] - rglam[k]) <= 1e-3 * abs(rglam[k]) + 1e-9, (k, glam, rglam)
+
+
+def test_scratch_cap_shrinks_the_planes(ctx):
+    """Under smaller and smaller scratch caps a plan holds the weights of all D, of
+    a slab, of smaller slabs, and at last is refused; the map stays the same and
+    the gradients stay those of the uncapped plan to float rounding (sums over
+    slabs of other sizes; dL/dlambda's terms cancel by three digits)."""
+    from paper_2212_00488_amd.binding import SOFT_F_REUSE_FEATURES, SOFT_F_SAVE_WEIGHTS, StereoError
+    p, dmax = osoft.SoftParams(), 128
+    L, R, G, M = float_pairs(1, 150, 60, dmax, 610, noise=0.002)
+    left, right = to_dev(L), to_dev(R)
+    lam = torch.tensor((p.lambda_ad, p.lambda_census), dtype=torch.float32, device=DEV)
+    g = to_dev(np.random.default_rng(610).standard_normal((1, 30, 75)).astype(np.float32))
+    ref = soft_grads(ctx, left, right, lam, dmax, p, g, SOFT_F_SAVE_WEIGHTS, SOFT_F_REUSE_FEATURES)
+    # planes of all 64 disparities take 2 x 600 kB
+    ran, refused = 0, 0
+    for cap in (4000, 2200, 1700, 1400, 1200, 1000, 900, 800, 100):
+        small = Stereo(0, mem_cap=cap * 1000)
+        try:
+            got = soft_grads(small, left, right, lam, dmax, p, g, SOFT_F_SAVE_WEIGHTS,
+                             SOFT_F_REUSE_FEATURES)
+        except StereoError:
+            refused += 1
+            continue
+        finally:
+            small.close()
+        ran += 1
+        assert np.array_equal(got[0], ref[0])
+        assert_grad_close(got[1], ref[1], f"g_left, cap {cap} kB", rel=1e-5, rel_elem=1e-4)
+        assert_grad_close(got[2], ref[2], f"g_right, cap {cap} kB", rel=1e-5, rel_elem=1e-4)
+        assert np.all(np.abs(got[3] - ref[3]) <= 1e-4 * np.abs(ref[3])), (cap, got[3], ref[3])
+    assert ran >= 3 and refused >= 1, (ran, refused)
