@@ -153,7 +153,9 @@ __global__ void __launch_bounds__(256) k_prep(PairPtrs pp, int W, int H, int X, 
 
 // ---------------------------------------------------------------- k_feat
 // Packed half-res pixels.  The differentiable head takes {the float half
-// image value's bits, census string} (8 bytes).  k_match takes gray in
+// image value's bits, census string in each of the four bytes} (8 bytes; the
+// bit count of an xor of two such words is the byte offset of the distance in a
+// table of floats).  k_match takes gray in
 // bits 0..7 and the census string in bits 8..13 (16 bits), two pixels per
 // 32-bit load; that plane is stored twice, the second copy one pixel to the
 // right, so that the pair of pixels starting at any column is one aligned
@@ -161,6 +163,7 @@ __global__ void __launch_bounds__(256) k_prep(PairPtrs pp, int W, int H, int X, 
 // k_match's row loads are bound by).
 constexpr int kFeatRows = 16;    // output rows per k_feat workgroup (one pixel per thread)
 constexpr int kMaxArm = 127;
+constexpr uint32_t kCensus4 = 0x01010101u;  // a census string (6 bits) to four bytes
 
 // Length of one arm of a pixel of value c: the number of steps t = 1, 2, ...
 // along the axis, taken without a break, whose pixel satisfies |I - c| < delta,
@@ -229,7 +232,7 @@ __device__ __forceinline__ int arm_len(const uint8_t* p, int c, int delta, int c
 //   arms  : contiguous pixels with |I - I(centre)| < delta, capped per side
 //           and at the image border; packed m | n<<8 | M<<16 | N<<24
 // Pixels go to sp ({bits of half_f at the pixel (an unpadded [Y][X] plane per
-// image), census}, may be NULL) and to the two copies of pk16 (gray | census
+// image), kCensus4 * census}, may be NULL) and to the two copies of pk16 (gray | census
 // << 8, may be NULL; the second copy copy16 elements after the first, one
 // pixel to the right); pitch XP, column x at pad + x.
 // xoff (may be NULL) takes, for k_match's row pass, the distances in bytes
@@ -330,7 +333,7 @@ k_feat(const uint8_t* __restrict__ half, int X, int Y, int delta, int arm_x_l, i
     const int N = arm_len<64>(col, c, delta, arm_y, min(arm_y, Y - 1 - y));
     if (sp)
       sp[((size_t)img * Y + y) * XP + pad + x] =
-          make_uint2(__float_as_uint(half_f[((size_t)img * Y + y) * X + x]), (uint32_t)bits);
+          make_uint2(__float_as_uint(half_f[((size_t)img * Y + y) * X + x]), (uint32_t)bits * kCensus4);
     arms[((size_t)img * Y + y) * XA + x] =
         (uint32_t)m | ((uint32_t)n << 8) | ((uint32_t)M << 16) | ((uint32_t)N << 24);
     if (xoff)

@@ -148,7 +148,7 @@ size_t soft_bytes(const SoftPlan& pl, int nw, int nds) {
   return al(nimg * npix * 4) + al(nimg * npix) + al(nimg * Y * pl.XA * 4) +
          al(nimg * Y * pl.XS * 8) + al(n * npix * 4) + al(n * pl.nchunk * npix * 8) +
          al(n * npix * 16) + al(nw * n * npix * 4) + al(nds * n * npix * 4) +
-         al(nimg * npix * 4) + al(nslab * n * pl.nstrips * ((Y + kSoftBR - 1) / kSoftBR) * 8) +
+         al(nimg * npix * 4) + al(nslab * n * pl.nstrips * ((Y + kTrRows - 1) / kTrRows) * 8) +
          al(n * pl.nstrips * Y * (64 + nds - 1) * 4);
 }
 
@@ -204,7 +204,7 @@ int make_soft_plan(stereo_ctx* c, int n, int W, int H, int Dmax, const stereo_so
   pl->nw = nw;
   pl->nds = nds;
   pl->WP = 64 + nds - 1;
-  pl->lam_count = (size_t)((D + nds - 1) / nds) * n * pl->nstrips * ((Y + kSoftBR - 1) / kSoftBR);
+  pl->lam_count = (size_t)((D + nds - 1) / nds) * n * pl->nstrips * ((Y + kTrRows - 1) / kTrRows);
   pl->bytes = bytes;
   char* cur = static_cast<char*>(pl->block);
   pl->half_f = carve<float>(cur, nimg * npix);
@@ -463,7 +463,7 @@ int stereo_soft_backward(stereo_ctx* c, const float* left, const float* right, i
   };
   if (!saved && whole) weights(0, pl->D);
   int slab = 0;
-  const int lam_slab = pl->nstrips * ((Y + kSoftBR - 1) / kSoftBR) * pl->n;
+  const int lam_slab = pl->nstrips * ((Y + kTrRows - 1) / kTrRows) * pl->n;
   for (int dlo = 0; dlo < pl->D; dlo += pl->nds, ++slab) {
     const int dhi = std::min(pl->D, dlo + pl->nds);
     if (!saved && !whole) weights(dlo, dhi);
@@ -485,10 +485,10 @@ int stereo_soft_backward(stereo_ctx* c, const float* left, const float* right, i
     ta.lam_part = pl->lam_part + (size_t)slab * lam_slab;
     ta.X = X; ta.Y = Y; ta.XS = pl->XS; ta.pads = pl->pads; ta.XA = pl->XA;
     ta.npair = pl->n; ta.dlo = dlo; ta.dhi = dhi; ta.WP = pl->WP;
-    ta.nstrips = pl->nstrips; ta.nbands = (Y + kSoftBR - 1) / kSoftBR;
+    ta.nstrips = pl->nstrips;
     ta.first = dlo == 0;  // the first slab writes every half-image gradient
-    hipLaunchKernelGGL(k_soft_tr, dim3((unsigned)(ta.nstrips * ta.nbands), (unsigned)pl->n), dim3(256),
-                       0, stream, ta);
+    hipLaunchKernelGGL(k_soft_tr, dim3((unsigned)((lam_slab + kXcds - 1) / kXcds * kXcds)), dim3(256), 0,
+                       stream, ta);
     hipLaunchKernelGGL(k_soft_gright, dim3((X + 255) / 256, Y, pl->n), dim3(256), 0, stream,
                        pl->gr_part, pl->nstrips, pl->WP, dlo, dhi, X, Y, (int)(dlo == 0),
                        pl->g_half);

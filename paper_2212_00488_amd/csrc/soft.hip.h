@@ -218,6 +218,7 @@ __global__ void __launch_bounds__(kThreads) k_soft_agg(SoftArgs a) {
   extern __shared__ __align__(16) uint8_t s_agg[];
   auto s_row = reinterpret_cast<uint32_t(*)[128]>(s_agg);
   float* s_ex = reinterpret_cast<float*>(s_agg + kWaves * 128 * 4);
+  const uint32_t ex0 = lds_addr(s_ex);
   uint32_t* s_plane = reinterpret_cast<uint32_t*>(s_agg + kAggRowBytes);  // row 0 = zeros
 
   const int t = threadIdx.x, lane = t & 63;
@@ -282,7 +283,8 @@ __global__ void __launch_bounds__(kThreads) k_soft_agg(SoftArgs a) {
   // cost of a pair of pixels in fixed point (the columns without a match apart)
   auto cost = [&](uint32_t lv, uint32_t lc, uint32_t rv, uint32_t rc) -> uint32_t {
     const float di = fabsf(__uint_as_float(lv) - __uint_as_float(rv));
-    const float cf = (2.f - fast_exp2(-di * k2)) - s_ex[__builtin_popcount(lc ^ rc)];
+    const float ex = __uint_as_float(lds_read(__builtin_popcount(lc ^ rc) + ex0));
+    const float cf = (2.f - fast_exp2(-di * k2)) - ex;
     return (uint32_t)(cf * fx + 0.5f);
   };
   const uint32_t cout = (uint32_t)(2.f * fx + 0.5f);
@@ -708,39 +710,44 @@ __global__ void __launch_bounds__(64 * kTcwWaves) k_soft_tcolw(TcwArgs a) {
 }
 
 // ------------------------------------------------------------- k_soft_tr
-// Transpose of the horizontal window sum (Eq. 7) over a 64-column strip and
-// a band of kSoftBR rows, for every disparity of a slab in turn, then the
-// cost derivatives there, summed over the slab into the half-image gradients.
-//   CA_x(x,y) = sum_{t=-m}^{n} C(x+t,y) transposes to a difference array
-//   along the row (+g at x - m, -g at x + n + 1) and a prefix along it,
-//   giving dL/dC from dL/dCA_x (k_soft_tcolw's planes).
-// Then with dI = L(x,y) - R(x-d,y), a = 255 |dI|, E = e^{-a/lambda_AD}:
+// Transpose of the horizontal window sum (Eq. 7), then the cost derivatives
+// there, summed over a slab of disparities into the half-image gradients.
+//   CA_x(x,y) = sum_{t=-m}^{n} C(x+t,y)  gives
+//   dL/dC(c,y,d) = sum over the x with x - m(x) <= c <= x + n(x) of
+//                  dL/dCA_x(x,y,d):
+// for a row, a product of the [disparity][x] matrix with the 0/1 matrix
+// [x][c] of the row's arms, which is the same for every disparity.  Then with
+// dI = L(x,y) - R(x-d,y), a = 255 |dI|, E = e^{-a/lambda_AD}:
 //   t = dL/dC * dC/d(dI) = dL/dC * (255 / lambda_AD) E sign(dI)
 //   dL/dL(x,y)        += t       dL/dR(x-d,y) -= t
 //   dL/dlambda_AD     += dL/dC * (-E a / lambda_AD^2)
 //   dL/dlambda_census += dL/dC * (-e^{-H/lambda_census} H / lambda_census^2)
 // for x - d >= 0 (the constant cost of x - d < 0 has no derivative).
-// The sources of a row are the columns x0 - 32 .. x0 + 95 (every column
-// whose horizontal window reaches the strip, arm_x <= 31).  Wave w owns the
-// band rows w + 4 i, i < kSoftBR / 4 (one row with bands of 4: 51 VGPRs, 8
-// waves per SIMD, and the grid of 5952 workgroups at the paper's size takes
-// 2.9 rounds; bands of 16 rows took 120 VGPRs and 1.45 rounds, and ran
-// slower than bands of 8, which ran slower than bands of 4): lane l loads
-// source columns x0 - 32 + l and x0 + 32 + l of them (coalesced), scatters
-// them into the rows' difference arrays, scans the rows and takes the
-// derivatives at output column x0 + l, so the disparity loop needs no
-// barrier (a wave's LDS
-// accesses are served in order).  The difference arrays are integer fixed
-// point with a per-row scale (as in k_soft_tcolw: terms below 2^23, sums of
-// at most 63 terms below 2^29), added with LDS integer atomics, so the
-// result does not depend on their order.  The left gradient of a pixel stays
-// in a register over the slab and goes to g_half once (written by the first
-// slab, added by the others); the right one, at column x - d, goes to the
-// wave's LDS row (one writer per entry and
-// disparity, disparities in order) and then to this strip's partial row,
-// which k_soft_gright sums over the strips.  The horizontal arms and the
-// left pixels do not depend on d and are loaded once.
-// grid: (strips * bands, n), block 256.
+// A wave takes 64 columns of one row.  The 0/1 matrix of the 128 source columns
+// x0 - 32 .. x0 + 95 (every column whose window reaches the strip, arm_x <= 31)
+// is built once, in registers, and the matrix cores form 16 disparities x 64
+// columns at a time (v_mfma_i32_16x16x64_i8: four groups of 16 columns, two
+// tiles of 64 sources).  The terms are integer fixed point with a scale
+// 2^(23 - e) per row and disparity, 2^(e-1) <= the largest |g| of the 128
+// sources < 2^e, each as three bytes: the sums of up to 63 terms stay below 2^30
+// and are exact, so the only rounding is that of a term to 2^(e-24).  (The lower
+// two bytes u are unsigned; the instruction's are signed, so u - 128 goes in and
+// 128 times the number of a column's sources is added.  Three bf16 terms of a
+// float are exact too, but the bf16 instruction's accumulation is biased:
+// dL/dlambda, a sum of millions of cancelling terms, lost three digits.)
+// The sums go through the wave's LDS tile, so that a lane takes the derivatives
+// of one column at the disparities in order: dL/dlambda cancels so far that its
+// float sums keep their digits only in a fixed order of additions.  The left
+// gradient of the column stays in a register; the right one, of column x - d,
+// is in the neighbouring lane at the next disparity: one lane shift, and the
+// values of a disparity go to an LDS row that ends with each entry's last one,
+// then to the strip's partial row, which k_soft_gright sums over the strips.
+// A block takes 4 rows of a strip.
+// Vector arithmetic bound (about 43 instructions a column and disparity, 16 of
+// them for the derivatives; three waves a SIMD).  4 pairs of 718x496, 73
+// disparities: 242 us as a scan and scatter of difference arrays in LDS, 202 now;
+// at 960x540 and 128 disparities 557 and 445.
+// grid: strips * ceil(Y / 4) * n rounded up to 8 (1-D, xcd_item), block 256.
 struct TrArgs {
   const float* gcax;        // [nds][n][Y][X] dL/dCA_x
   const uint32_t* arms;     // [2n][Y][XA]
@@ -749,226 +756,248 @@ struct TrArgs {
   float* g_half;            // [2n][Y][X] half-image gradients (left ones written or added here)
   float* gr_part;           // [n][strips][Y][WP] -dL/dR partials of this slab
   float2* lam_part;         // one {d/dlambda_AD, d/dlambda_census} per workgroup
-  int X, Y, XS, pads, XA, npair, dlo, dhi, nstrips, nbands, WP;
+  int X, Y, XS, pads, XA, npair, dlo, dhi, nstrips, WP;
   int first;                // first slab: the left gradients are written, not added
 };
 
-// Inclusive maximum scan over the 64 lanes of a wave of values >= 0 (the
-// steps of wave_scan_incl; lanes a shift reaches past the row's start see 0).
-__device__ __forceinline__ int wave_max_scan_incl(int v) {
-  v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, false));  // row_shr:1
-  v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, false));  // row_shr:2
-  v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, false));  // row_shr:4
-  v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, false));  // row_shr:8
-  v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, false));  // row_bcast:15
-  v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false));  // row_bcast:31
-  return v;
-}
-
-// Maximum over the 64 lanes of a wave (row rotations inside rows of 16
-// lanes, then row broadcasts; lane 63 ends with the maximum of all).
-__device__ __forceinline__ uint32_t wave_max_u32(uint32_t v) {
-  v = max(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x128, 0xf, 0xf, false));  // row_ror:8
-  v = max(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x124, 0xf, 0xf, false));  // row_ror:4
-  v = max(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x4e, 0xf, 0xf, false));   // quad_perm 2,3,0,1
-  v = max(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0xb1, 0xf, 0xf, false));   // quad_perm 1,0,3,2
-  v = max(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x142, 0xa, 0xf, false));  // row_bcast:15
-  v = max(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x143, 0xc, 0xf, false));  // row_bcast:31
-  return (uint32_t)__builtin_amdgcn_readlane((int)v, 63);
-}
-
-constexpr int kSoftBR = 4;  // output rows per k_soft_tr workgroup (one per wave)
 constexpr int kTrMaxWP = 64 + 127;  // 64 columns + a slab of up to 128 disparities
+constexpr int kTrD = 16;            // disparities of a tile
+constexpr int kTrRows = 4;          // rows of a block, one a wave
+constexpr int kTrPitch = 68;        // of an LDS tile: the four quarters' rows in different banks
+typedef uint16_t u16x2 __attribute__((ext_vector_type(2)));
+typedef int i32x4 __attribute__((ext_vector_type(4)));
 
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) k_soft_tr(TrArgs a) {
-  constexpr int BR = kSoftBR;
-  static_assert(BR % 4 == 0, "whole rows per wave");
-  constexpr int RPW = BR / 4;  // rows per wave: r = wave + 4 i
-  __shared__ int s_d[BR][64];
-  __shared__ float s_gr[BR][kTrMaxWP];
-  __shared__ float2 s_red[4];
+// Four bytes by selector: 0..3 take a byte of lo, 4..7 one of hi, 12 zero.
+__device__ __forceinline__ uint32_t perm8(uint32_t hi, uint32_t lo, uint32_t sel) {
+  return __builtin_amdgcn_perm(hi, lo, sel);
+}
+
+// -1, 0 or 1 by the sign of the integer v.
+__device__ __forceinline__ int sign_int(uint32_t v) {
+  int r;
+  __asm__("v_med3_i32 %0, %1, -1, 1" : "=v"(r) : "v"(v));
+  return r;
+}
+// max(m, |a|, |b|)
+__device__ __forceinline__ float max3_abs(float m, float a, float b) {
+  __asm__("v_max3_f32 %0, %1, |%2|, |%3|" : "=v"(m) : "v"(m), "v"(a), "v"(b));
+  return m;
+}
+
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) k_soft_tr(TrArgs a) {
+  __shared__ uint2 s_r[4][kTrMaxWP];
+  __shared__ float s_gr[4][kTrMaxWP];
+  __shared__ float s_g[4][kTrD][kTrPitch];
+  __shared__ __align__(16) float s_dn[4][kTrD];  // per wave: scales of a tile's disparities
   __shared__ float s_hc[4][8];  // per wave: the census term of dC/dlambda_census by h
-  const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
-  const int strip = blockIdx.x % a.nstrips, band = blockIdx.x / a.nstrips;
-  const int pair = blockIdx.y;
+  __shared__ float2 s_red[4];
+  const int t = threadIdx.x, lane = t & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
+  const int nbands = (a.Y + kTrRows - 1) / kTrRows, count = a.nstrips * nbands * a.npair;
+  const int item = xcd_item(blockIdx.x, count);
+  if (item >= count) return;
+  const int strip = item % a.nstrips, y = item / a.nstrips % nbands * kTrRows + wave;
+  const int pair = item / (a.nstrips * nbands);
   const int X = a.X, Y = a.Y;
-  const int x0 = strip * 64, y0 = band * BR;
-  const size_t plane = (size_t)X * Y;
-  const uint32_t* arm = a.arms + (size_t)(2 * pair) * Y * a.XA;
-  const uint2* spl = a.sp + (size_t)(2 * pair) * Y * a.XS + a.pads;
-  const uint2* spr = a.sp + (size_t)(2 * pair + 1) * Y * a.XS + a.pads;
-  const int x = x0 + lane;
-  const bool xin = x < X;
-  // per row i and source h: column x0 - 32 + 64 h + lane
-  int ys[RPW];
-  bool yv[RPW], cv[RPW][2];
-  uint32_t mv[RPW][2];
-  uint2 pl_[RPW];
-  float gl[RPW];
-#pragma unroll
-  for (int i = 0; i < RPW; ++i) {
-    const int y = y0 + wave + 4 * i;
-    yv[i] = y < Y;
-    ys[i] = min(y, Y - 1);
-#pragma unroll
-    for (int h = 0; h < 2; ++h) {
-      const int col = x0 - 32 + 64 * h + lane;
-      cv[i][h] = yv[i] && col >= 0 && col < X;
-      mv[i][h] = arm[(size_t)ys[i] * a.XA + min(max(col, 0), X - 1)];
-    }
-    pl_[i] = xin ? spl[(size_t)ys[i] * a.XS + x] : make_uint2(0u, 0u);
-    gl[i] = 0.f;
-    for (int c = lane; c < kTrMaxWP; c += 64) s_gr[wave + 4 * i][c] = 0.f;
-  }
-  // Each source adds +q at the left end of its window (its position clamped
-  // to the strip's first column) and -q after the right end (when that is
-  // inside the strip).  Neighbouring sources whose windows end at the same
-  // edge form runs of lanes with the same position, which would serialise
-  // their atomics on one address.  The runs do not depend on d: per row,
-  // source set h and end, 16 bits give the lane before the run's first
-  // (bits 0..7, as a ds_bpermute address) and whether it exists (bit 8),
-  // whether this lane ends a run of contributing sources (bit 9) and the
-  // position (bits 10..15); the left end's in the low half of a word, the
-  // right end's in the high half.  Per d and source set one wave scan of the
-  // terms serves both ends: each run's sum is the scan at its last lane
-  // minus the scan before its first, added (left ends) or subtracted (right
-  // ends) by its last lane.
-  uint32_t rw[RPW][2];
-  auto run_word = [&](int key, bool ends, int pos) -> uint32_t {
-    const int kp = __builtin_amdgcn_update_dpp(1000, key, 0x138, 0xf, 0xf, false);  // wave_shr:1
-    const int kn = __builtin_amdgcn_update_dpp(1000, key, 0x130, 0xf, 0xf, false);  // wave_shl:1
-    const int hs = wave_max_scan_incl(key != kp ? lane : 0);  // first lane of the run
-    return (uint32_t)(max(hs - 1, 0) * 4) | (hs > 0 ? 256u : 0u) |
-           (ends && key != kn ? 512u : 0u) | (uint32_t)(pos & 63) << 10;
-  };
-#pragma unroll
-  for (int i = 0; i < RPW; ++i) {
-#pragma unroll
-    for (int h = 0; h < 2; ++h) {
-      const int col = x0 - 32 + 64 * h + lane;
-      const int lo = col - (int)(mv[i][h] & 255u) - x0;
-      const int hi = col + (int)((mv[i][h] >> 8) & 255u) + 1 - x0;
-      // the window reaches the strip (lo < 64 for h = 0 and hi > 0 for h = 1
-      // always hold with arm_x <= 31)
-      const bool part = cv[i][h] && (h == 0 ? hi > 0 : lo < 64);
-      const int plo = max(lo, 0);
-      const bool phi = part && hi < 64;
-      rw[i][h] = run_word(part ? plo : -1 - lane, part, plo) |
-                 run_word(phi ? hi : -1 - lane, phi, hi) << 16;
-    }
-  }
-  const float lam_ad = a.lam[0], lam_c = a.lam[1];
-  const float k2 = 255.f * 1.4426950408889634f / lam_ad;
-  const float kt = 255.f / lam_ad, ka = 1.f / (lam_ad * lam_ad), kc = 1.f / (lam_c * lam_c);
-  const float l2c = 1.4426950408889634f / lam_c;
-  // -e^{-h/lambda_census} h / lambda_census^2 for h = 0..6, one copy per wave
-  // (a wave's LDS accesses are served in order: no barrier)
-  if (lane < 7) s_hc[wave][lane] = -fast_exp2(-(float)lane * l2c) * (float)lane * kc;
-  WAVE_LDS_ORDER();
+  const int l16 = lane & 15, quarter = lane >> 4;
   float pa = 0.f, pcs = 0.f;
-  // the loads of disparity d + 1 are issued before d is processed (two
-  // register sets used in turn; the last disparity is reloaded past the end,
-  // so the loads are unconditional and the waits stay exact)
-  struct DIn {
-    float g[RPW][2];
-    uint2 pr[RPW];
-  };
-  const float* gbase = a.gcax + (size_t)pair * plane;
-  const size_t dstride = (size_t)a.npair * plane;
-  auto load_d = [&](int d, DIn& in) {
-    const float* g = gbase + (size_t)(d - a.dlo) * dstride;
-    const bool dv = x - d >= 0;
+  if (y < Y) {
+    const int x0 = strip * 64, x = x0 + lane;
+    const uint2* spl = a.sp + ((size_t)(2 * pair) * Y + y) * a.XS + a.pads;
+    const uint2* spr = spl + (size_t)Y * a.XS;
+    const uint32_t* arm = a.arms + ((size_t)(2 * pair) * Y + y) * a.XA;
+    const float* grow = a.gcax + ((size_t)pair * Y + y) * X;
+    const size_t dstride = (size_t)a.npair * Y * X;
+    const bool ends = x0 < 32 || x0 + 96 > X;  // some sources lie outside the image
+    // the sources of a tile of 16 disparities: source tile k, this lane's
+    // disparity (past the slab the last one again; its rows are not used) and its
+    // 16 columns x0 - 32 + 64 k + 16 quarter + j
+    float4 v[2][4];
+    auto load_tile = [&](int dt) {
+      const int dl = min(dt + l16, a.dhi - 1) - a.dlo;
 #pragma unroll
-    for (int i = 0; i < RPW; ++i) {
+      for (int k = 0; k < 2; ++k) {
+        // (a group past the row's end reads on, at most 15 columns into the
+        // next row or plane, or past the planes into the scratch behind them)
+        const int xs = x0 - 32 + 64 * k + 16 * quarter;
+        const float* gp = grow + (size_t)dl * dstride + min(max(xs, 0), (X - 1) & ~15);
 #pragma unroll
-      for (int h = 0; h < 2; ++h) {
-        const int cc = min(max(x0 - 32 + 64 * h + lane, 0), X - 1);
-        in.g[i][h] = g[ys[i] * X + cc];
+        for (int j = 0; j < 4; ++j) __builtin_memcpy(&v[k][j], gp + 4 * j, 16);
       }
-      in.pr[i] = spr[ys[i] * a.XS + min(max(x - d, 0), X - 1)];
-      if (!(xin && dv)) in.pr[i] = make_uint2(0u, 0u);
-    }
-  };
-  auto process_d = [&](int d, const DIn& in) {
-    const bool dv = x - d >= 0;
-    // the wave's LDS accesses stay in program order across lanes: the
-    // compiler may not move one across these points
+    };
+    load_tile(a.dlo);
+    // right pixels of columns x0 - dhi + 1 .. x0 + 63 - dlo (the plane's padding
+    // reads zero outside the image)
+    const int wd = 64 + (a.dhi - a.dlo) - 1;
+    for (int i = lane; i < wd; i += 64) s_r[wave][i] = spr[x0 - a.dhi + 1 + i];
+    const float lam_ad = a.lam[0], lam_c = a.lam[1];
+    const float k2 = 255.f * 1.4426950408889634f / lam_ad;
+    const float kt = 255.f / lam_ad, ka = 1.f / (lam_ad * lam_ad), kc = 1.f / (lam_c * lam_c);
+    const float l2c = 1.4426950408889634f / lam_c;
+    // -e^{-h/lambda_census} h / lambda_census^2 for h = 0..6, one copy per wave
+    // (a wave's LDS accesses are served in order: no barrier)
+    if (lane < 7)
+      s_hc[wave][lane] = -fast_exp2(-(float)lane * l2c) * (float)lane * kc;
     WAVE_LDS_ORDER();
+    const uint32_t hc0 = lds_addr(s_hc[wave]);
+    uint2 lp = spl[x];
+    lp.x = __float_as_uint(__uint_as_float(lp.x) + 0.f);  // (-0 - 0 would be -0)
+    // the 0/1 matrix: of source tile k, this lane's 16 sources against its column
+    // of group n, one byte each.  A source x holds column c when v = c - x + m
+    // and m + n - v are both >= 0; two sources a word, in 16 bits, where the sign
+    // byte of either is 0xff or 0.  Sources left of the image or past
+    // the rows of arms hold none; those between X and there have no arms.
+    uint32_t bm[4][2][4];
+    int k128[4] = {0, 0, 0, 0};  // the number of the column's sources, then 128 times it
 #pragma unroll
-    for (int i = 0; i < RPW; ++i) s_d[wave + 4 * i][lane] = 0;
-    WAVE_LDS_ORDER();
-    float down[RPW];
+    for (int k = 0; k < 2; ++k) {
+      const int xs = x0 - 32 + 64 * k + 16 * quarter;  // first of the 16
+      const uint4* ap = reinterpret_cast<const uint4*>(arm + min(max(xs, 0), a.XA - 16));
+      const uint32_t rel = (uint32_t)(x0 + l16 - xs) & 0xffffu;  // c - x of source 0, group 0
+      const u16x2 rel2 = {(uint16_t)rel, (uint16_t)rel};
 #pragma unroll
-    for (int i = 0; i < RPW; ++i) {
-      const int r = wave + 4 * i;
-      const float g0 = cv[i][0] ? in.g[i][0] : 0.f, g1 = cv[i][1] ? in.g[i][1] : 0.f;
-      // the row's scale 2^(23 - e), 2^(e - 1) <= max |g| < 2^e (frexp's e),
-      // from the largest magnitude's bits (the bit order of floats >= 0)
-      const uint32_t mb = wave_max_u32(max(__float_as_uint(g0) & 0x7fffffffu,
-                                           __float_as_uint(g1) & 0x7fffffffu));
-      const int be = (int)(mb >> 23);
-      const int e = be > 0 ? be - 126 : -117 - (int)__builtin_clz(mb | 1u);
-      const float up = mb ? ldexpf(1.f, 23 - e) : 0.f;
-      down[i] = mb ? ldexpf(1.f, e - 23) : 0.f;
+      for (int jj = 0; jj < 4; ++jj) {
+        const uint4 w4 = ap[jj];
 #pragma unroll
-      for (int h = 0; h < 2; ++h) {
-        const int q = (int)rintf((h ? g1 : g0) * up);
-        const int P = (int)wave_scan_incl((uint32_t)q);
-        const uint32_t w = rw[i][h];
-        const int Pl = __builtin_amdgcn_ds_bpermute((int)(w & 255u), P);
-        const int Ph = __builtin_amdgcn_ds_bpermute((int)((w >> 16) & 255u), P);
-        if (w & (512u << 16)) atomicSub(&s_d[r][w >> 26], P - ((w & (256u << 16)) ? Ph : 0));
-        if (w & 512u) atomicAdd(&s_d[r][(w >> 10) & 63u], P - ((w & 256u) ? Pl : 0));
+        for (int i = 0; i < 2; ++i) {
+          // m and m + n of sources 4 jj + 2 i, + 1
+          const uint32_t wa = i ? w4.z : w4.x, wb = i ? w4.w : w4.y;
+          const u16x2 m = __builtin_bit_cast(u16x2, perm8(wb, wa, 0x0c040c00u));
+          u16x2 l = m + __builtin_bit_cast(u16x2, perm8(wb, wa, 0x0c050c01u));
+          l = (uint32_t)xs < (uint32_t)a.XA ? l : u16x2{0xff80, 0xff80};  // -128: below every v
+          const u16x2 v0 = rel2 + m - u16x2{(uint16_t)(4 * jj + 2 * i), (uint16_t)(4 * jj + 2 * i + 1)};
+#pragma unroll
+          for (int n = 0; n < 4; ++n) {
+            const u16x2 v2 = v0 + u16x2{(uint16_t)(16 * n), (uint16_t)(16 * n)};
+            const uint32_t miss = __builtin_bit_cast(uint32_t, v2) | __builtin_bit_cast(uint32_t, l - v2);
+            if (i == 0) {
+              bm[n][k][jj] = miss;
+            } else {
+              const uint32_t b = ~perm8(miss, bm[n][k][jj], 0x07050301u) & 0x01010101u;
+              bm[n][k][jj] = b;
+              k128[n] += __builtin_popcount(b);
+            }
+          }
+        }
       }
     }
-    WAVE_LDS_ORDER();
-    // prefix along each row, then the cost derivatives; the right gradient
-    // of column x - d sits at s_gr[r][x - d - (x0 - dhi + 1)]
-    const int gcol = lane + (a.dhi - 1 - d);
 #pragma unroll
-    for (int i = 0; i < RPW; ++i) {
-      const int r = wave + 4 * i;
-      const float gc = (float)(int)wave_scan_incl((uint32_t)s_d[r][lane]) * down[i];
-      if (xin && dv && yv[i]) {
-        const float di = __uint_as_float(pl_[i].x) - __uint_as_float(in.pr[i].x);
-        const float ad = fabsf(di);
+    for (int n = 0; n < 4; ++n) {
+      k128[n] += __shfl_xor(k128[n], 16);
+      k128[n] = 128 * (k128[n] + __shfl_xor(k128[n], 32));
+    }
+    float gl = 0.f, gr = 0.f;
+    for (int dt = a.dlo; dt < a.dhi; dt += kTrD) {
+      // scale of this lane's disparity, from its 32 values and the other quarters'
+      float mx = 0.f;
+      if (ends) {
+#pragma unroll
+        for (int k = 0; k < 2; ++k) {
+          int xs = x0 - 32 + 64 * k + 16 * quarter;
+          __asm__ volatile("" : "+v"(xs));  // keeps this a branch
+#pragma unroll
+          for (int j = 0; j < 4; ++j) {
+            v[k][j].x = (uint32_t)(xs + 4 * j) < (uint32_t)X ? v[k][j].x : 0.f;
+            v[k][j].y = (uint32_t)(xs + 4 * j + 1) < (uint32_t)X ? v[k][j].y : 0.f;
+            v[k][j].z = (uint32_t)(xs + 4 * j + 2) < (uint32_t)X ? v[k][j].z : 0.f;
+            v[k][j].w = (uint32_t)(xs + 4 * j + 3) < (uint32_t)X ? v[k][j].w : 0.f;
+          }
+        }
+      }
+#pragma unroll
+      for (int k = 0; k < 2; ++k) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+          mx = max3_abs(max3_abs(mx, v[k][j].x, v[k][j].y), v[k][j].z, v[k][j].w);
+      }
+      mx = fmaxf(mx, __shfl_xor(mx, 16));
+      mx = fmaxf(mx, __shfl_xor(mx, 32));
+      // (the next float up: a mantissa of ones would round to 2^23; the smallest
+      // terms' scale stays finite)
+      const uint32_t mb = __float_as_uint(mx);
+      const int ex = max(float_exp(mb + 1u), -100);
+      const float up = mb ? ldexpf(1.f, 23 - ex) : 0.f;
+      if (lane < kTrD) s_dn[wave][lane] = mb ? ldexpf(1.f, ex - 23) : 0.f;
+      // the terms' bytes, the lower two less 128
+      uint32_t dig[3][2][4];
+#pragma unroll
+      for (int k = 0; k < 2; ++k)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          const float f[4] = {v[k][j].x, v[k][j].y, v[k][j].z, v[k][j].w};
+          uint32_t q[4];
+#pragma unroll
+          for (int i = 0; i < 4; ++i) q[i] = (uint32_t)(int)rintf(f[i] * up);
+          const uint32_t l01 = perm8(q[1], q[0], 0x05010400u), l23 = perm8(q[3], q[2], 0x05010400u);
+          const uint32_t h01 = perm8(q[1], q[0], 0x0c0c0602u), h23 = perm8(q[3], q[2], 0x06020c0cu);
+          dig[0][k][j] = perm8(l23, l01, 0x05040100u) ^ 0x80808080u;
+          dig[1][k][j] = perm8(l23, l01, 0x07060302u) ^ 0x80808080u;
+          dig[2][k][j] = h01 | h23;
+        }
+      i32x4 acc[4] = {};
+      auto frag = [](const uint32_t (&u)[4]) {
+        return i32x4{(int)u[0], (int)u[1], (int)u[2], (int)u[3]};
+      };
+#pragma unroll
+      for (int g = 2; g >= 0; --g) {
+        if (g < 2) {
+#pragma unroll
+          for (int n = 0; n < 4; ++n)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) acc[n][i] = (acc[n][i] << 8) + k128[n];
+        }
+#pragma unroll
+        for (int k = 0; k < 2; ++k)
+#pragma unroll
+          for (int n = 0; n < 4; ++n)
+            acc[n] = __builtin_amdgcn_mfma_i32_16x16x64_i8(frag(dig[g][k]), frag(bm[n][k]), acc[n], 0, 0, 0);
+      }
+      if (dt + kTrD < a.dhi) load_tile(dt + kTrD);  // in flight through the derivatives
+      WAVE_LDS_ORDER();
+      const float4 dn4 = *reinterpret_cast<const float4*>(&s_dn[wave][4 * quarter]);
+      const float dn[4] = {dn4.x, dn4.y, dn4.z, dn4.w};
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+#pragma unroll
+        for (int n = 0; n < 4; ++n)
+          s_g[wave][4 * quarter + r][16 * n + l16] = (float)acc[n][r] * dn[r];
+      WAVE_LDS_ORDER();
+      // columns without a match and columns past X add nothing: only in the
+      // strips left of the disparity and in the last strip
+      const bool edge = x0 < dt + kTrD - 1 || x0 + 64 > X;
+      const int ib = lane + (a.dhi - 1 - dt);  // LDS entry of column x - dt
+      const int nr = min(kTrD, a.dhi - dt);
+      static_while<kTrD>([&](auto R) {
+        constexpr int r = decltype(R)::value;
+        if (r >= nr) return false;
+        float gc = s_g[wave][r][lane];
+        if (edge) {
+          int xx = x;
+          __asm__ volatile("" : "+v"(xx));  // keeps this a branch
+          gc = xx >= dt + r && xx < X ? gc : 0.f;
+        }
+        const uint2 rp = s_r[wave][ib - r];
+        const float di = __uint_as_float(lp.x) - __uint_as_float(rp.x), ad = fabsf(di);
         const float E = fast_exp2(-ad * k2);
-        const float sg = di > 0.f ? 1.f : (di < 0.f ? -1.f : 0.f);
-        const float tv = gc * kt * E * sg;
-        gl[i] += tv;
-        s_gr[r][gcol] -= tv;
-        pa += gc * (-E * 255.f * ad * ka);
-        const int hh = __builtin_popcount(pl_[i].y ^ in.pr[i].y);
-        pcs += gc * s_hc[wave][hh];
-      }
+        const float tv = (float)sign_int(__float_as_uint(di)) * (gc * E);
+        gl += tv;
+        gr = tv + __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(gr), 0x138, 0xf, 0xf, true));
+        s_gr[wave][ib - r] = gr;
+        pa = fmaf(gc, __fmul_rn(__fmul_rn(__fmul_rn(E, -255.f), ad), ka), pa);
+        pcs = fmaf(gc, __uint_as_float(lds_read(__builtin_popcount(lp.y ^ rp.y) + hc0)), pcs);
+        return true;
+      });
+      WAVE_LDS_ORDER();
     }
-    WAVE_LDS_ORDER();
-  };
-  DIn in0, in1;
-  load_d(a.dlo, in0);
-  for (int d = a.dlo; d < a.dhi; d += 2) {
-    load_d(min(d + 1, a.dhi - 1), in1);
-    process_d(d, in0);
-    if (d + 1 >= a.dhi) break;
-    load_d(min(d + 2, a.dhi - 1), in0);
-    process_d(d + 1, in1);
-  }
-  WAVE_LDS_ORDER();
-  // left gradients: each pixel has one owner (so the first slab writes every
-  // one); slabs run one after another
-  float* glp = a.g_half + (size_t)(2 * pair) * plane;
-  // right partials of this strip: columns x0 - dhi + 1 .. x0 + 63 - dlo
-  const int wd = 64 + (a.dhi - a.dlo) - 1;
-  float* gp = a.gr_part + ((size_t)pair * a.nstrips + strip) * Y * a.WP;
-#pragma unroll
-  for (int i = 0; i < RPW; ++i) {
-    if (!yv[i]) continue;
-    const int y = ys[i], r = wave + 4 * i;
-    if (xin) {
-      float* g = glp + (size_t)y * X + x;
-      *g = a.first ? gl[i] : *g + gl[i];
+    // left gradients: each pixel has one owner (so the first slab writes every
+    // one); slabs run one after another
+    if (x < X) {
+      float* g = a.g_half + ((size_t)(2 * pair) * Y + y) * X + x;
+      *g = a.first ? kt * gl : *g + kt * gl;
     }
-    for (int c = lane; c < wd; c += 64) gp[(size_t)y * a.WP + c] = s_gr[r][c];
+    // right partials of this strip: columns x0 - dhi + 1 .. x0 + 63 - dlo
+    float* gp = a.gr_part + (((size_t)pair * a.nstrips + strip) * Y + y) * a.WP;
+    for (int c = lane; c < wd; c += 64) gp[c] = -kt * s_gr[wave][c];
   }
   // fixed-order reduction of the lambda partials over the workgroup
 #pragma unroll
@@ -981,7 +1010,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) k
   if (t == 0) {
     float2 s = s_red[0];
     for (int w = 1; w < 4; ++w) { s.x += s_red[w].x; s.y += s_red[w].y; }
-    a.lam_part[(size_t)pair * gridDim.x + blockIdx.x] = s;
+    a.lam_part[item] = s;
   }
 }
 

@@ -434,3 +434,25 @@ def test_scratch_cap_shrinks_the_planes(ctx):
         assert_grad_close(got[2], ref[2], f"g_right, cap {cap} kB", rel=1e-5, rel_elem=1e-4)
         assert np.all(np.abs(got[3] - ref[3]) <= 1e-4 * np.abs(ref[3])), (cap, got[3], ref[3])
     assert ran >= 3 and refused >= 1, (ran, refused)
+
+
+@pytest.mark.parametrize("case", [
+    dict(W=128, H=10, dmax=32, seed=620),              # one full strip, one tile of 16
+    dict(W=130, H=10, dmax=34, seed=621, arm_x=31),    # one column more, one disparity more
+    dict(W=190, H=10, dmax=66, seed=622, arm_x=31),    # sources of both tiles past the image
+    dict(W=194, H=10, dmax=34, seed=623, arm_x=16),
+    dict(W=256, H=8, dmax=30, seed=624, arm_x=0),      # two full strips, no remainder row
+])
+def test_horizontal_adjoint_edges_match_oracle(ctx, case):
+    """k_soft_tr at the edges of its strips (64 columns, sources 32 further on
+    either side), tiles (16 disparities) and blocks (4 rows)."""
+    W, H, dmax, seed = case["W"], case["H"], case["dmax"], case["seed"]
+    p = osoft.SoftParams(**({"arm_x": case["arm_x"]} if "arm_x" in case else {}))
+    L, R, G, M = float_pairs(1, W, H, dmax, seed, noise=0.002)
+    print(f"[soft] horizontal adjoint {W}x{H} Dmax={dmax}", flush=True)
+    rloss, rgl, rgr, rglam = osoft.loss_and_grads(list(L), list(R), list(G), list(M), dmax, p)
+    d_hat, loss, gl, gr, glam = run_gpu(ctx, L, R, G, M, dmax, p)
+    assert_grad_close(gl, rgl, "g_left")
+    assert_grad_close(gr, rgr, "g_right")
+    for k in range(2):
+        assert abs(glam[k] - rglam[k]) <= 1e-3 * abs(rglam[k]) + 1e-9, (k, glam, rglam)
