@@ -441,7 +441,10 @@ def test_scratch_cap_shrinks_the_planes(ctx):
     dict(W=130, H=10, dmax=34, seed=621, arm_x=31),    # one column more, one disparity more
     dict(W=190, H=10, dmax=66, seed=622, arm_x=31),    # sources of both tiles past the image
     dict(W=194, H=10, dmax=34, seed=623, arm_x=16),
-    dict(W=256, H=8, dmax=30, seed=624, arm_x=0),      # two full strips, no remainder row
+    # two full strips, no remainder row; an input whose half-image differences
+    # stay away from 0 (at seed 624 one is 2.5e-8, below float rounding, and its
+    # sign is not the oracle's)
+    dict(W=256, H=8, dmax=30, seed=625, arm_x=0),
 ])
 def test_horizontal_adjoint_edges_match_oracle(ctx, case):
     """k_soft_tr at the edges of its strips (64 columns, sources 32 further on
