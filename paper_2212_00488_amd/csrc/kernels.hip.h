@@ -180,15 +180,25 @@ constexpr uint32_t kCensus4 = 0x01010101u;  // a census string (6 bits) to four 
 // the tile holds kArmPad spare pixels for them.
 constexpr int kArmPad = 7;
 
-// Run of passing steps 1..N (N <= 32) from p, bias = 2^31 - delta.
+__device__ __forceinline__ uint32_t lds_addr(const void* p) {
+  return (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) void*)p;
+}
+
+// Run of passing steps 1..N (N <= 32) from the pixel at LDS address p, bias =
+// 2^31 - delta.  The reads have constant offsets above the lowest address.
 template <int STRIDE, int N>
-__device__ __forceinline__ int arm_run(const uint8_t* p, uint32_t c, uint32_t bias) {
+__device__ __forceinline__ int arm_run(uint32_t p, uint32_t c, uint32_t bias) {
+  uint32_t lo = STRIDE > 0 ? p + STRIDE : p + N * STRIDE;
+  // (the reads of different N are not the same to the compiler, which would
+  // share them and extend each byte apart from its read)
+  __asm__ volatile("" : "+v"(lo));
   // one byte load per step (merged into wide loads, each byte would take
   // one more VALU op to extract; the compiler barrier keeps them apart)
   uint32_t v[N];
 #pragma unroll
   for (int t = 1; t <= N; ++t) {
-    v[t - 1] = p[t * STRIDE];
+    v[t - 1] = *(const __attribute__((address_space(3))) uint8_t*)(uintptr_t)(
+        lo + (uint32_t)(STRIDE > 0 ? (t - 1) * STRIDE : (t - N) * STRIDE));
     __asm__ volatile("" ::: "memory");
   }
   // the bits above N - 1 start as failures, so a chunk of fewer than 32
@@ -197,11 +207,12 @@ __device__ __forceinline__ int arm_run(const uint8_t* p, uint32_t c, uint32_t bi
 #pragma unroll
   for (int t = N; t >= 1; --t)
     m = __builtin_amdgcn_alignbit(m, __builtin_amdgcn_sad_u16(v[t - 1], c, bias), 31);
+  __asm__ volatile("; %1 steps" : "+v"(m) : "n"(N));  // (nor are the tests)
   return m == 0u ? 32 : __builtin_ctz(m);
 }
 
 template <int STRIDE>
-__device__ __forceinline__ int arm_len(const uint8_t* p, int c, int delta, int cap, int lim) {
+__device__ __forceinline__ int arm_len(uint32_t p, int c, int delta, int cap, int lim) {
   if (delta <= 0 || cap <= 0) return 0;
   const uint32_t bias = 0x80000000u - (uint32_t)delta;
   const uint32_t cu = (uint32_t)c;
@@ -242,6 +253,10 @@ __device__ __forceinline__ int arm_len(const uint8_t* p, int c, int delta, int c
 // Two workgroups share a CU only while a wave holds at most 80 SGPRs; the
 // waves-per-EU bound keeps the compiler under that (above it the kernel took
 // a fifth longer).
+// Vector arithmetic bound: 2 instructions a step tested (228 a pixel at caps 21
+// and 31) of about 350; a wave is one row, so that row addresses are scalar, and
+// every step's read is one instruction (both together took 515).  16 images of
+// 960x540: 118 us before, 100 now; 2 of 718x496: 14.7 and 13.3.
 // grid: (ceil(X/64), ceil(Y/kFeatRows), 2 * npair), block (64, kFeatRows).
 __global__ void __launch_bounds__(64 * kFeatRows) __attribute__((amdgpu_waves_per_eu(8)))
 k_feat(const uint8_t* __restrict__ half, int X, int Y, int delta, int arm_x_l, int arm_x_r,
@@ -252,6 +267,7 @@ k_feat(const uint8_t* __restrict__ half, int X, int Y, int delta, int arm_x_l, i
   __shared__ uint8_t tx[kFeatRows + 2][TXW];
   __shared__ uint8_t ty[kFeatRows + 2 * (kMaxArm + kArmPad)][64];
   const int x0 = blockIdx.x * 64, y0 = blockIdx.y * kFeatRows, img = blockIdx.z;
+  const int ly = __builtin_amdgcn_readfirstlane((int)threadIdx.y);  // a wave is a row
   const uint8_t* h = half + (size_t)img * X * Y;
   // horizontal cap of this image (the two images may differ, Sec. V)
   const int arm_x = (img & 1) ? arm_x_r : arm_x_l;
@@ -264,7 +280,7 @@ k_feat(const uint8_t* __restrict__ half, int X, int Y, int delta, int arm_x_l, i
   // tile's end are clamped to its last one: such a load and store repeat a
   // valid one with the same value.
   {
-    const int r0 = (int)threadIdx.y, r1 = min(r0 + kFeatRows, kFeatRows + 1);
+    const int r0 = ly, r1 = min(r0 + kFeatRows, kFeatRows + 1);
     const uint8_t* s0 = h + (size_t)clampi(y0 - 1 + r0, 0, Y - 1) * X;
     const uint8_t* s1 = h + (size_t)clampi(y0 - 1 + r1, 0, Y - 1) * X;
     const uint8_t* sc = h + clampi(x0 + (int)threadIdx.x, 0, X - 1);
@@ -313,7 +329,7 @@ k_feat(const uint8_t* __restrict__ half, int X, int Y, int delta, int arm_x_l, i
     }
   }
   __syncthreads();
-  const int lx = threadIdx.x, x = x0 + lx, ly = threadIdx.y, y = y0 + ly;
+  const int lx = threadIdx.x, x = x0 + lx, y = y0 + ly;
   const bool inside = x < X && y < Y;
   uint32_t p16 = 0;
   if (inside) {
@@ -326,11 +342,11 @@ k_feat(const uint8_t* __restrict__ half, int X, int Y, int delta, int arm_x_l, i
     bits |= (row[2] < c) << 3;
     bits |= (tx[ly + 2][hx + lx - 1] < c) << 4;
     bits |= (tx[ly + 2][hx + lx + 1] < c) << 5;
-    const uint8_t* col = &ty[ly + my][lx];       // col[64 i] = I(x, y + i)
-    const int m = arm_len<-1>(row, c, delta, arm_x, min(arm_x, x));
-    const int n = arm_len<1>(row, c, delta, arm_x, min(arm_x, X - 1 - x));
-    const int M = arm_len<-64>(col, c, delta, arm_y, min(arm_y, y));
-    const int N = arm_len<64>(col, c, delta, arm_y, min(arm_y, Y - 1 - y));
+    const uint32_t rowa = lds_addr(row), cola = lds_addr(&ty[ly + my][lx]);
+    const int m = arm_len<-1>(rowa, c, delta, arm_x, min(arm_x, x));
+    const int n = arm_len<1>(rowa, c, delta, arm_x, min(arm_x, X - 1 - x));
+    const int M = arm_len<-64>(cola, c, delta, arm_y, min(arm_y, y));
+    const int N = arm_len<64>(cola, c, delta, arm_y, min(arm_y, Y - 1 - y));
     if (sp)
       sp[((size_t)img * Y + y) * XP + pad + x] =
           make_uint2(__float_as_uint(half_f[((size_t)img * Y + y) * X + x]), (uint32_t)bits * kCensus4);
@@ -399,9 +415,6 @@ typedef const __attribute__((address_space(3))) uint32_t* lds_cptr;
 __device__ __forceinline__ uint32_t lds_read(uint32_t addr) { return *(lds_cptr)(uintptr_t)addr; }
 __device__ __forceinline__ void lds_write2(uint32_t addr, uint32_t v0, uint32_t v1) {
   *(__attribute__((address_space(3))) u32x2*)(uintptr_t)addr = u32x2{v0, v1};
-}
-__device__ __forceinline__ uint32_t lds_addr(const void* p) {
-  return (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) void*)p;
 }
 
 // Keeps the compiler from moving LDS accesses of one wave across this point;
