@@ -64,6 +64,9 @@ inline int fail(stereo_ctx* c, int code, const char* fmt, ...) {
   return code;
 }
 
+// The pending launch error of this thread, if any.
+int launch_status(stereo_ctx* c);
+
 #define HIP_TRY(ctx, call)                                                              \
   do {                                                                                  \
     hipError_t e_ = (call);                                                             \

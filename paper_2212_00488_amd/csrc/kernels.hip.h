@@ -8,7 +8,8 @@
 //   k_wta      combine the d-chunk minima                       (Eq. 9)
 //   k_refine   cross-check, 3x3 median and bilateral filling    (Eq. 10, Sec. III-E, Eq. 11)
 //   k_upscale  bilateral x / linear y upscale to full res      (Step8)
-//   k_gray_full, k_copy_out: the full-resolution mode's ends   (Sec. V)
+//   k_post     the last three in one, for small frames
+//   k_gray_full  the full-resolution mode's first step          (Sec. V)
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -1003,6 +1004,31 @@ __global__ void __launch_bounds__(kThreads) k_match(MatchArgs a) {
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef int16_t i16x4 __attribute__((ext_vector_type(4)));
 
+// Minimum keys of four pixels over the chunks; kp the first chunk's, planes
+// stride words apart.  Loads in groups of kWtaGroup chunks (of NB bases, stride / 2
+// apart) in flight together; a group running past the last chunk reloads the
+// last one, which leaves the minimum unchanged.
+constexpr int kWtaGroup = 8;
+template <int NB>
+__device__ __forceinline__ void min_keys(const uint32_t* kp, int nchunk, size_t stride, u32x4 (&mb)[NB]) {
+#pragma unroll
+  for (int b = 0; b < NB; ++b) mb[b] = u32x4{0xffffffffu, 0xffffffffu, 0xffffffffu, 0xffffffffu};
+  for (int c0 = 0; c0 < nchunk; c0 += kWtaGroup) {
+    u32x4 v[kWtaGroup][NB];
+#pragma unroll
+    for (int g = 0; g < kWtaGroup; ++g) {
+      const int c = min(c0 + g, nchunk - 1);
+#pragma unroll
+      for (int b = 0; b < NB; ++b)
+        __builtin_memcpy(&v[g][b], kp + (size_t)c * stride + (size_t)b * (stride / 2), 16);
+    }
+#pragma unroll
+    for (int g = 0; g < kWtaGroup; ++g)
+#pragma unroll
+      for (int b = 0; b < NB; ++b) mb[b] = __builtin_elementwise_min(mb[b], v[g][b]);
+  }
+}
+
 __global__ void __launch_bounds__(256) k_wta(const uint32_t* __restrict__ keys, int nchunk,
                                              int nk, int dbits, int16_t* __restrict__ disp,
                                              uint32_t* __restrict__ mincost) {
@@ -1010,29 +1036,8 @@ __global__ void __launch_bounds__(256) k_wta(const uint32_t* __restrict__ keys, 
   const int pair = blockIdx.y;
   if (i >= nk) return;
   const uint32_t* kp = keys + (size_t)pair * nchunk * 2 * nk + i;
-  // chunks in groups of kWtaGroup, all loads of a group (both bases) in
-  // flight together; a group running past the last chunk reloads the last
-  // one, which leaves the minimum unchanged
-  constexpr int kWtaGroup = 8;
   u32x4 mb[2];
-  mb[0] = mb[1] = u32x4{0xffffffffu, 0xffffffffu, 0xffffffffu, 0xffffffffu};
-  for (int c0 = 0; c0 < nchunk; c0 += kWtaGroup) {
-    u32x4 v[kWtaGroup][2];
-#pragma unroll
-    for (int g = 0; g < kWtaGroup; ++g) {
-      const int c = min(c0 + g, nchunk - 1);
-#pragma unroll
-      for (int b = 0; b < 2; ++b)
-        v[g][b] = *reinterpret_cast<const u32x4*>(kp + ((size_t)c * 2 + b) * nk);
-    }
-#pragma unroll
-    for (int g = 0; g < kWtaGroup; ++g)
-#pragma unroll
-      for (int b = 0; b < 2; ++b) {
-        mb[b].x = min(mb[b].x, v[g][b].x); mb[b].y = min(mb[b].y, v[g][b].y);
-        mb[b].z = min(mb[b].z, v[g][b].z); mb[b].w = min(mb[b].w, v[g][b].w);
-      }
-  }
+  min_keys<2>(kp, nchunk, 2 * (size_t)nk, mb);
 #pragma unroll
   for (int b = 0; b < 2; ++b) {
     const u32x4 m = mb[b];
@@ -1057,7 +1062,9 @@ __global__ void __launch_bounds__(256) k_wta(const uint32_t* __restrict__ keys, 
 // distance (the right one at equal distance), or the smaller disparity.
 // The rows are staged in LDS, the GCP flags of the row become a bit array
 // (one wave ballot per 64 columns), and each non-GCP finds its nearest GCPs
-// by bit search in that array.
+// by bit search in that array.  The values go to filled (may be NULL) and, in
+// full-resolution mode, where they are the map, to the output (as a kernel of
+// its own that copy took 5 us at 1436x992).
 // grid: (Y, npair), block 256.
 __device__ __forceinline__ int floor_div_pos(int n, int d) {  // d > 0
   return n >= 0 ? n / d : -((-n + d - 1) / d);
@@ -1074,6 +1081,30 @@ __device__ __forceinline__ int median9(int* v) {
   return v[4];
 }
 
+// Value of column x of a row of X (bit x of gm set: a GCP), its medians med and
+// grays h.
+__device__ __forceinline__ int fill_value(const uint64_t* gm, const int16_t* med, const uint8_t* h,
+                                          int x, int X, int T, int fill_mode) {
+  const int wx = x >> 6, bx = x & 63, nw = (X + 63) >> 6;
+  if ((gm[wx] >> bx) & 1ull) return med[x];
+  int w = wx, xl = -1, xr = X;
+  uint64_t mk = gm[w] & ((1ull << bx) - 1ull);            // columns < x
+  while (mk == 0ull && w > 0) mk = gm[--w];
+  if (mk) xl = w * 64 + 63 - __builtin_clzll(mk);
+  w = wx;
+  mk = bx == 63 ? 0ull : gm[w] & (~0ull << (bx + 1));     // columns > x
+  while (mk == 0ull && w + 1 < nw) mk = gm[++w];
+  if (mk) xr = w * 64 + __builtin_ctzll(mk);
+  if (xl >= 0 && xr < X) {
+    const int i = x - xl, j = xr - x, dla = med[xl], drb = med[xr];
+    if (fill_mode == 1) return i < j ? dla : drb;
+    if (fill_mode == 2) return min(dla, drb);
+    if (iabs(dla - drb) <= T) return dla + floor_div_pos(2 * i * (drb - dla) + (i + j), 2 * (i + j));
+    return iabs(h[xl] - h[x]) < iabs(h[xr] - h[x]) ? dla : drb;
+  }
+  return xl >= 0 ? med[xl] : xr < X ? med[xr] : 0;
+}
+
 constexpr int kRefMaxX = 4096;  // widest half-res (or full-res mode) row
 
 __global__ void __launch_bounds__(256) k_refine(const int16_t* __restrict__ disp, int nk,
@@ -1081,7 +1112,8 @@ __global__ void __launch_bounds__(256) k_refine(const int16_t* __restrict__ disp
                                                 int X, int Y, int T, int fill_mode,
                                                 uint8_t* __restrict__ gcp_out,
                                                 int16_t* __restrict__ med_out,
-                                                int16_t* __restrict__ filled) {
+                                                int16_t* __restrict__ filled, PairPtrs pp,
+                                                int full) {
   __shared__ int16_t s_d[4][kRefMaxX];          // D^L rows y-1, y, y+1 (clamped), D^R row y
   __shared__ int16_t s_med[kRefMaxX];
   __shared__ uint8_t s_h[kRefMaxX];             // left gray of row y
@@ -1138,43 +1170,10 @@ __global__ void __launch_bounds__(256) k_refine(const int16_t* __restrict__ disp
   }
   __syncthreads();
   // fill: the nearest GCPs left and right from the bit array
-  const int nw = (X + 63) >> 6;
-  int16_t* fo = filled + (size_t)pair * plane + r0;
   for (int x = t; x < X; x += 256) {
-    const int wx = x >> 6, bx = x & 63;
-    int v;
-    if ((s_gm[wx] >> bx) & 1ull) {
-      v = s_med[x];
-    } else {
-      int w = wx, xl = -1, xr = X;
-      uint64_t mk = s_gm[w] & ((1ull << bx) - 1ull);            // columns < x
-      while (mk == 0ull && w > 0) mk = s_gm[--w];
-      if (mk) xl = w * 64 + 63 - __builtin_clzll(mk);
-      w = wx;
-      mk = bx == 63 ? 0ull : s_gm[w] & (~0ull << (bx + 1));     // columns > x
-      while (mk == 0ull && w + 1 < nw) mk = s_gm[++w];
-      if (mk) xr = w * 64 + __builtin_ctzll(mk);
-      if (xl >= 0 && xr < X) {
-        const int i = x - xl, j = xr - x, dla = s_med[xl], drb = s_med[xr];
-        if (fill_mode == 1) {
-          v = i < j ? dla : drb;
-        } else if (fill_mode == 2) {
-          v = min(dla, drb);
-        } else if (iabs(dla - drb) <= T) {
-          v = dla + floor_div_pos(2 * i * (drb - dla) + (i + j), 2 * (i + j));
-        } else {
-          const int ch = s_h[x];
-          v = iabs(s_h[xl] - ch) < iabs(s_h[xr] - ch) ? dla : drb;
-        }
-      } else if (xl >= 0) {
-        v = s_med[xl];
-      } else if (xr < X) {
-        v = s_med[xr];
-      } else {
-        v = 0;
-      }
-    }
-    fo[x] = (int16_t)v;
+    const int16_t v = (int16_t)fill_value(s_gm, s_med, s_h, x, X, T, fill_mode);
+    if (filled) filled[(size_t)pair * plane + r0 + x] = v;
+    if (full) pp.out[pair][r0 + x] = v;
   }
 }
 
@@ -1188,15 +1187,6 @@ __global__ void __launch_bounds__(256) k_gray_full(PairPtrs pp, int W, int H,
   if (x >= W) return;
   const uint8_t* rgb = (img & 1) ? pp.right[img >> 1] : pp.left[img >> 1];
   half[(size_t)img * W * H + (size_t)y * W + x] = (uint8_t)gray_of(rgb + ((size_t)y * W + x) * 3);
-}
-
-// Full-resolution mode: the filled map is the output (no upscale).
-// grid: (ceil(W*H/256), npair), block 256.
-__global__ void __launch_bounds__(256) k_copy_out(PairPtrs pp, const int16_t* __restrict__ filled,
-                                                  int n) {
-  const int i = blockIdx.x * 256 + threadIdx.x, pair = blockIdx.y;
-  if (i >= n) return;
-  pp.out[pair][i] = filled[(size_t)pair * n + i];
 }
 
 // ------------------------------------------------------------- k_upscale
@@ -1216,18 +1206,13 @@ __device__ __forceinline__ int up_odd(int dlv, int drv, const uint8_t* rgb_row, 
   return iabs(g0 - g1) < iabs(g2 - g1) ? 2 * dlv : 2 * drv;
 }
 
-__global__ void __launch_bounds__(256) k_upscale(PairPtrs pp, const int16_t* __restrict__ filled,
-                                                 int W, int H, int X, int Y, int T) {
-  const int x = blockIdx.x * 64 + threadIdx.x;
-  const int y = blockIdx.y * 4 + threadIdx.y;
-  const int pair = blockIdx.z;
-  if (x >= X || y >= Y) return;
-  const int16_t* f = filled + (size_t)pair * X * Y;
-  const uint8_t* rgb = pp.left[pair];
-  int16_t* out = pp.out[pair];
+// Output pixels of half-res pixel (x, y); f0 and f1 are the filled rows y and
+// y + 1.
+__device__ __forceinline__ void up_block(const int16_t* f0, const int16_t* f1, const uint8_t* rgb,
+                                         int16_t* out, int x, int y, int W, int H, int X, int Y, int T) {
   const int xo = 2 * x, yo = 2 * y;
   const bool hasr = x + 1 < X, hasd = y + 1 < Y;
-  const int a = f[(size_t)y * X + x], b = hasr ? f[(size_t)y * X + x + 1] : a;
+  const int a = f0[x], b = hasr ? f0[x + 1] : a;
   // upscaled row y at columns 2x and 2x+1
   const int u0 = 2 * a;
   const int u1 = hasr ? up_odd(a, b, rgb + (size_t)yo * W * 3, xo + 1, T) : 2 * a;
@@ -1237,7 +1222,7 @@ __global__ void __launch_bounds__(256) k_upscale(PairPtrs pp, const int16_t* __r
   if (yo + 1 < H) {
     int v0 = u0, v1 = u1;
     if (hasd) {
-      const int c = f[(size_t)(y + 1) * X + x], e = hasr ? f[(size_t)(y + 1) * X + x + 1] : c;
+      const int c = f1[x], e = hasr ? f1[x + 1] : c;
       const int w0 = 2 * c;
       const int w1 = hasr ? up_odd(c, e, rgb + (size_t)(yo + 2) * W * 3, xo + 1, T) : 2 * c;
       v0 = (u0 + w0 + 1) >> 1;
@@ -1245,6 +1230,89 @@ __global__ void __launch_bounds__(256) k_upscale(PairPtrs pp, const int16_t* __r
     }
     out[(size_t)(yo + 1) * W + xo] = (int16_t)v0;
     if (odd_col) out[(size_t)(yo + 1) * W + xo + 1] = (int16_t)v1;
+  }
+}
+
+__global__ void __launch_bounds__(256) k_upscale(PairPtrs pp, const int16_t* __restrict__ filled,
+                                                 int W, int H, int X, int Y, int T) {
+  const int x = blockIdx.x * 64 + threadIdx.x;
+  const int y = blockIdx.y * 4 + threadIdx.y;
+  const int pair = blockIdx.z;
+  if (x >= X || y >= Y) return;
+  const int16_t* f = filled + ((size_t)pair * Y + y) * X;
+  up_block(f, f + X, pp.left[pair], pp.out[pair], x, y, W, H, X, Y, T);
+}
+
+// ---------------------------------------------------------------- k_post
+// k_wta, k_refine and k_upscale in one: a workgroup takes kPostRows half-res rows
+// y0 .. of a pair, which need the filled rows y0 .. y0 + kPostRows, their medians
+// D^L one row further on either side and their cross-check D^R, all in LDS.
+// The rows that two workgroups need are reduced by both (8 rows of keys for
+// every 2, where k_wta reads 4), so this pays while launches and latency count
+// (kPostMaxPixels): 320x240 28.8 us a frame with three kernels, 23.7 with one;
+// 640x480 45.2 and 41.8; 1237x823 84.1 and 83.5; 1436x992 105.4 and 105.2;
+// 2872x1984 597 and 605; 8 pairs of 1920x1080 1466 and 1501.  1 or 4 rows, or 512
+// threads, took 0.2 to 5 us more at all of the first four.
+// grid: (ceil(Y / kPostRows), npair), block kPostThreads.
+constexpr int kPostRows = 2, kPostThreads = 1024, kPostMaxX = 2048, kPostMaxPixels = 1 << 18;
+
+__global__ void __launch_bounds__(kPostThreads) k_post(PairPtrs pp, const uint32_t* __restrict__ keys,
+                                                       int nchunk, int nk, int dbits,
+                                                       const uint16_t* __restrict__ pk, int XP, int pad,
+                                                       int W, int H, int X, int Y, int T, int fill_mode) {
+  constexpr int NF = kPostRows + 1, NL = NF + 2;  // filled rows, rows of D^L
+  __shared__ int16_t s_d[NL + NF][kPostMaxX];     // D^L rows y0 - 1 .. (clamped), D^R rows y0 ..
+  __shared__ int16_t s_med[NF][kPostMaxX];
+  __shared__ uint8_t s_h[NF][kPostMaxX];
+  __shared__ uint64_t s_gm[NF][kPostMaxX / 64];
+  const int t = threadIdx.x, lane = t & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
+  const int y0 = blockIdx.x * kPostRows, pair = blockIdx.y;
+  const uint32_t dm = (1u << dbits) - 1u;
+  // minima of four columns a thread (the last four again where X is no multiple)
+  const int nq = (X + 3) / 4;
+  const uint32_t* kp = keys + (size_t)pair * nchunk * 2 * nk;
+  for (int i = t; i < (NL + NF) * nq; i += kPostThreads) {
+    const int j = i / nq, x = min(4 * (i - j * nq), X - 4);
+    const int y = j < NL ? clampi(y0 - 1 + j, 0, Y - 1) : min(y0 + j - NL, Y - 1);
+    u32x4 m[1];
+    min_keys<1>(kp + (j < NL ? 0 : nk) + (size_t)y * X + x, nchunk, 2 * (size_t)nk, m);
+    s_d[j][x] = (int16_t)(m[0].x & dm);
+    s_d[j][x + 1] = (int16_t)(m[0].y & dm);
+    s_d[j][x + 2] = (int16_t)(m[0].z & dm);
+    s_d[j][x + 3] = (int16_t)(m[0].w & dm);
+  }
+  const int nw = (X + 63) >> 6;
+  for (int i = wave; i < NF * nw; i += kPostThreads / 64) {
+    const int j = i / nw, x = (i - j * nw) * 64 + lane;
+    if (x < X)
+      s_h[j][x] = (uint8_t)pk[((size_t)(2 * pair) * Y + min(y0 + j, Y - 1)) * XP + pad + x];
+  }
+  __syncthreads();
+  for (int i = wave; i < NF * nw; i += kPostThreads / 64) {
+    const int j = i / nw, w = i - j * nw, x = w * 64 + lane;
+    bool g = false;
+    if (x < X) {
+      const int xm = max(x - 1, 0), xp = min(x + 1, X - 1);
+      int v[9] = {s_d[j][xm],     s_d[j][x],     s_d[j][xp],     s_d[j + 1][xm], s_d[j + 1][x],
+                  s_d[j + 1][xp], s_d[j + 2][xm], s_d[j + 2][x], s_d[j + 2][xp]};
+      const int k = v[4];
+      g = x - k >= 0 && s_d[NL + j][x - k] == k;
+      s_med[j][x] = (int16_t)median9(v);
+    }
+    const uint64_t bal = __ballot(g);
+    if (lane == 0) s_gm[j][w] = bal;
+  }
+  __syncthreads();
+  // the filled rows take the place of D^L's first ones
+  for (int i = wave; i < NF * nw; i += kPostThreads / 64) {
+    const int j = i / nw, x = (i - j * nw) * 64 + lane;
+    if (x < X) s_d[j][x] = (int16_t)fill_value(s_gm[j], s_med[j], s_h[j], x, X, T, fill_mode);
+  }
+  __syncthreads();
+  for (int i = wave; i < kPostRows * nw; i += kPostThreads / 64) {
+    const int r = i / nw, x = (i - r * nw) * 64 + lane, y = y0 + r;
+    if (x < X && y < Y) up_block(s_d[r], s_d[r + 1], pp.left[pair], pp.out[pair], x, y, W, H, X, Y, T);
   }
 }
 

@@ -332,12 +332,6 @@ int soft_prologue(stereo_ctx* c, int n, int W, int H, int Dmax, const stereo_sof
   return get_soft_plan(c, n, W, H, Dmax, p, s, pl);
 }
 
-int launch_status(stereo_ctx* c) {
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return fail(c, STEREO_EHIP, "kernel launch: %s", hipGetErrorString(e));
-  return 0;
-}
-
 constexpr int kL1Blocks = 256;  // partial-sum blocks per pair
 
 // L1 scratch of the context for the stream s: partials [kSoftMaxPairs][kL1Blocks],

@@ -633,6 +633,11 @@ int timing_events(stereo_ctx* c, hipEvent_t** ev) {
   return 0;
 }
 
+int launch_status(stereo_ctx* c) {
+  const hipError_t e = hipGetLastError();
+  return e == hipSuccess ? 0 : fail(c, STEREO_EHIP, "kernel launch: %s", hipGetErrorString(e));
+}
+
 // The whole path for npair pairs already checked against the plan.
 int run(stereo_ctx* c, Plan& pl, const PairPtrs& pp, int npair, bool keep, bool timed,
         hipStream_t s) {
@@ -661,22 +666,26 @@ int run(stereo_ctx* c, Plan& pl, const PairPtrs& pp, int npair, bool keep, bool 
   mark(2);
   launch_match(pl, match_args(pl, npair, 0, pl.D, pl.nchunk), s);
   mark(3);
+  // one kernel for the rest of small frames (stage times and kept planes need the
+  // three; rows of fewer than 4 columns do not fill its loads)
+  if (!full && !keep && !timed && X >= 4 && X <= kPostMaxX && (size_t)npair * X * Y <= kPostMaxPixels) {
+    hipLaunchKernelGGL(k_post, dim3((Y + kPostRows - 1) / kPostRows, npair), dim3(kPostThreads), 0, s, pp,
+                       pl.keys, pl.nchunk, pl.nk, pl.dbits, pl.pk, pl.XP, pl.pad, pl.W, pl.H, X, Y,
+                       pl.p.fill_T, pl.p.fill_mode);
+    return launch_status(c);
+  }
   hipLaunchKernelGGL(k_wta, dim3((pl.nk + 1023) / 1024, npair), dim3(256), 0, s, pl.keys,
                      pl.nchunk, pl.nk, pl.dbits, pl.disp, keep ? pl.mincost : nullptr);
   mark(4);
   hipLaunchKernelGGL(k_refine, dim3(Y, npair), dim3(256), 0, s, pl.disp, pl.nk, pl.pk, pl.XP,
                      pl.pad, X, Y, pl.p.fill_T, pl.p.fill_mode, keep ? pl.gcp : nullptr,
-                     keep ? pl.med : nullptr, pl.filled);
+                     keep ? pl.med : nullptr, full && !keep ? nullptr : pl.filled, pp, (int)full);
   mark(5);
-  if (full)
-    hipLaunchKernelGGL(k_copy_out, dim3((X * Y + 255) / 256, npair), dim3(256), 0, s, pp,
-                       pl.filled, X * Y);
-  else
+  if (!full)
     hipLaunchKernelGGL(k_upscale, dim3((X + 63) / 64, (Y + 3) / 4, npair), b2, 0, s, pp,
                        pl.filled, pl.W, pl.H, X, Y, pl.p.fill_T);
   mark(6);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return fail(c, STEREO_EHIP, "kernel launch: %s", hipGetErrorString(e));
+  if (int rc = launch_status(c)) return rc;
   if (timed) ++c->timed_calls;
   return 0;
 }

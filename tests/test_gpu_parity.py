@@ -548,3 +548,42 @@ def test_autotune_keeps_results(sm, ctx):
     for i in range(2):
         exp = oracle.disparity(pairs[i].left, pairs[i].right, 48)["out"]
         assert np.array_equal(outs[i].cpu().numpy(), exp)
+
+
+@pytest.mark.parametrize("W,H,dmax,n,kw", [
+    (6, 4, 4, 1, {}),                                # 3 half columns: three kernels
+    (8, 2, 6, 1, {}), (7, 3, 5, 1, {}),              # 4 columns; one row, two rows
+    (9, 6, 6, 2, dict(fill_mode=1)),                 # last columns again, odd rows
+    (126, 7, 40, 1, dict(fill_mode=2)),              # 63, 64, 65, 66 columns
+    (127, 8, 40, 1, {}), (129, 10, 40, 3, {}), (131, 9, 40, 1, dict(fill_T=0)),
+    (4096, 6, 64, 1, {}), (4097, 6, 64, 1, {}),      # 2048 columns, and one more
+    (512, 512, 16, 4, {}), (514, 512, 16, 4, {}),    # 2^18 half pixels, and more
+])
+def test_one_kernel_tail_equals_three(sm, ctx, W, H, dmax, n, kw):
+    """Calls small enough for k_post give the map of k_wta, k_refine and k_upscale
+    (which a call that keeps its intermediates takes), at the edges of its rule,
+    its four-column loads, its 64-column words and its row pairs."""
+    say(f"case: one kernel tail {n} x {W}x{H} Dmax {dmax} {kw}")
+    pairs = [make_pair(W, H, dmax, segments=4, seed=700 + W + i) for i in range(n)]
+    lefts = [torch.from_numpy(p.left).cuda() for p in pairs]
+    rights = [torch.from_numpy(p.right).cuda() for p in pairs]
+    outs = ctx.disparity_batch(lefts, rights, dmax, sm.default_params(**kw))
+    for i in range(n):
+        exp = ctx.disparity(lefts[i], rights[i], dmax, keep_params(sm, **kw))
+        torch.cuda.synchronize()
+        assert_same(f"pair {i}", outs[i].cpu().numpy(), exp.cpu().numpy())
+    if W < 200:
+        p = sm.default_params(**kw)
+        exp = oracle.disparity(pairs[0].left, pairs[0].right, dmax, oracle_params(p))
+        assert_same("oracle", outs[0].cpu().numpy(), exp["out"])
+
+
+def test_full_resolution_output_without_kept_planes(sm, ctx):
+    """k_refine writes a full-resolution map itself, with kept planes and without."""
+    pair = make_pair(131, 50, 20, segments=5, seed=720)
+    lt, rt = torch.from_numpy(pair.left).cuda(), torch.from_numpy(pair.right).cuda()
+    p = sm.default_params(flags=sm.F_FULL_RES)
+    out = ctx.disparity(lt, rt, 20, p)
+    torch.cuda.synchronize()
+    exp = oracle.disparity(pair.left, pair.right, 20, oracle_params(p))
+    assert_same("full-resolution map", out.cpu().numpy(), exp["out"])
