@@ -29,6 +29,7 @@ struct SoftPlan {
   int ns = 1, kmax = 8, nstrips = 0, nbands = 0, rows = 0;
   int csize = 1, nchunk = 0;   // k_soft_agg d-chunk size and forward chunk count
   int XS = 0, pads = 0, XA = 0;
+  int XW = 0;          // row pitch of the weight and dL/dCA_x planes: whole 128-byte lines
   int fxk = 18;        // fixed-point bits of the costs
   int nw = 1;          // disparities the weight planes hold: all D, or a slab's
   int nds = 1;         // disparities per backward slab
@@ -43,8 +44,8 @@ struct SoftPlan {
   float* inv_size = nullptr;   // [n][Y][X]
   float2* part = nullptr;      // [n][nchunk][Y][X]
   float4* pc = nullptr;        // [n][Y][X]
-  float* wts = nullptr;        // [nw][n][Y][X] e_d or CA
-  float* gcax = nullptr;       // [nds][n][Y][X] dL/dCA_x
+  float* wts = nullptr;        // [nw][n][Y][XW] e_d or CA
+  float* gcax = nullptr;       // [nds][n][Y][XW] dL/dCA_x
   float* gr_part = nullptr;    // [n][nstrips][Y][WP] right-gradient partials of a slab
   int WP = 0;                  // 64 + nds - 1 columns per partial row
   float* g_half = nullptr;     // [2n][Y][X]
@@ -132,6 +133,7 @@ void soft_geometry(SoftPlan& pl, int num_cu) {
   pl.rows = nb == 1 ? Y : std::min(Y, (Y + nb - 1) / nb + 2 * p.arm_y);
   pl.nstrips = (X + kTX - 1) / kTX;
   pl.XA = pl.nstrips * kTX;
+  pl.XW = (X + 31) & ~31;
   // row loads reach x0 - hx - d .. x0 - hx + 127 for every strip x0
   pl.pads = ((128 + D + 2) + 1) & ~1;
   pl.XS = (pl.pads + pl.XA + 128 + 2 + 1) & ~1;
@@ -143,11 +145,11 @@ void soft_geometry(SoftPlan& pl, int num_cu) {
 // Device bytes of a plan with weight planes of nw disparities and slabs of nds.
 size_t soft_bytes(const SoftPlan& pl, int nw, int nds) {
   auto al = [](size_t b) { return (b + 255) & ~size_t(255); };
-  const size_t n = pl.n, nimg = 2 * n, Y = pl.Y, npix = (size_t)pl.X * Y;
+  const size_t n = pl.n, nimg = 2 * n, Y = pl.Y, npix = (size_t)pl.X * Y, nplane = (size_t)pl.XW * Y;
   const size_t nslab = (pl.D + nds - 1) / nds;
   return al(nimg * npix * 4) + al(nimg * npix) + al(nimg * Y * pl.XA * 4) +
          al(nimg * Y * pl.XS * 8) + al(n * npix * 4) + al(n * pl.nchunk * npix * 8) +
-         al(n * npix * 16) + al(nw * n * npix * 4) + al(nds * n * npix * 4) +
+         al(n * npix * 16) + al(nw * n * nplane * 4) + al(nds * n * nplane * 4) +
          al(nimg * npix * 4) + al(nslab * n * pl.nstrips * ((Y + kTrRows - 1) / kTrRows) * 8) +
          al(n * pl.nstrips * Y * (64 + nds - 1) * 4);
 }
@@ -158,7 +160,7 @@ int make_soft_plan(stereo_ctx* c, int n, int W, int H, int Dmax, const stereo_so
   pl->n = n; pl->W = W; pl->H = H; pl->Dmax = Dmax; pl->p = p;
   soft_geometry(*pl, c->num_cu);
   const int X = pl->X, Y = pl->Y, D = pl->D;
-  const size_t npix = (size_t)X * Y, nimg = 2 * (size_t)n;
+  const size_t npix = (size_t)X * Y, nplane = (size_t)pl->XW * Y, nimg = 2 * (size_t)n;
   // k_soft_agg addresses the pixel and arm planes through 32-bit buffer
   // offsets
   if (nimg * Y * pl->XS * 8 >= (size_t(1) << 32) || nimg * Y * pl->XA * 4 >= (size_t(1) << 32)) {
@@ -175,9 +177,9 @@ int make_soft_plan(stereo_ctx* c, int n, int W, int H, int Dmax, const stereo_so
   // device does not hold the scratch.
   const size_t budget = std::max<size_t>(1, kSlabBudget / (2 * n * npix * 4));
   int nds = std::min(p.slab > 0 ? std::min(p.slab, D) : (int)std::min<size_t>(D, budget), kTrMaxWP - 63);
-  nds = (int)std::max<size_t>(1, std::min<size_t>(nds, kPlanesMost / (n * npix * 4)));
+  nds = (int)std::max<size_t>(1, std::min<size_t>(nds, kPlanesMost / (n * nplane * 4)));
   pl->ca = nds < D;
-  int nw = p.slab > 0 || (size_t)D * n * npix * 4 > kPlanesMost ? nds : D;
+  int nw = p.slab > 0 || (size_t)D * n * nplane * 4 > kPlanesMost ? nds : D;
   size_t bytes = 0;
   int rc = 0;
   for (;;) {
@@ -214,8 +216,8 @@ int make_soft_plan(stereo_ctx* c, int n, int W, int H, int Dmax, const stereo_so
   pl->inv_size = carve<float>(cur, n * npix);
   pl->part = carve<float2>(cur, (size_t)n * pl->nchunk * npix);
   pl->pc = carve<float4>(cur, n * npix);
-  pl->wts = carve<float>(cur, (size_t)nw * n * npix);
-  pl->gcax = carve<float>(cur, (size_t)nds * n * npix);
+  pl->wts = carve<float>(cur, (size_t)nw * n * nplane);
+  pl->gcax = carve<float>(cur, (size_t)nds * n * nplane);
   pl->g_half = carve<float>(cur, nimg * npix);
   pl->lam_part = carve<float2>(cur, pl->lam_count);
   pl->gr_part = carve<float>(cur, (size_t)n * pl->nstrips * Y * pl->WP);
@@ -281,7 +283,7 @@ void soft_features(SoftPlan& pl, const float* left, const float* right, hipStrea
 SoftArgs soft_args(const SoftPlan& pl, const float* lambdas, int dlo, int dhi, int csize) {
   SoftArgs a{};
   a.sp = pl.sp; a.arms = pl.arms; a.lam = lambdas; a.inv_size = pl.inv_size;
-  a.X = pl.X; a.Y = pl.Y; a.XS = pl.XS; a.pads = pl.pads; a.XA = pl.XA;
+  a.X = pl.X; a.Y = pl.Y; a.XS = pl.XS; a.pads = pl.pads; a.XA = pl.XA; a.XW = pl.XW;
   a.arm_x = pl.p.arm_x; a.arm_y = pl.p.arm_y;
   a.nbands = pl.nbands; a.dlo = dlo; a.dhi = dhi;
   a.csize = std::max(1, std::min(csize, dhi - dlo));
@@ -463,8 +465,8 @@ int stereo_soft_backward(stereo_ctx* c, const float* left, const float* right, i
     if (!saved && !whole) weights(dlo, dhi);
     TcwArgs tc{};
     tc.wts = pl->wts; tc.pc = pl->pc; tc.arms = pl->arms; tc.gcax = pl->gcax;
-    tc.wts_bytes = (uint32_t)((size_t)pl->nw * pl->n * npix * 4);
-    tc.X = X; tc.Y = Y; tc.XA = pl->XA; tc.arm_y = pl->p.arm_y; tc.npair = pl->n;
+    tc.wts_bytes = (uint32_t)((size_t)pl->nw * pl->n * pl->XW * Y * 4);
+    tc.X = X; tc.Y = Y; tc.XA = pl->XA; tc.XW = pl->XW; tc.arm_y = pl->p.arm_y; tc.npair = pl->n;
     tc.dlo = dlo; tc.dhi = dhi; tc.wlo = whole ? 0 : dlo;
     // disparity groups so that the grid fills the CUs about three blocks deep
     // (each group reloads the per-pixel constants: at 4 x 718x496, 4 groups
@@ -477,7 +479,7 @@ int stereo_soft_backward(stereo_ctx* c, const float* left, const float* right, i
     ta.gcax = pl->gcax; ta.arms = pl->arms; ta.sp = pl->sp; ta.lam = lambdas;
     ta.g_half = pl->g_half; ta.gr_part = pl->gr_part;
     ta.lam_part = pl->lam_part + (size_t)slab * lam_slab;
-    ta.X = X; ta.Y = Y; ta.XS = pl->XS; ta.pads = pl->pads; ta.XA = pl->XA;
+    ta.X = X; ta.Y = Y; ta.XS = pl->XS; ta.pads = pl->pads; ta.XA = pl->XA; ta.XW = pl->XW;
     ta.npair = pl->n; ta.dlo = dlo; ta.dhi = dhi; ta.WP = pl->WP;
     ta.nstrips = pl->nstrips;
     ta.first = dlo == 0;  // the first slab writes every half-image gradient

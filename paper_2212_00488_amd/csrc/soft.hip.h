@@ -176,7 +176,7 @@ struct SoftArgs {
   float2* part;             // [n][nchunk][Y][X] {sum e, sum d e}, or NULL
   float* wts;               // [..][n][Y][X] e_d, plane 0 = disparity wlo, or NULL
   int ca;                   // wts takes CA in place of e_d
-  int X, Y, XS, pads, XA, arm_x, arm_y;
+  int X, Y, XS, pads, XA, XW, arm_x, arm_y;
   int nbands, dlo, dhi, wlo, nstrips, ngroups, npair;
   int csize, nchunk;        // d-chunk size; chunks = ceil((dhi - dlo) / csize), the last the remainder
   float fx;                 // fixed-point scale 2^k of the costs
@@ -211,7 +211,7 @@ constexpr int kAggRows = (kLdsBytes - kAggRowBytes) / 256 - 1;
 // Vector arithmetic and LDS bound: the row sums in registers and two barriers
 // a disparity (one for the segments' totals, one for the plane) in place of
 // three and a second pass over the plane.  4 pairs of 718x496, 73 disparities:
-// 440 us before, 390 us now.
+// 440 us before, 366 us now (24 of it from weight rows of whole 128-byte lines).
 // grid: ceil(groups / 8) * 8 * nchunk workgroups (1-D), block 1024.
 template <int KMAX, int SEG>
 __global__ void __launch_bounds__(kThreads) k_soft_agg(SoftArgs a) {
@@ -395,7 +395,7 @@ __global__ void __launch_bounds__(kThreads) k_soft_agg(SoftArgs a) {
     uint32_t kpermM = 0x020c000cu;
     __asm__ volatile("" : "+v"(kpermM));
     // rows of the weight plane of d
-    float* wd = a.wts ? a.wts + ((size_t)(d - a.wlo) * a.npair + pair) * X * Y + (size_t)(ya + o0 + wave) * X + x0
+    float* wd = a.wts ? a.wts + (((size_t)(d - a.wlo) * a.npair + pair) * Y + ya + o0 + wave) * a.XW + x0
                       : nullptr;
     if (x < X) {
       uint32_t wh[2][kWinGroup][2], wl[2][kWinGroup][2];
@@ -433,7 +433,7 @@ __global__ void __launch_bounds__(kThreads) k_soft_agg(SoftArgs a) {
             se[k] += ev;
             sde[k] += fd * ev;
             if (wd && o0 + wave + k * kWaves < o1)
-              wd[(size_t)k * kWaves * X + ln] = a.ca ? (float)ca : ev;
+              wd[(size_t)k * kWaves * a.XW + ln] = a.ca ? (float)ca : ev;
           }
       });
     }
@@ -519,8 +519,9 @@ __global__ void __launch_bounds__(256) k_soft_bprep(const float* __restrict__ in
 // wave does B of one disparity, D and C of the two before it and A of the next,
 // on three difference arrays in turn: one barrier a disparity instead of three.
 // Bound by the 24 LDS atomics a thread and disparity and by the 16 waves that a
-// CU holds: 4 pairs of 718x496, 73 disparities, 264 us with three barriers and
-// 246 now.  CA = true takes saved CA: at 4 pairs of 960x540 and 128 disparities,
+// CU holds, and close to the memory rate (0.83 GB of planes, half as much again of
+// halo rows): 4 pairs of 718x496, 73 disparities, 264 us with three barriers, 246
+// with one, 217 with rows of whole 128-byte lines.  CA = true takes saved CA: at 4 pairs of 960x540 and 128 disparities,
 // where the backward computed CA again and summed its planes one by one,
 // forward and backward together took 3.61 ms and take 2.27 (this kernel 0.60).
 // grid: strips * bands * n * ndg rounded up to 8 (1-D, xcd_item), block 1024;
@@ -533,12 +534,12 @@ static_assert(tcol_band(31) + 2 * 31 <= kTcwWaves * kTcwSrc &&
                   tcol_band(63) + 2 * 63 <= kTcwWaves * kTcwSrc, "k_soft_tcolw source rows");
 
 struct TcwArgs {
-  const float* wts;         // [..][n][Y][X] e_d or CA, plane 0 = disparity wlo
+  const float* wts;         // [..][n][Y][XW] e_d or CA, plane 0 = disparity wlo
   const float4* pc;         // [n][Y][X] constants (k_soft_bprep)
   const uint32_t* arms;     // [2n][Y][XA]
-  float* gcax;              // [nds][n][Y][X] dL/dCA_x
+  float* gcax;              // [nds][n][Y][XW] dL/dCA_x
   uint32_t wts_bytes;
-  int X, Y, XA, arm_y, npair, dlo, dhi, wlo, ndg;
+  int X, Y, XA, XW, arm_y, npair, dlo, dhi, wlo, ndg;
 };
 
 // Exponent e with 2^(e-1) <= v < 2^e of the bits of a float v >= 0 (frexp's;
@@ -569,7 +570,7 @@ __global__ void __launch_bounds__(64 * kTcwWaves) k_soft_tcolw(TcwArgs a) {
   const int Y1 = min(Y, Y0 + B);
   const bool xv = x < X;
   const int xc = min(x, X - 1);
-  const size_t plane = (size_t)X * Y;
+  const size_t plane = (size_t)a.XW * Y;
   const int ys = max(0, Y0 - a.arm_y), ye = min(Y, Y1 + a.arm_y);
   // source row of slot i (wave-uniform), clamped into the sources
   auto src_row = [&](int i) { return min(ys + wave + kTcwWaves * i, ye - 1); };
@@ -611,7 +612,7 @@ __global__ void __launch_bounds__(64 * kTcwWaves) k_soft_tcolw(TcwArgs a) {
 #pragma unroll
     for (int i = 0; i < kTcwSrc; ++i)
       w[i] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(
-          rw, vcol, sp + (uint32_t)src_row(i) * (uint32_t)X * 4u, 0));
+          rw, vcol, sp + (uint32_t)src_row(i) * (uint32_t)a.XW * 4u, 0));
   };
   auto stage_a = [&](int k, uint32_t* mx) {
     const float fd = (float)(d0 + k);
@@ -633,7 +634,7 @@ __global__ void __launch_bounds__(64 * kTcwWaves) k_soft_tcolw(TcwArgs a) {
   // output rows Y0 + r0 .. of this wave, and the lane's place in a row
   const int rpw = B / kTcwWaves, r0 = wave * rpw;
   const size_t dstride = (size_t)a.npair * plane;
-  float* gout = a.gcax + ((size_t)(d0 - a.dlo) * a.npair + pair) * plane + (size_t)(Y0 + r0) * X + x;
+  float* gout = a.gcax + ((size_t)(d0 - a.dlo) * a.npair + pair) * plane + (size_t)(Y0 + r0) * a.XW + x;
   if (n <= 0) return;  // block-uniform
   load_w(0);
   if (t < 192) (&s_max[0][0])[t] = 0u;
@@ -686,7 +687,7 @@ __global__ void __launch_bounds__(64 * kTcwWaves) k_soft_tcolw(TcwArgs a) {
         float* o = gout + (size_t)(k - 2) * dstride;
 #pragma unroll
         for (int i = 0; i < RPW; ++i)
-          if (i < rpw && Y0 + r0 + i < Y1) o[(size_t)i * X] = (float)(loc[i] + off) * down;
+          if (i < rpw && Y0 + r0 + i < Y1) o[(size_t)i * a.XW] = (float)(loc[i] + off) * down;
       }
     }
     if (k >= 1 && k <= n) {  // C
@@ -745,18 +746,18 @@ __global__ void __launch_bounds__(64 * kTcwWaves) k_soft_tcolw(TcwArgs a) {
 // A block takes 4 rows of a strip.
 // Vector arithmetic bound (about 43 instructions a column and disparity, 16 of
 // them for the derivatives; three waves a SIMD).  4 pairs of 718x496, 73
-// disparities: 242 us as a scan and scatter of difference arrays in LDS, 202 now;
+// disparities: 242 us as a scan and scatter of difference arrays in LDS, 197 now;
 // at 960x540 and 128 disparities 557 and 445.
 // grid: strips * ceil(Y / 4) * n rounded up to 8 (1-D, xcd_item), block 256.
 struct TrArgs {
-  const float* gcax;        // [nds][n][Y][X] dL/dCA_x
+  const float* gcax;        // [nds][n][Y][XW] dL/dCA_x
   const uint32_t* arms;     // [2n][Y][XA]
   const uint2* sp;          // [2n][Y][XS] padded pixel planes
   const float* lam;         // device [2]
   float* g_half;            // [2n][Y][X] half-image gradients (left ones written or added here)
   float* gr_part;           // [n][strips][Y][WP] -dL/dR partials of this slab
   float2* lam_part;         // one {d/dlambda_AD, d/dlambda_census} per workgroup
-  int X, Y, XS, pads, XA, npair, dlo, dhi, nstrips, WP;
+  int X, Y, XS, pads, XA, XW, npair, dlo, dhi, nstrips, WP;
   int first;                // first slab: the left gradients are written, not added
 };
 
@@ -806,8 +807,8 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) k
     const uint2* spl = a.sp + ((size_t)(2 * pair) * Y + y) * a.XS + a.pads;
     const uint2* spr = spl + (size_t)Y * a.XS;
     const uint32_t* arm = a.arms + ((size_t)(2 * pair) * Y + y) * a.XA;
-    const float* grow = a.gcax + ((size_t)pair * Y + y) * X;
-    const size_t dstride = (size_t)a.npair * Y * X;
+    const float* grow = a.gcax + ((size_t)pair * Y + y) * a.XW;
+    const size_t dstride = (size_t)a.npair * Y * a.XW;
     const bool ends = x0 < 32 || x0 + 96 > X;  // some sources lie outside the image
     // the sources of a tile of 16 disparities: source tile k, this lane's
     // disparity (past the slab the last one again; its rows are not used) and its
@@ -817,12 +818,11 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) k
       const int dl = min(dt + l16, a.dhi - 1) - a.dlo;
 #pragma unroll
       for (int k = 0; k < 2; ++k) {
-        // (a group past the row's end reads on, at most 15 columns into the
-        // next row or plane, or past the planes into the scratch behind them)
+        // (a group that reaches past X ends in the row's padding)
         const int xs = x0 - 32 + 64 * k + 16 * quarter;
         const float* gp = grow + (size_t)dl * dstride + min(max(xs, 0), (X - 1) & ~15);
 #pragma unroll
-        for (int j = 0; j < 4; ++j) __builtin_memcpy(&v[k][j], gp + 4 * j, 16);
+        for (int j = 0; j < 4; ++j) v[k][j] = reinterpret_cast<const float4*>(gp)[j];
       }
     };
     load_tile(a.dlo);
