@@ -1105,7 +1105,10 @@ __device__ __forceinline__ int fill_value(const uint64_t* gm, const int16_t* med
   return xl >= 0 ? med[xl] : xr < X ? med[xr] : 0;
 }
 
-constexpr int kRefMaxX = 4096;  // widest half-res (or full-res mode) row
+// LDS bytes of a workgroup, by the row's width: with 45 kB for every width (4096
+// columns) a CU held 12 waves.  8 pairs of 960x540 31.6 us before, 23.4 now; one of
+// 1436x992 14.0 and 12.0; 718x496, where the grid does not fill the CUs, 6.1 and 6.3.
+inline unsigned refine_lds(int X) { return (unsigned)((X + 63) / 64) * (8 + 64 * 11); }
 
 __global__ void __launch_bounds__(256) k_refine(const int16_t* __restrict__ disp, int nk,
                                                 const uint16_t* __restrict__ pk, int XP, int pad,
@@ -1114,10 +1117,12 @@ __global__ void __launch_bounds__(256) k_refine(const int16_t* __restrict__ disp
                                                 int16_t* __restrict__ med_out,
                                                 int16_t* __restrict__ filled, PairPtrs pp,
                                                 int full) {
-  __shared__ int16_t s_d[4][kRefMaxX];          // D^L rows y-1, y, y+1 (clamped), D^R row y
-  __shared__ int16_t s_med[kRefMaxX];
-  __shared__ uint8_t s_h[kRefMaxX];             // left gray of row y
-  __shared__ uint64_t s_gm[kRefMaxX / 64];      // GCP flag of column x in bit x % 64 of word x / 64
+  extern __shared__ uint64_t s_ref[];           // refine_lds(X) bytes, rows of P columns
+  const int P = (X + 63) & ~63;
+  uint64_t* s_gm = s_ref;                       // GCP flag of column x in bit x % 64 of word x / 64
+  int16_t* s_d = reinterpret_cast<int16_t*>(s_gm + P / 64);  // 4 rows: D^L y-1, y, y+1 (clamped), D^R y
+  int16_t* s_med = s_d + 4 * P;
+  uint8_t* s_h = reinterpret_cast<uint8_t*>(s_med + P);      // left gray of row y
   const int y = blockIdx.x, pair = blockIdx.y, t = threadIdx.x;
   const size_t plane = (size_t)X * Y;
   const int16_t* dl = disp + (size_t)(2 * pair) * nk;
@@ -1143,7 +1148,7 @@ __global__ void __launch_bounds__(256) k_refine(const int16_t* __restrict__ disp
       const int x = xb + t + 256 * i;
       if (x < X) {
 #pragma unroll
-        for (int q = 0; q < 4; ++q) s_d[q][x] = a[i][q];
+        for (int q = 0; q < 4; ++q) s_d[q * P + x] = a[i][q];
         s_h[x] = (uint8_t)hp[i];
       }
     }
@@ -1156,17 +1161,17 @@ __global__ void __launch_bounds__(256) k_refine(const int16_t* __restrict__ disp
     bool g = false;
     if (x < X) {
       const int xm = max(x - 1, 0), xp = min(x + 1, X - 1);
-      int v[9] = {s_d[0][xm], s_d[0][x], s_d[0][xp], s_d[1][xm], s_d[1][x],
-                  s_d[1][xp], s_d[2][xm], s_d[2][x], s_d[2][xp]};
+      const int16_t *d1 = s_d + P, *d2 = d1 + P;
+      int v[9] = {s_d[xm], s_d[x], s_d[xp], d1[xm], d1[x], d1[xp], d2[xm], d2[x], d2[xp]};
       const int k = v[4];
-      g = x - k >= 0 && s_d[3][x - k] == k;
+      g = x - k >= 0 && d2[P + x - k] == k;
       const int m = median9(v);
       s_med[x] = (int16_t)m;
       if (gcp_out) gcp_out[(size_t)pair * plane + r0 + x] = (uint8_t)g;
       if (med_out) med_out[(size_t)pair * plane + r0 + x] = (int16_t)m;
     }
     const uint64_t bal = __ballot(g);
-    if ((t & 63) == 0) s_gm[x >> 6] = bal;
+    if ((t & 63) == 0 && x < X) s_gm[x >> 6] = bal;  // (words of the row only)
   }
   __syncthreads();
   // fill: the nearest GCPs left and right from the bit array

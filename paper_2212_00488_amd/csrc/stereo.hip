@@ -677,7 +677,7 @@ int run(stereo_ctx* c, Plan& pl, const PairPtrs& pp, int npair, bool keep, bool 
   hipLaunchKernelGGL(k_wta, dim3((pl.nk + 1023) / 1024, npair), dim3(256), 0, s, pl.keys,
                      pl.nchunk, pl.nk, pl.dbits, pl.disp, keep ? pl.mincost : nullptr);
   mark(4);
-  hipLaunchKernelGGL(k_refine, dim3(Y, npair), dim3(256), 0, s, pl.disp, pl.nk, pl.pk, pl.XP,
+  hipLaunchKernelGGL(k_refine, dim3(Y, npair), dim3(256), refine_lds(X), s, pl.disp, pl.nk, pl.pk, pl.XP,
                      pl.pad, X, Y, pl.p.fill_T, pl.p.fill_mode, keep ? pl.gcp : nullptr,
                      keep ? pl.med : nullptr, full && !keep ? nullptr : pl.filled, pp, (int)full);
   mark(5);
