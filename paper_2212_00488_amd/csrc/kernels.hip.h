@@ -378,21 +378,10 @@ k_feat(const uint8_t* __restrict__ half, int X, int Y, int delta, int arm_x_l, i
 }
 
 // ---------------------------------------------------------------- k_match
-// Inclusive prefix sum over the 64 lanes of a wave (DPP row shifts inside
-// rows of 16 lanes, then row broadcasts across rows).
-__device__ __forceinline__ uint32_t wave_scan_incl(uint32_t v) {
-  v += __builtin_amdgcn_update_dpp(0u, v, 0x111, 0xf, 0xf, false);  // row_shr:1
-  v += __builtin_amdgcn_update_dpp(0u, v, 0x112, 0xf, 0xf, false);  // row_shr:2
-  v += __builtin_amdgcn_update_dpp(0u, v, 0x114, 0xf, 0xf, false);  // row_shr:4
-  v += __builtin_amdgcn_update_dpp(0u, v, 0x118, 0xf, 0xf, false);  // row_shr:8
-  v += __builtin_amdgcn_update_dpp(0u, v, 0x142, 0xa, 0xf, false);  // row_bcast:15
-  v += __builtin_amdgcn_update_dpp(0u, v, 0x143, 0xc, 0xf, false);  // row_bcast:31
-  return v;
-}
-
-
-// The same scan of N values, step by step in turn: each DPP step waits two
-// slots for the value it reads, which the other values' steps fill.
+// Inclusive prefix sums over the 64 lanes of a wave of N values (DPP row shifts
+// inside rows of 16 lanes, then row broadcasts across rows), step by step in turn:
+// each DPP step waits two slots for the value it reads, which the other values'
+// steps fill.
 template <int N>
 __device__ __forceinline__ void wave_scan_incl_n(uint32_t (&v)[N]) {
 #pragma unroll

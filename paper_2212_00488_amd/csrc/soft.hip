@@ -26,7 +26,7 @@ constexpr size_t kSlabBudget = size_t(1) << 30;
 struct SoftPlan {
   int n = 0, W = 0, H = 0, Dmax = 0, X = 0, Y = 0, D = 0;
   stereo_soft_params p{};
-  int ns = 1, kmax = 8, nstrips = 0, nbands = 0, rows = 0;
+  int kmax = 8, nstrips = 0, nbands = 0, rows = 0;
   int csize = 1, nchunk = 0;   // k_soft_agg d-chunk size and forward chunk count
   int XS = 0, pads = 0, XA = 0;
   int XW = 0;          // row pitch of the weight and dL/dCA_x planes: whole 128-byte lines
