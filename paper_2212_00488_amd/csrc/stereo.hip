@@ -788,8 +788,11 @@ int stereo_disparity_batch(stereo_ctx* c, const uint8_t* const* left, const uint
   if (hipStreamIsCapturing(stream, &cs) == hipSuccess && cs != hipStreamCaptureStatusNone)
     pl->captured = true;
   (void)hipGetLastError();
-  for (int i0 = 0; i0 < n; i0 += kMaxPairs) {
-    const int m = std::min(kMaxPairs, n - i0);
+  // where planes are kept, those of pair 0: its launch comes last, since every
+  // launch uses the same scratch
+  const int ngroups = (n + kMaxPairs - 1) / kMaxPairs;
+  for (int g = 0; g < ngroups; ++g) {
+    const int i0 = (keep ? (g + 1) % ngroups : g) * kMaxPairs, m = std::min(kMaxPairs, n - i0);
     PairPtrs pp{};
     for (int i = 0; i < m; ++i) {
       pp.left[i] = left[i0 + i];

@@ -587,3 +587,21 @@ def test_full_resolution_output_without_kept_planes(sm, ctx):
     torch.cuda.synchronize()
     exp = oracle.disparity(pair.left, pair.right, 20, oracle_params(p))
     assert_same("full-resolution map", out.cpu().numpy(), exp["out"])
+
+
+def test_kept_planes_of_a_batch_of_more_than_eight_are_pair_0s(sm, ctx):
+    """A batch of nine runs as two launches; the planes kept are pair 0's, all of
+    them (the second launch uses the same scratch)."""
+    pairs = [make_pair(96, 64, 24, segments=3, seed=820 + i) for i in range(9)]
+    lefts = [torch.from_numpy(p.left).cuda() for p in pairs]
+    rights = [torch.from_numpy(p.right).cuda() for p in pairs]
+    outs = ctx.disparity_batch(lefts, rights, 24, keep_params(sm))
+    torch.cuda.synchronize()
+    exp = oracle.disparity(pairs[0].left, pairs[0].right, 24)
+    for k in HALF_KEYS:
+        assert_same(k, ctx.intermediate(k), exp[k])
+    for k, o in MIN_KEYS:
+        assert_same(k, ctx.intermediate(k), exp[o])
+    for i in (0, 7, 8):
+        assert_same(f"pair {i}", outs[i].cpu().numpy(),
+                    oracle.disparity(pairs[i].left, pairs[i].right, 24)["out"])
