@@ -912,10 +912,24 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) k
       }
       mx = fmaxf(mx, __shfl_xor(mx, 16));
       mx = fmaxf(mx, __shfl_xor(mx, 32));
-      // (the next float up: a mantissa of ones would round to 2^23; the smallest
-      // terms' scale stays finite)
+      // (the smallest terms' scale stays finite)
       const uint32_t mb = __float_as_uint(mx);
-      const int ex = max(float_exp(mb + 1u), -100);
+      const int ex = max(float_exp(mb), -100);
+      // a mantissa of ones would round to 2^23, one more than three bytes hold: such
+      // values are taken as the float below, 2^23 - 1 units (as near as 2^23 is)
+      const bool ones = (mb & 0x7fffffu) == 0x7fffffu;
+      if (__any(ones)) {
+        const float lim = __uint_as_float(ones ? mb - 1u : mb);
+#pragma unroll
+        for (int k = 0; k < 2; ++k)
+#pragma unroll
+          for (int j = 0; j < 4; ++j) {
+            v[k][j].x = fminf(fmaxf(v[k][j].x, -lim), lim);
+            v[k][j].y = fminf(fmaxf(v[k][j].y, -lim), lim);
+            v[k][j].z = fminf(fmaxf(v[k][j].z, -lim), lim);
+            v[k][j].w = fminf(fmaxf(v[k][j].w, -lim), lim);
+          }
+      }
       const float up = mb ? ldexpf(1.f, 23 - ex) : 0.f;
       if (lane < kTrD) s_dn[wave][lane] = mb ? ldexpf(1.f, ex - 23) : 0.f;
       // the terms' bytes, the lower two less 128

@@ -459,3 +459,64 @@ def test_horizontal_adjoint_edges_match_oracle(ctx, case):
     assert_grad_close(gr, rgr, "g_right")
     for k in range(2):
         assert abs(glam[k] - rglam[k]) <= 1e-3 * abs(rglam[k]) + 1e-9, (k, glam, rglam)
+
+
+def test_adjoint_terms_keep_their_unit_at_a_mantissa_of_ones():
+    """k_soft_tr's terms are rounded to 2^(e-24), 2^(e-1) <= the largest |dL/dCA_x|
+    of a row's sources < 2^e: also where that largest value is all ones in its
+    mantissa, just below 2^e.  Constant images, so that every quantity below is
+    exact in floats: column A's three sources add up to a largest value of S units
+    of 2^(e-24), S = 2^24 - 2, 2^24 - 1 and 2^24, and column B's is 0.8 of 2^(e-23)
+    with e of the first two: one unit there, none for the third."""
+    f = np.float32
+    W, H, X, Y, arm_y, tau = 256, 160, 128, 80, 2, f(0.2)
+    p = soft_default_params(tau=float(tau), arm_x=0, arm_y=arm_y)
+    left = torch.full((1, H, W, 3), 1e-20, device=DEV)
+    right = torch.zeros((1, H, W, 3), device=DEV)
+    lam = torch.tensor((255.0, 30.0), device=DEV)
+    A, B = 40, 48
+
+    def const(g):  # A of k_soft_bprep for a g_dhat, |S| = 5
+        return f(f(-g * f(f(1) / f(2 * arm_y + 1))) * f(f(1) / tau))
+
+    def g_for(value):  # a g_dhat whose dL/dCA at d = 1 is exactly value
+        g = f(-value * 4)
+        for _ in range(64):
+            got = const(g) * f(0.25)
+            if got == f(value):
+                return g
+            g = np.nextafter(g, f(-np.inf) if got < value else f(np.inf))
+        return None
+
+    # terms of column A: q units of 2^-25 (all below 2^23: 2^-2 is the column's scale)
+    g = np.zeros((1, Y, X), f)
+    rows, units = [], []
+    y = 6
+    for S in (2**24 - 2, 2**24 - 1, 2**24):
+        for q1 in (6710886, 7000001, 7300000):
+            q2 = 5000000 + q1 % 1000
+            qs = (q1, q2, S - q1 - q2)
+            gs = [g_for(q * 2.0**-25) for q in qs]
+            if None in gs or max(qs) >= 2**23:
+                continue
+            g[0, y - 1:y + 2, A] = gs
+            g[0, y, B] = f(-0.8 * 2.0**-22)
+            rows.append(y)
+            units.append(S)
+            y += 8
+    assert set(units) == {2**24 - 2, 2**24 - 1, 2**24}, units
+    c = Stereo(0)
+    d_hat, lse2 = c.soft_forward(left, right, lam, 4, p)
+    assert float((d_hat[0, :, 1:] - 0.5).abs().max()) == 0.0
+    gl, gr, _ = c.soft_backward(left, right, lam, 4, d_hat, lse2, torch.from_numpy(g).to(DEV), p)
+    torch.cuda.synchronize()
+    c.close()
+    # half-image gradient from the red channel of the pixel at even coordinates
+    half = gr[0, ::2, ::2, 0].cpu().numpy().astype(np.float64) * (2304.0 / 77.0)
+    for y, S in zip(rows, units):
+        # right pixel x - 1 takes -dL/dC(x, d = 1)
+        a, b = -half[y, A - 1], -half[y, B - 1]
+        print(f"[soft] S = 2^24 - {2**24 - S}: A {a!r}, B {b!r}", flush=True)
+        assert abs(a - S * 2.0**-25) <= 2.0**-22 * a, (S, a)
+        exp = 2.0**-24 if S < 2**24 else 0.0
+        assert abs(b - exp) <= 2.0**-40, (S, b, exp)
