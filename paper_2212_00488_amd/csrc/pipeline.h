@@ -22,6 +22,7 @@ struct Plan {
   int ns = 1, nbase = 2, kmax = 8, nbands = 0, brows = 0;
   int csize = 1, nchunk = 0;    // largest d-chunk and chunk count
   int ccap = 1;                 // largest chunk size the strips of both bases allow
+  double model_t = 0.0;         // modelled k_match time of the geometry (plan_geometry)
   int XP = 0, pad = 0, XA = 0;  // padded pitches of pk and arms
   int nk = 0;                   // padded plane stride of keys, disp and mincost
   size_t bytes = 0;
@@ -55,9 +56,10 @@ struct Plan {
 int common_checks(stereo_ctx* c, int W, int H, int Dmax, const stereo_params* params,
                   stereo_params* p);
 // The cached plan of (W, H, Dmax, p, owner) holding at least npair pairs,
-// made (and least recently used plans evicted under the memory cap, except
-// pinned ones) when missing; a new plan's set-up is enqueued on stream s,
-// the stream its work will run on.  Calls with different owners never share
+// made when missing: least recently used plans are given up (except pinned ones)
+// while the memory cap or the device does not hold the preferred launch
+// geometry, and only then a smaller one is taken.  A new plan's set-up is
+// enqueued on stream s, the stream its work will run on.  Calls with different owners never share
 // scratch, so their work may overlap on the device.
 int get_plan(stereo_ctx* c, int W, int H, int Dmax, const stereo_params& p, int npair,
              const void* owner, hipStream_t s, Plan** out);

@@ -318,6 +318,7 @@ void plan_geometry(Plan& pl, int num_cu, int forced_csize, int nbase) {
         pl.kmax = b.kmax;
         pl.brows = b.rows;
         pl.nchunk = n;
+        pl.model_t = t;
       }
     }
   }
@@ -361,9 +362,9 @@ PlanBytes plan_bytes(const Plan& pl) {
   return b;
 }
 
-// Launch geometries of a shape, the first the preferred one: where scratch is
-// bounded, the later ones need less of it (fewer chunk keys; one base a
-// workgroup, whose chunks may hold all disparities).
+// Launch geometries of a shape, the first the preferred one: both bases a
+// workgroup or one base (whose chunks may hold all disparities), the chunks of
+// the shortest modelled time or as few as the strips allow (fewer keys).
 struct Form {
   int nbase;
   bool fewest_chunks;
@@ -423,34 +424,43 @@ void plan_carve_and_init(Plan& pl, void* base, hipStream_t s) {
                      reinterpret_cast<uint32_t*>(pl.pk), nzero, pl.tab, t);
 }
 
-int make_plan(stereo_ctx* c, int W, int H, int Dmax, const stereo_params& p, int npair,
-              hipStream_t s, Plan** out) {
-  // the first form whose scratch the cap and the device allow
-  Plan* pl = nullptr;
-  size_t bytes = 0;
-  hipError_t e = hipSuccess;
-  int rc = 0;
+// The geometries to take where the scratch does not hold the preferred one
+// (`first`): the other forms in order of modelled time, each needing less scratch
+// than every one before it (at 1436x992 Dmax 145 the forms take 45.9, 28.8, 31.7
+// and 20.3 MB at 4224, 4829, 7240 and 15157 units: the third is none of these).
+std::vector<Plan> smaller_forms(stereo_ctx* c, const Plan& first) {
+  std::vector<Plan> all, out;
+  const std::string err = c->err;  // a form that is refused is left out
   for (const Form& form : kForms) {
-    delete pl;
-    pl = new Plan();
-    rc = plan_setup(c, *pl, W, H, Dmax, p, npair, form);
-    if (rc) break;
-    bytes = plan_bytes(*pl).total;
-    if (c->mem_cap && c->used + bytes > c->mem_cap) {
-      rc = fail(c, STEREO_ENOMEM, "plan needs %zu bytes, cap %zu, in use %zu", bytes, c->mem_cap,
-                c->used);
-      continue;
+    Plan pl;
+    if (&form != kForms && !plan_setup(c, pl, first.W, first.H, first.Dmax, first.p, first.npair, form))
+      all.push_back(pl);
+  }
+  c->err = err;
+  std::sort(all.begin(), all.end(), [](const Plan& a, const Plan& b) { return a.model_t < b.model_t; });
+  size_t least = plan_bytes(first).total;
+  for (const Plan& pl : all)
+    if (plan_bytes(pl).total < least) {
+      least = plan_bytes(pl).total;
+      out.push_back(pl);
     }
-    e = hipMalloc(&pl->block, bytes);
-    if (e == hipSuccess) break;
+  return out;
+}
+
+// A plan of the geometry geo: its device memory, and its set-up enqueued on s.
+int make_plan(stereo_ctx* c, const Plan& geo, hipStream_t s, Plan** out) {
+  const size_t bytes = plan_bytes(geo).total;
+  if (c->mem_cap && c->used + bytes > c->mem_cap)
+    return fail(c, STEREO_ENOMEM, "plan needs %zu bytes, cap %zu, in use %zu", bytes, c->mem_cap,
+                c->used);
+  void* block = nullptr;
+  hipError_t e = hipMalloc(&block, bytes);
+  if (e != hipSuccess) {
     (void)hipGetLastError();
-    rc = fail(c, STEREO_ENOMEM, "hipMalloc(%zu): %s", bytes, hipGetErrorString(e));
+    return fail(c, STEREO_ENOMEM, "hipMalloc(%zu): %s", bytes, hipGetErrorString(e));
   }
-  if (rc) {
-    delete pl;
-    return rc;
-  }
-  c->err.clear();
+  Plan* pl = new Plan(geo);
+  pl->block = block;
   pl->bytes = bytes;
   // set-up on the stream the plan serves: later work on that stream follows
   // it, and no other stream or slot is stalled
@@ -463,6 +473,39 @@ int make_plan(stereo_ctx* c, int W, int H, int Dmax, const stereo_params& p, int
   c->used += bytes;
   *out = pl;
   return 0;
+}
+
+// Plans that may be given up for another: not the one whose intermediates are
+// kept nor those a captured graph still launches into.
+bool evictable(const stereo_ctx* c, const Plan* pl) {
+  return pl != c->last && pl->pins == 0 && !pl->captured;
+}
+
+// Gives up the least recently used plan that may be (after the device has
+// finished with it); false when there is none.
+bool evict_one(stereo_ctx* c) {
+  Plan* lru = nullptr;
+  for (Plan* pl : c->plans)
+    if (evictable(c, pl) && (!lru || pl->last_use < lru->last_use)) lru = pl;
+  if (!lru) return false;
+  (void)hipDeviceSynchronize();
+  drop_plan(c, lru);
+  return true;
+}
+
+// make_plan, with idle plans given up while the scratch does not hold it.  A cap
+// that would not hold it with all of them gone is left as it is.
+int make_plan_evicting(stereo_ctx* c, const Plan& geo, hipStream_t s, Plan** out) {
+  const size_t bytes = plan_bytes(geo).total;
+  size_t kept = c->used;
+  for (const Plan* pl : c->plans)
+    if (evictable(c, pl)) kept -= pl->bytes;
+  if (c->mem_cap && kept + bytes > c->mem_cap)
+    return fail(c, STEREO_ENOMEM, "plan needs %zu bytes, cap %zu, in use %zu", bytes, c->mem_cap,
+                c->used);
+  int rc = make_plan(c, geo, s, out);
+  while (rc == STEREO_ENOMEM && evict_one(c)) rc = make_plan(c, geo, s, out);
+  return rc;
 }
 
 int get_plan(stereo_ctx* c, int W, int H, int Dmax, const stereo_params& p, int npair,
@@ -482,26 +525,19 @@ int get_plan(stereo_ctx* c, int W, int H, int Dmax, const stereo_params& p, int 
                 "no scratch yet for %dx%d Dmax %d on this stream: make one call outside the "
                 "graph capture first (or use stereo_disparity_noalloc)", W, H, Dmax);
   (void)hipGetLastError();
-  Plan* pl = nullptr;
-  int rc = make_plan(c, W, H, Dmax, p, npair, s, &pl);
-  if (rc == STEREO_ENOMEM && !c->plans.empty()) {
-    // evict least recently used plans, except the one whose intermediates are
-    // kept and those a captured graph still launches into, then retry
-    std::sort(c->plans.begin(), c->plans.end(),
-              [](Plan* a, Plan* b) { return a->last_use < b->last_use; });
-    for (size_t i = 0; i < c->plans.size() && rc == STEREO_ENOMEM;) {
-      if (c->plans[i] == c->last || c->plans[i]->pins > 0 || c->plans[i]->captured) {
-        ++i;
-        continue;
-      }
-      (void)hipDeviceSynchronize();
-      c->used -= c->plans[i]->bytes;
-      free_plan(c->plans[i]);
-      c->plans.erase(c->plans.begin() + i);
-      rc = make_plan(c, W, H, Dmax, p, npair, s, &pl);
-    }
-  }
+  // the preferred form, idle plans given up for it; where the scratch does not
+  // hold it even so, the fastest of the smaller ones that it does
+  Plan geo, *pl = nullptr;
+  int rc = plan_setup(c, geo, W, H, Dmax, p, npair, kForms[0]);
   if (rc) return rc;
+  rc = make_plan_evicting(c, geo, s, &pl);
+  if (rc == STEREO_ENOMEM)
+    for (const Plan& g : smaller_forms(c, geo)) {
+      rc = make_plan_evicting(c, g, s, &pl);
+      if (rc != STEREO_ENOMEM) break;
+    }
+  if (rc) return rc;
+  c->err.clear();
   pl->last_use = ++c->tick;
   pl->owner = owner;
   c->plans.push_back(pl);
@@ -911,14 +947,14 @@ int stereo_disparity_noalloc(stereo_ctx* c, const uint8_t* left, const uint8_t* 
   // and tables are host arithmetic, the set-up (padding cleared, cost table
   // written) is a kernel on the caller's stream
   Plan pl{};
-  size_t bytes = 0;
-  for (const Form& form : kForms) {
-    pl = Plan{};
-    rc = plan_setup(c, pl, W, H, Dmax, p, 1, form);
-    if (rc) return rc;
-    bytes = plan_bytes(pl).total;
-    if (bytes <= kNoallocBytes) break;
-  }
+  rc = plan_setup(c, pl, W, H, Dmax, p, 1, kForms[0]);
+  if (rc) return rc;
+  if (plan_bytes(pl).total > kNoallocBytes)
+    for (const Plan& g : smaller_forms(c, pl)) {
+      pl = g;
+      if (plan_bytes(pl).total <= kNoallocBytes) break;
+    }
+  const size_t bytes = plan_bytes(pl).total;
   if (bytes > kNoallocBytes)
     return fail(c, STEREO_EINVAL, "%dx%d Dmax %d needs %zu bytes of scratch; the fixed array "
                 "holds %zu (use stereo_disparity)", W, H, Dmax, bytes, kNoallocBytes);

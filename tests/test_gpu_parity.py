@@ -605,3 +605,69 @@ def test_kept_planes_of_a_batch_of_more_than_eight_are_pair_0s(sm, ctx):
     for i in (0, 7, 8):
         assert_same(f"pair {i}", outs[i].cpu().numpy(),
                     oracle.disparity(pairs[i].left, pairs[i].right, 24)["out"])
+
+
+def device_bytes_free():
+    torch.cuda.synchronize()
+    return torch.cuda.mem_get_info()[0]
+
+
+def noise_pair(W, H, seed):
+    g = torch.Generator().manual_seed(seed)
+    im = torch.randint(0, 256, (H, W + 8, 3), dtype=torch.uint8, generator=g)
+    return im[:, :W].contiguous().cuda(), im[:, 8:].contiguous().cuda()
+
+
+def test_cap_evicts_an_idle_plan_before_a_smaller_form(sm):
+    """A cap that holds one plan of two shapes served in turn: each call evicts
+    the idle plan and runs its shape's preferred form (seen by the scratch it
+    takes, the same as in a context of its own), not a form of fewer chunks
+    beside the idle plan."""
+    shapes = [(1436, 992, 145), (1400, 1000, 145)]
+    data = [noise_pair(w, h, 800 + i) for i, (w, h, _) in enumerate(shapes)]
+    outs = [torch.empty((h, w), dtype=torch.int16, device="cuda") for w, h, _ in shapes]
+    ref, alone = [], []
+    for (w, h, dm), (lt, rt), o in zip(shapes, data, outs):
+        c = sm.Stereo(0)
+        c.disparity(lt, rt, dm, out=o)  # kernels loaded before memory is counted
+        ref.append(o.cpu().numpy())
+        c.close()
+        free0 = device_bytes_free()
+        c = sm.Stereo(0)
+        c.disparity(lt, rt, dm, out=o)
+        alone.append(free0 - device_bytes_free())
+        c.close()
+    say(f"scratch of each shape alone: {alone}")
+    assert min(alone) > 30 << 20
+    # beside either plan there is room for a form of fewer chunks only
+    cap = int(1.55 * max(alone))
+    free0 = device_bytes_free()
+    c = sm.Stereo(0, mem_cap=cap)
+    for k in (0, 1, 0, 1):
+        w, h, dm = shapes[k]
+        outs[k].fill_(-7)
+        c.disparity(*data[k], dm, out=outs[k])
+        taken = free0 - device_bytes_free()
+        say(f"shape {k}: scratch {taken}")
+        assert abs(taken - alone[k]) <= 4 << 20, (k, taken, alone)
+        assert_same(f"shape {k}", outs[k].cpu().numpy(), ref[k])
+    c.close()
+
+
+def test_refused_shape_evicts_nothing(sm):
+    """A shape that no form of fits the cap is refused without giving up the
+    plans of the shapes that do."""
+    lt, rt = noise_pair(640, 480, 810)
+    bl, br = noise_pair(2872, 1984, 811)
+    out, bo = (torch.empty(t.shape[:2], dtype=torch.int16, device="cuda") for t in (lt, bl))
+    c = sm.Stereo(0, mem_cap=24 << 20)
+    c.disparity(lt, rt, 64, out=out)
+    exp, free0 = out.cpu().numpy(), device_bytes_free()
+    with pytest.raises(sm.StereoError) as e:
+        c.disparity(bl, br, 290, out=bo)
+    assert e.value.code == sm.binding.ENOMEM
+    assert abs(free0 - device_bytes_free()) <= 2 << 20
+    c.disparity(lt, rt, 64, out=out)
+    torch.cuda.synchronize()
+    assert_same("map", out.cpu().numpy(), exp)
+    c.close()
