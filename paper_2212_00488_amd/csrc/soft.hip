@@ -154,59 +154,52 @@ size_t soft_bytes(const SoftPlan& pl, int nw, int nds) {
          al(n * pl.nstrips * Y * (64 + nds - 1) * 4);
 }
 
-int make_soft_plan(stereo_ctx* c, int n, int W, int H, int Dmax, const stereo_soft_params& p,
-                   hipStream_t s, SoftPlan** out) {
-  SoftPlan* pl = new SoftPlan();
-  pl->n = n; pl->W = W; pl->H = H; pl->Dmax = Dmax; pl->p = p;
-  soft_geometry(*pl, c->num_cu);
-  const int X = pl->X, Y = pl->Y, D = pl->D;
-  const size_t npix = (size_t)X * Y, nplane = (size_t)pl->XW * Y, nimg = 2 * (size_t)n;
-  // k_soft_agg addresses the pixel and arm planes through 32-bit buffer
-  // offsets
-  if (nimg * Y * pl->XS * 8 >= (size_t(1) << 32) || nimg * Y * pl->XA * 4 >= (size_t(1) << 32)) {
-    delete pl;
-    return fail(c, STEREO_EINVAL, "%d pairs of %dx%d exceed the 4 GiB pixel or arm planes of the "
-                "soft head; pass fewer pairs per call", n, W, H);
-  }
-  // the slab of kSlabBudget, or the caller's (at most 128 disparities: k_soft_tr's
-  // LDS rows of right gradients), and weight planes of all D when they can be
-  // addressed and the caller sets no slab: the backward then computes no CA
-  // again.  One slab saves e_d; the terms of several are formed from CA itself,
-  // p_d = 2^{-CA w - log2 sum e} in one rounding of the exponent, as they are when
-  // the planes are computed again.  Smaller planes and slabs where the cap or the
-  // device does not hold the scratch.
+// Disparities that a plan's weight planes (nw) and a backward slab (nds) hold.
+struct SoftPlanes {
+  int nw, nds;
+};
+
+// The planes of a plan, the preferred ones first: the slab of kSlabBudget, or the
+// caller's (at most 128 disparities: k_soft_tr's LDS rows of right gradients), and
+// weight planes of all D when they can be addressed and the caller sets no slab:
+// the backward then computes no CA again.  The others, for where the cap or the
+// device does not hold the scratch: the weights of a slab, then smaller slabs.
+std::vector<SoftPlanes> soft_planes(const SoftPlan& pl) {
+  const size_t npix = (size_t)pl.X * pl.Y, nplane = (size_t)pl.XW * pl.Y, n = pl.n;
+  const int D = pl.D, slab = pl.p.slab;
   const size_t budget = std::max<size_t>(1, kSlabBudget / (2 * n * npix * 4));
-  int nds = std::min(p.slab > 0 ? std::min(p.slab, D) : (int)std::min<size_t>(D, budget), kTrMaxWP - 63);
+  int nds = std::min(slab > 0 ? std::min(slab, D) : (int)std::min<size_t>(D, budget), kTrMaxWP - 63);
   nds = (int)std::max<size_t>(1, std::min<size_t>(nds, kPlanesMost / (n * nplane * 4)));
-  pl->ca = nds < D;
-  int nw = p.slab > 0 || (size_t)D * n * nplane * 4 > kPlanesMost ? nds : D;
-  size_t bytes = 0;
-  int rc = 0;
-  for (;;) {
-    bytes = soft_bytes(*pl, nw, nds);
-    rc = 0;
-    if (c->mem_cap && c->used + bytes > c->mem_cap) {
-      rc = fail(c, STEREO_ENOMEM, "soft plan needs %zu bytes, cap %zu, in use %zu", bytes,
+  std::vector<SoftPlanes> v;
+  if (slab == 0 && nds < D && (size_t)D * n * nplane * 4 <= kPlanesMost) v.push_back({D, nds});
+  for (;; nds = (nds + 1) / 2) {
+    v.push_back({nds, nds});
+    if (nds == 1) return v;
+  }
+}
+
+// A plan of the geometry geo with the planes z: its device memory, and its set-up
+// enqueued on s.
+int make_soft_plan(stereo_ctx* c, const SoftPlan& geo, const SoftPlanes& z, hipStream_t s,
+                   SoftPlan** out) {
+  const size_t bytes = soft_bytes(geo, z.nw, z.nds);
+  if (c->mem_cap && c->used + bytes > c->mem_cap)
+    return fail(c, STEREO_ENOMEM, "soft plan needs %zu bytes, cap %zu, in use %zu", bytes,
                 c->mem_cap, c->used);
-    } else {
-      const hipError_t e = hipMalloc(&pl->block, bytes);
-      if (e == hipSuccess) break;
-      (void)hipGetLastError();
-      rc = fail(c, STEREO_ENOMEM, "hipMalloc(%zu): %s", bytes, hipGetErrorString(e));
-    }
-    if (nds == 1 && nw == 1) break;
-    if (nw == nds) nds = (nds + 1) / 2;
-    nw = nds;
+  void* block = nullptr;
+  hipError_t e = hipMalloc(&block, bytes);
+  if (e != hipSuccess) {
+    (void)hipGetLastError();
+    return fail(c, STEREO_ENOMEM, "hipMalloc(%zu): %s", bytes, hipGetErrorString(e));
   }
-  if (rc) {
-    delete pl;
-    return rc;
-  }
-  c->err.clear();
-  pl->nw = nw;
-  pl->nds = nds;
-  pl->WP = 64 + nds - 1;
-  pl->lam_count = (size_t)((D + nds - 1) / nds) * n * pl->nstrips * ((Y + kTrRows - 1) / kTrRows);
+  SoftPlan* pl = new SoftPlan(geo);
+  const int n = pl->n, Y = pl->Y, D = pl->D;
+  const size_t npix = (size_t)pl->X * Y, nplane = (size_t)pl->XW * Y, nimg = 2 * (size_t)n;
+  pl->block = block;
+  pl->nw = z.nw;
+  pl->nds = z.nds;
+  pl->WP = 64 + z.nds - 1;
+  pl->lam_count = (size_t)((D + z.nds - 1) / z.nds) * n * pl->nstrips * ((Y + kTrRows - 1) / kTrRows);
   pl->bytes = bytes;
   char* cur = static_cast<char*>(pl->block);
   pl->half_f = carve<float>(cur, nimg * npix);
@@ -216,8 +209,8 @@ int make_soft_plan(stereo_ctx* c, int n, int W, int H, int Dmax, const stereo_so
   pl->inv_size = carve<float>(cur, n * npix);
   pl->part = carve<float2>(cur, (size_t)n * pl->nchunk * npix);
   pl->pc = carve<float4>(cur, n * npix);
-  pl->wts = carve<float>(cur, (size_t)nw * n * nplane);
-  pl->gcax = carve<float>(cur, (size_t)nds * n * nplane);
+  pl->wts = carve<float>(cur, (size_t)z.nw * n * nplane);
+  pl->gcax = carve<float>(cur, (size_t)z.nds * n * nplane);
   pl->g_half = carve<float>(cur, nimg * npix);
   pl->lam_part = carve<float2>(cur, pl->lam_count);
   pl->gr_part = carve<float>(cur, (size_t)n * pl->nstrips * Y * pl->WP);
@@ -227,7 +220,7 @@ int make_soft_plan(stereo_ctx* c, int n, int W, int H, int Dmax, const stereo_so
                      nimg * Y * pl->XA, 0.f);
   hipLaunchKernelGGL(k_fill_f32, dim3(1024), dim3(256), 0, s, reinterpret_cast<float*>(pl->sp),
                      nimg * Y * pl->XS * 2, 0.f);
-  const hipError_t e = hipGetLastError();
+  e = hipGetLastError();
   if (e != hipSuccess) {
     (void)hipFree(pl->block);
     delete pl;
@@ -236,6 +229,35 @@ int make_soft_plan(stereo_ctx* c, int n, int W, int H, int Dmax, const stereo_so
   c->used += bytes;
   *out = pl;
   return 0;
+}
+
+// Gives up the least recently used soft plan (after the device has finished with
+// it); false when there is none.
+bool evict_one_soft(stereo_ctx* c) {
+  if (c->soft_plans.empty()) return false;
+  const auto lru = std::min_element(c->soft_plans.begin(), c->soft_plans.end(),
+                                    [](SoftPlan* a, SoftPlan* b) { return a->last_use < b->last_use; });
+  std::vector<SoftPlan*> one{*lru};
+  c->soft_plans.erase(lru);
+  (void)hipDeviceSynchronize();
+  c->used -= one[0]->bytes;
+  free_soft_plans(one);
+  return true;
+}
+
+// make_soft_plan, with other soft plans given up while the scratch does not hold
+// it.  A cap that would not hold it with all of them gone is left as it is.
+int make_soft_plan_evicting(stereo_ctx* c, const SoftPlan& geo, const SoftPlanes& z, hipStream_t s,
+                            SoftPlan** out) {
+  const size_t bytes = soft_bytes(geo, z.nw, z.nds);
+  size_t kept = c->used;
+  for (const SoftPlan* pl : c->soft_plans) kept -= pl->bytes;
+  if (c->mem_cap && kept + bytes > c->mem_cap)
+    return fail(c, STEREO_ENOMEM, "soft plan needs %zu bytes, cap %zu, in use %zu", bytes,
+                c->mem_cap, c->used);
+  int rc = make_soft_plan(c, geo, z, s, out);
+  while (rc == STEREO_ENOMEM && evict_one_soft(c)) rc = make_soft_plan(c, geo, z, s, out);
+  return rc;
 }
 
 int get_soft_plan(stereo_ctx* c, int n, int W, int H, int Dmax, const stereo_soft_params& p,
@@ -247,15 +269,27 @@ int get_soft_plan(stereo_ctx* c, int n, int W, int H, int Dmax, const stereo_sof
       *out = pl;
       return 0;
     }
-  SoftPlan* pl = nullptr;
-  int rc = make_soft_plan(c, n, W, H, Dmax, p, s, &pl);
-  if (rc == STEREO_ENOMEM && !c->soft_plans.empty()) {
-    (void)hipDeviceSynchronize();
-    for (SoftPlan* q : c->soft_plans) c->used -= q->bytes;
-    free_soft_plans(c->soft_plans);
-    rc = make_soft_plan(c, n, W, H, Dmax, p, s, &pl);
+  SoftPlan geo, *pl = nullptr;
+  geo.n = n; geo.W = W; geo.H = H; geo.Dmax = Dmax; geo.p = p;
+  soft_geometry(geo, c->num_cu);
+  // k_soft_agg addresses the pixel and arm planes through 32-bit buffer
+  // offsets
+  const size_t rows = (size_t)2 * n * geo.Y;
+  if (rows * geo.XS * 8 >= (size_t(1) << 32) || rows * geo.XA * 4 >= (size_t(1) << 32))
+    return fail(c, STEREO_EINVAL, "%d pairs of %dx%d exceed the 4 GiB pixel or arm planes of the "
+                "soft head; pass fewer pairs per call", n, W, H);
+  const std::vector<SoftPlanes> planes = soft_planes(geo);
+  // One slab saves e_d; the terms of several are formed from CA itself, p_d =
+  // 2^{-CA w - log2 sum e} in one rounding of the exponent, as they are when the
+  // planes are computed again.
+  geo.ca = planes[0].nds < geo.D;
+  int rc = STEREO_ENOMEM;
+  for (const SoftPlanes& z : planes) {
+    rc = make_soft_plan_evicting(c, geo, z, s, &pl);
+    if (rc != STEREO_ENOMEM) break;
   }
   if (rc) return rc;
+  c->err.clear();
   pl->last_use = ++c->tick;
   pl->owner = s;
   c->soft_plans.push_back(pl);

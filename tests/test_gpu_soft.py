@@ -520,3 +520,74 @@ def test_adjoint_terms_keep_their_unit_at_a_mantissa_of_ones():
         assert abs(a - S * 2.0**-25) <= 2.0**-22 * a, (S, a)
         exp = 2.0**-24 if S < 2**24 else 0.0
         assert abs(b - exp) <= 2.0**-40, (S, b, exp)
+
+
+# ------------------------------------------------------- scratch under a cap
+
+
+def device_bytes_free():
+    torch.cuda.synchronize()
+    return torch.cuda.mem_get_info()[0]
+
+
+class HeadCall:
+    """Device inputs of one call of the head, made before any memory is counted;
+    the outputs are torch's and stay in its cache."""
+
+    def __init__(self, n, W, H, dmax, seed, slab=0):
+        g = torch.Generator().manual_seed(seed)
+        self.left = torch.rand((n, H, W, 3), generator=g).to(DEV)
+        self.right = torch.rand((n, H, W, 3), generator=g).to(DEV)
+        self.g = torch.randn((n, (H + 1) // 2, (W + 1) // 2), generator=g).to(DEV)
+        self.lam = torch.tensor((10.0, 30.0), device=DEV)
+        self.dmax, self.slab = dmax, slab
+
+    def forward(self, ctx, flags=0):
+        d_hat, lse2 = ctx.soft_forward(self.left, self.right, self.lam, self.dmax,
+                                       soft_default_params(flags=flags, slab=self.slab))
+        return d_hat, lse2
+
+    def backward(self, ctx, d_hat, lse2, flags=0):
+        return ctx.soft_backward(self.left, self.right, self.lam, self.dmax, d_hat, lse2, self.g,
+                                 soft_default_params(flags=flags, slab=self.slab))
+
+    def step(self, ctx, save=True):
+        from paper_2212_00488_amd.binding import SOFT_F_REUSE_FEATURES, SOFT_F_SAVE_WEIGHTS
+        d_hat, lse2 = self.forward(ctx, SOFT_F_SAVE_WEIGHTS if save else 0)
+        out = (d_hat,) + self.backward(ctx, d_hat, lse2, SOFT_F_REUSE_FEATURES)
+        torch.cuda.synchronize()
+        return [t.cpu().numpy() for t in out]
+
+
+def taken_by(ctx, free0):
+    return free0 - device_bytes_free()
+
+
+def test_cap_frees_idle_plans_before_smaller_slabs():
+    """A cap that holds one plan of two shapes trained in turn: each call frees
+    the idle plan and runs its shape with the slabs of a context without a cap
+    (the scratch it takes, and every bit of its results), not with smaller ones
+    beside the idle plan."""
+    calls = [HeadCall(1, 640, 480, 64, 630), HeadCall(1, 620, 496, 64, 631)]
+    ref, alone = [], []
+    for h in calls:
+        for _ in range(2):  # the first time loads kernels
+            free0 = device_bytes_free()
+            c = Stereo(0)
+            r = h.step(c)
+            taken = taken_by(c, free0)
+            c.close()
+        ref.append(r)
+        alone.append(taken)
+    print(f"[soft] scratch of each shape alone: {alone}", flush=True)
+    assert min(alone) > 20 << 20
+    free0 = device_bytes_free()
+    c = Stereo(0, mem_cap=int(1.75 * max(alone)))
+    for k in (0, 1, 0, 1):
+        got = calls[k].step(c)
+        taken = taken_by(c, free0)
+        print(f"[soft] shape {k}: scratch {taken}", flush=True)
+        assert abs(taken - alone[k]) <= 4 << 20, (k, taken, alone)
+        for u, v in zip(got, ref[k]):
+            assert np.array_equal(u, v)
+    c.close()
