@@ -249,9 +249,10 @@ typedef struct stereo_soft_params {
  * SAVE_WEIGHTS, for stereo_soft_forward: keep the softmax weight, or the
  * aggregate, of every pixel and disparity (n * X * Y * D floats of the
  * context's scratch; ignored when a slab is given that does not hold all D,
- * or the scratch or 4 GiB do not) for a following backward with REUSE_FEATURES.  Any later forward or
- * backward with other inputs on the same context, stream and parameters
- * replaces or drops them. */
+ * or the scratch or 4 GiB do not) for a following backward with
+ * REUSE_FEATURES.  Any later forward or backward with other inputs on the same
+ * context, stream and parameters replaces or drops them, and a call on the
+ * context that needs their scratch may drop those beyond a slab. */
 #define STEREO_SOFT_F_REUSE_FEATURES 1u
 #define STEREO_SOFT_F_SAVE_WEIGHTS 2u
 
@@ -272,9 +273,10 @@ int stereo_soft_forward(stereo_ctx* ctx, const float* left, const float* right, 
  * inputs.  The adjoint takes the aggregate that the forward saved, or computes
  * it again, and runs the window sums backward over slabs of disparities
  * (difference arrays and prefix sums over the frozen arms); no cost volume is
- * stored.  Scratch: n * X * Y * 4 bytes per disparity, and as much again per
- * disparity of a slab; where that does not fit, the planes shrink to a slab's
- * and then the slabs. */
+ * stored.  Scratch: 2 n * X * Y * 4 bytes per disparity of a slab (1 GiB at
+ * most with an automatic slab, smaller slabs where that does not fit), and
+ * n * X * Y * 4 per further disparity once a forward saves its weights or a
+ * backward runs, where there is room. */
 int stereo_soft_backward(stereo_ctx* ctx, const float* left, const float* right, int n, int W,
                          int H, int Dmax, const float* lambdas, const stereo_soft_params* params,
                          const float* d_hat, const float* lse2, const float* g_dhat,

@@ -16,6 +16,10 @@ namespace stereo_host {
 struct Plan;      // plan of the integer path, per (W, H, Dmax, params)
 struct SoftPlan;  // plan of the soft-argmin head, per (n, W, H, Dmax, params)
 void free_soft_plans(std::vector<SoftPlan*>& plans);
+// Scratch of the soft head that only saves it work: the bytes that could be given
+// back, and giving back one plan's (false when there is none).
+size_t soft_optional_bytes(const stereo_ctx* c);
+bool drop_soft_optional(stereo_ctx* c);
 }  // namespace stereo_host
 
 namespace stereo_host {

@@ -17,8 +17,8 @@ using namespace stereo_dev;
 namespace stereo_host {
 
 constexpr int kSoftMaxPairs = 64;
-// The weight and dL/dCA_x planes of a plan: at most this many bytes each, so
-// that 32-bit offsets reach every weight (k_soft_tcolw).
+// The weight planes of all disparities of a plan and its dL/dCA_x planes: at most
+// this many bytes each, so that 32-bit offsets reach every weight (k_soft_tcolw).
 constexpr size_t kPlanesMost = (size_t(1) << 32) - 1;
 // A slab's weight and dL/dCA_x planes, where the caller sets no slab.
 constexpr size_t kSlabBudget = size_t(1) << 30;
@@ -31,8 +31,7 @@ struct SoftPlan {
   int XS = 0, pads = 0, XA = 0;
   int XW = 0;          // row pitch of the weight and dL/dCA_x planes: whole 128-byte lines
   int fxk = 18;        // fixed-point bits of the costs
-  int nw = 1;          // disparities the weight planes hold: all D, or a slab's
-  int nds = 1;         // disparities per backward slab
+  int nds = 1;         // disparities per backward slab, and of the plan's own weight planes
   bool ca = false;     // a forward saves CA, not e_d (several slabs)
   size_t lam_count = 0;
   size_t bytes = 0;
@@ -44,7 +43,15 @@ struct SoftPlan {
   float* inv_size = nullptr;   // [n][Y][X]
   float2* part = nullptr;      // [n][nchunk][Y][X]
   float4* pc = nullptr;        // [n][Y][X]
-  float* wts = nullptr;        // [nw][n][Y][XW] e_d or CA
+  float* wts = nullptr;        // [nds][n][Y][XW] e_d or CA
+  // The weight planes of the disparities from nds on, an allocation of their own:
+  // made by the first call that uses them (a forward that saves its weights, a
+  // backward) where the scratch has room, and given back when it is wanted for
+  // something else; without them a backward computes CA again, slab by slab.
+  float* rest = nullptr;       // [D - nds][n][Y][XW]
+  size_t rest_bytes = 0;       // of rest while it is there
+  bool rest_captured = false;  // a captured graph uses rest: never given back
+  uint64_t rest_retry = 0;     // after a failed allocation: not tried before this tick
   float* gcax = nullptr;       // [nds][n][Y][XW] dL/dCA_x
   float* gr_part = nullptr;    // [n][nstrips][Y][WP] right-gradient partials of a slab
   int WP = 0;                  // 64 + nds - 1 columns per partial row
@@ -54,13 +61,13 @@ struct SoftPlan {
   const float* feat_left = nullptr;
   const float* feat_right = nullptr;
   // inputs of the last forward, when it saved its weights e_d in the weight
-  // planes (STEREO_SOFT_F_SAVE_WEIGHTS, planes of all D); any other forward,
-  // and a backward that recomputes the weights, clears wts_valid
+  // planes (STEREO_SOFT_F_SAVE_WEIGHTS, planes of all D); any other forward, a
+  // backward that recomputes the weights and the loss of rest clear wts_valid
   bool wts_valid = false;
   const float* wts_left = nullptr;
   const float* wts_right = nullptr;
   const float* wts_lam = nullptr;
-  uint64_t last_use = 0;
+  uint64_t last_use = 0, prev_use = 0;  // ticks of the last two calls
   hipStream_t owner = nullptr; // the stream the plan serves (plans are never shared
                                // between streams, so calls on two streams may overlap)
 };
@@ -68,6 +75,7 @@ struct SoftPlan {
 void free_soft_plans(std::vector<SoftPlan*>& plans) {
   for (SoftPlan* pl : plans) {
     if (pl->block) (void)hipFree(pl->block);
+    if (pl->rest) (void)hipFree(pl->rest);
     delete pl;
   }
   plans.clear();
@@ -106,8 +114,7 @@ int soft_checks(stereo_ctx* c, int n, int W, int H, int Dmax, const stereo_soft_
   return 0;
 }
 
-// Shape and launch geometry of a plan (host side only), for weight planes of nw
-// disparities and backward slabs of nds.
+// Shape and launch geometry of a plan (host side only).
 void soft_geometry(SoftPlan& pl, int num_cu) {
   const stereo_soft_params& p = pl.p;
   pl.X = (pl.W + 1) / 2; pl.Y = (pl.H + 1) / 2; pl.D = (pl.Dmax + 1) / 2;
@@ -142,47 +149,43 @@ void soft_geometry(SoftPlan& pl, int num_cu) {
   pl.nchunk = (D + pl.csize - 1) / pl.csize;
 }
 
-// Device bytes of a plan with weight planes of nw disparities and slabs of nds.
-size_t soft_bytes(const SoftPlan& pl, int nw, int nds) {
+// Device bytes of a plan with weight planes and slabs of nds disparities.
+size_t soft_bytes(const SoftPlan& pl, int nds) {
   auto al = [](size_t b) { return (b + 255) & ~size_t(255); };
   const size_t n = pl.n, nimg = 2 * n, Y = pl.Y, npix = (size_t)pl.X * Y, nplane = (size_t)pl.XW * Y;
   const size_t nslab = (pl.D + nds - 1) / nds;
   return al(nimg * npix * 4) + al(nimg * npix) + al(nimg * Y * pl.XA * 4) +
          al(nimg * Y * pl.XS * 8) + al(n * npix * 4) + al(n * pl.nchunk * npix * 8) +
-         al(n * npix * 16) + al(nw * n * nplane * 4) + al(nds * n * nplane * 4) +
+         al(n * npix * 16) + 2 * al(nds * n * nplane * 4) +
          al(nimg * npix * 4) + al(nslab * n * pl.nstrips * ((Y + kTrRows - 1) / kTrRows) * 8) +
          al(n * pl.nstrips * Y * (64 + nds - 1) * 4);
 }
 
-// Disparities that a plan's weight planes (nw) and a backward slab (nds) hold.
-struct SoftPlanes {
-  int nw, nds;
-};
+// Whether the weight planes may hold all disparities: the caller sets no slab and
+// every weight can be addressed.
+bool all_weights_allowed(const SoftPlan& pl) {
+  return pl.p.slab == 0 && (size_t)pl.D * pl.n * pl.XW * pl.Y * 4 <= kPlanesMost;
+}
 
-// The planes of a plan, the preferred ones first: the slab of kSlabBudget, or the
-// caller's (at most 128 disparities: k_soft_tr's LDS rows of right gradients), and
-// weight planes of all D when they can be addressed and the caller sets no slab:
-// the backward then computes no CA again.  The others, for where the cap or the
-// device does not hold the scratch: the weights of a slab, then smaller slabs.
-std::vector<SoftPlanes> soft_planes(const SoftPlan& pl) {
+// The slabs of a plan, the preferred one first: that of kSlabBudget, or the
+// caller's (at most 128 disparities: k_soft_tr's LDS rows of right gradients).
+// The others, half as large each, for where the cap or the device does not hold
+// the scratch.
+std::vector<int> soft_slabs(const SoftPlan& pl) {
   const size_t npix = (size_t)pl.X * pl.Y, nplane = (size_t)pl.XW * pl.Y, n = pl.n;
   const int D = pl.D, slab = pl.p.slab;
   const size_t budget = std::max<size_t>(1, kSlabBudget / (2 * n * npix * 4));
   int nds = std::min(slab > 0 ? std::min(slab, D) : (int)std::min<size_t>(D, budget), kTrMaxWP - 63);
   nds = (int)std::max<size_t>(1, std::min<size_t>(nds, kPlanesMost / (n * nplane * 4)));
-  std::vector<SoftPlanes> v;
-  if (slab == 0 && nds < D && (size_t)D * n * nplane * 4 <= kPlanesMost) v.push_back({D, nds});
-  for (;; nds = (nds + 1) / 2) {
-    v.push_back({nds, nds});
-    if (nds == 1) return v;
-  }
+  std::vector<int> v{nds};
+  while (v.back() > 1) v.push_back((v.back() + 1) / 2);
+  return v;
 }
 
-// A plan of the geometry geo with the planes z: its device memory, and its set-up
+// A plan of the geometry geo with slabs of nds: its device memory, and its set-up
 // enqueued on s.
-int make_soft_plan(stereo_ctx* c, const SoftPlan& geo, const SoftPlanes& z, hipStream_t s,
-                   SoftPlan** out) {
-  const size_t bytes = soft_bytes(geo, z.nw, z.nds);
+int make_soft_plan(stereo_ctx* c, const SoftPlan& geo, int nds, hipStream_t s, SoftPlan** out) {
+  const size_t bytes = soft_bytes(geo, nds);
   if (c->mem_cap && c->used + bytes > c->mem_cap)
     return fail(c, STEREO_ENOMEM, "soft plan needs %zu bytes, cap %zu, in use %zu", bytes,
                 c->mem_cap, c->used);
@@ -196,10 +199,9 @@ int make_soft_plan(stereo_ctx* c, const SoftPlan& geo, const SoftPlanes& z, hipS
   const int n = pl->n, Y = pl->Y, D = pl->D;
   const size_t npix = (size_t)pl->X * Y, nplane = (size_t)pl->XW * Y, nimg = 2 * (size_t)n;
   pl->block = block;
-  pl->nw = z.nw;
-  pl->nds = z.nds;
-  pl->WP = 64 + z.nds - 1;
-  pl->lam_count = (size_t)((D + z.nds - 1) / z.nds) * n * pl->nstrips * ((Y + kTrRows - 1) / kTrRows);
+  pl->nds = nds;
+  pl->WP = 64 + nds - 1;
+  pl->lam_count = (size_t)((D + nds - 1) / nds) * n * pl->nstrips * ((Y + kTrRows - 1) / kTrRows);
   pl->bytes = bytes;
   char* cur = static_cast<char*>(pl->block);
   pl->half_f = carve<float>(cur, nimg * npix);
@@ -209,8 +211,8 @@ int make_soft_plan(stereo_ctx* c, const SoftPlan& geo, const SoftPlanes& z, hipS
   pl->inv_size = carve<float>(cur, n * npix);
   pl->part = carve<float2>(cur, (size_t)n * pl->nchunk * npix);
   pl->pc = carve<float4>(cur, n * npix);
-  pl->wts = carve<float>(cur, (size_t)z.nw * n * nplane);
-  pl->gcax = carve<float>(cur, (size_t)z.nds * n * nplane);
+  pl->wts = carve<float>(cur, (size_t)nds * n * nplane);
+  pl->gcax = carve<float>(cur, (size_t)nds * n * nplane);
   pl->g_half = carve<float>(cur, nimg * npix);
   pl->lam_part = carve<float2>(cur, pl->lam_count);
   pl->gr_part = carve<float>(cur, (size_t)n * pl->nstrips * Y * pl->WP);
@@ -231,6 +233,73 @@ int make_soft_plan(stereo_ctx* c, const SoftPlan& geo, const SoftPlanes& z, hipS
   return 0;
 }
 
+// Gives back the further weight planes of a plan (after the device has finished
+// with them).
+void drop_rest(stereo_ctx* c, SoftPlan& pl) {
+  (void)hipDeviceSynchronize();
+  (void)hipFree(pl.rest);
+  c->used -= pl.rest_bytes;
+  pl.rest = nullptr;
+  pl.rest_bytes = 0;
+  pl.wts_valid = false;
+}
+
+// Gives back the further weight planes of the least recently used plan that has
+// some and was last used before the tick; false when there is none.
+bool drop_one_rest(stereo_ctx* c, uint64_t before) {
+  SoftPlan* lru = nullptr;
+  for (SoftPlan* pl : c->soft_plans)
+    if (pl->rest && !pl->rest_captured && pl->last_use < before &&
+        (!lru || pl->last_use < lru->last_use))
+      lru = pl;
+  if (lru) drop_rest(c, *lru);
+  return lru != nullptr;
+}
+
+size_t soft_optional_bytes(const stereo_ctx* c) {
+  size_t b = 0;
+  for (const SoftPlan* pl : c->soft_plans)
+    if (!pl->rest_captured) b += pl->rest_bytes;
+  return b;
+}
+
+bool drop_soft_optional(stereo_ctx* c) { return drop_one_rest(c, UINT64_MAX); }
+
+// Whether the plan's weight planes hold all D disparities, for a call on s that
+// would use them: those beyond a slab are allocated now if need be, where the
+// scratch has room with the further planes given back of the plans not used
+// since the tick `idle` (two shapes in turn do not take them from each other in
+// every call).  Nothing is allocated while s is captured.
+bool hold_all_weights(stereo_ctx* c, SoftPlan& pl, uint64_t idle, hipStream_t s) {
+  if (pl.nds >= pl.D) return true;
+  if (!pl.rest && (!all_weights_allowed(pl) || c->tick < pl.rest_retry)) return false;
+  hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+  const bool capturing =
+      hipStreamIsCapturing(s, &cs) == hipSuccess && cs != hipStreamCaptureStatusNone;
+  (void)hipGetLastError();
+  if (pl.rest) {
+    pl.rest_captured |= capturing;
+    return true;
+  }
+  if (capturing) return false;
+  const size_t bytes = (size_t)(pl.D - pl.nds) * pl.n * pl.XW * pl.Y * 4;
+  bool failed = false;
+  do {
+    if (c->mem_cap && c->used + bytes > c->mem_cap) continue;
+    void* block = nullptr;
+    failed = hipMalloc(&block, bytes) != hipSuccess;
+    if (!failed) {
+      pl.rest = static_cast<float*>(block);
+      pl.rest_bytes = bytes;
+      c->used += bytes;
+      return true;
+    }
+    (void)hipGetLastError();
+  } while (drop_one_rest(c, idle));
+  if (failed) pl.rest_retry = c->tick + 64;
+  return false;
+}
+
 // Gives up the least recently used soft plan (after the device has finished with
 // it); false when there is none.
 bool evict_one_soft(stereo_ctx* c) {
@@ -240,23 +309,25 @@ bool evict_one_soft(stereo_ctx* c) {
   std::vector<SoftPlan*> one{*lru};
   c->soft_plans.erase(lru);
   (void)hipDeviceSynchronize();
-  c->used -= one[0]->bytes;
+  c->used -= one[0]->bytes + one[0]->rest_bytes;
   free_soft_plans(one);
   return true;
 }
 
-// make_soft_plan, with other soft plans given up while the scratch does not hold
-// it.  A cap that would not hold it with all of them gone is left as it is.
-int make_soft_plan_evicting(stereo_ctx* c, const SoftPlan& geo, const SoftPlanes& z, hipStream_t s,
+// make_soft_plan, with the further weight planes of other soft plans given back,
+// then those plans given up, while the scratch does not hold it.  A cap that
+// would not hold it with all of them gone is left as it is.
+int make_soft_plan_evicting(stereo_ctx* c, const SoftPlan& geo, int nds, hipStream_t s,
                             SoftPlan** out) {
-  const size_t bytes = soft_bytes(geo, z.nw, z.nds);
+  const size_t bytes = soft_bytes(geo, nds);
   size_t kept = c->used;
-  for (const SoftPlan* pl : c->soft_plans) kept -= pl->bytes;
+  for (const SoftPlan* pl : c->soft_plans) kept -= pl->bytes + pl->rest_bytes;
   if (c->mem_cap && kept + bytes > c->mem_cap)
     return fail(c, STEREO_ENOMEM, "soft plan needs %zu bytes, cap %zu, in use %zu", bytes,
                 c->mem_cap, c->used);
-  int rc = make_soft_plan(c, geo, z, s, out);
-  while (rc == STEREO_ENOMEM && evict_one_soft(c)) rc = make_soft_plan(c, geo, z, s, out);
+  int rc = make_soft_plan(c, geo, nds, s, out);
+  while (rc == STEREO_ENOMEM && (drop_soft_optional(c) || evict_one_soft(c)))
+    rc = make_soft_plan(c, geo, nds, s, out);
   return rc;
 }
 
@@ -265,6 +336,7 @@ int get_soft_plan(stereo_ctx* c, int n, int W, int H, int Dmax, const stereo_sof
   for (SoftPlan* pl : c->soft_plans)
     if (pl->n == n && pl->W == W && pl->H == H && pl->Dmax == Dmax && pl->owner == s &&
         same_soft(pl->p, p)) {
+      pl->prev_use = pl->last_use;
       pl->last_use = ++c->tick;
       *out = pl;
       return 0;
@@ -278,14 +350,14 @@ int get_soft_plan(stereo_ctx* c, int n, int W, int H, int Dmax, const stereo_sof
   if (rows * geo.XS * 8 >= (size_t(1) << 32) || rows * geo.XA * 4 >= (size_t(1) << 32))
     return fail(c, STEREO_EINVAL, "%d pairs of %dx%d exceed the 4 GiB pixel or arm planes of the "
                 "soft head; pass fewer pairs per call", n, W, H);
-  const std::vector<SoftPlanes> planes = soft_planes(geo);
+  const std::vector<int> slabs = soft_slabs(geo);
   // One slab saves e_d; the terms of several are formed from CA itself, p_d =
   // 2^{-CA w - log2 sum e} in one rounding of the exponent, as they are when the
   // planes are computed again.
-  geo.ca = planes[0].nds < geo.D;
+  geo.ca = slabs[0] < geo.D;
   int rc = STEREO_ENOMEM;
-  for (const SoftPlanes& z : planes) {
-    rc = make_soft_plan_evicting(c, geo, z, s, &pl);
+  for (int nds : slabs) {
+    rc = make_soft_plan_evicting(c, geo, nds, s, &pl);
     if (rc != STEREO_ENOMEM) break;
   }
   if (rc) return rc;
@@ -328,6 +400,16 @@ SoftArgs soft_args(const SoftPlan& pl, const float* lambdas, int dlo, int dhi, i
   a.sp_bytes = (uint32_t)((size_t)2 * pl.n * pl.Y * pl.XS * 8);
   a.arms_bytes = (uint32_t)((size_t)2 * pl.n * pl.Y * pl.XA * 4);
   return a;
+}
+
+// k_soft_agg's weights of all disparities, in the plan's own planes and the rest.
+void all_weights(const SoftPlan& pl, SoftArgs& a) {
+  a.wts = pl.wts;
+  // plane 0 of the rest is disparity nds
+  a.wts2 = reinterpret_cast<float*>(reinterpret_cast<uintptr_t>(pl.rest) -
+                                    (size_t)pl.nds * pl.n * pl.XW * pl.Y * sizeof(float));
+  a.wlo = 0;
+  a.wsplit = pl.nds;
 }
 
 // Most rows of a k_soft_agg band: the first and the last band have one halo.
@@ -441,9 +523,10 @@ int stereo_soft_forward(stereo_ctx* c, const float* left, const float* right, in
   SoftArgs a = soft_args(*pl, lambdas, 0, pl->D, pl->csize);
   a.part = pl->part;
   a.ca = pl->ca;
-  pl->wts_valid = (flags & STEREO_SOFT_F_SAVE_WEIGHTS) && pl->nw >= pl->D;
+  pl->wts_valid = (flags & STEREO_SOFT_F_SAVE_WEIGHTS) &&
+                  hold_all_weights(c, *pl, pl->prev_use, stream);
   if (pl->wts_valid) {
-    a.wts = pl->wts;
+    all_weights(*pl, a);
     pl->wts_left = left;
     pl->wts_right = right;
     pl->wts_lam = lambdas;
@@ -481,13 +564,19 @@ int stereo_soft_backward(stereo_ctx* c, const float* left, const float* right, i
   const int groups = pl->nstrips * pl->nbands * pl->n;
   const int tb = tcol_band(pl->p.arm_y);
   const int base = pl->nstrips * ((Y + tb - 1) / tb) * pl->n;
-  const bool whole = pl->nw >= pl->D;  // weight planes of all D: computed once
+  // weight planes of all D: computed once (no other plan's are given back for it)
+  const bool whole = hold_all_weights(c, *pl, 0, stream);
   if (!saved) pl->wts_valid = false;  // the planes are overwritten below
   auto weights = [&](int dlo, int dhi) {
     SoftArgs a = soft_args(*pl, lambdas, dlo, dhi,
                            best_chunk_size(groups, dhi - dlo, pl->rows, c->num_cu, dhi - dlo));
-    a.wts = pl->wts;
-    a.wlo = dlo;
+    if (whole) {
+      all_weights(*pl, a);
+    } else {
+      a.wts = pl->wts;
+      a.wlo = dlo;
+      a.wsplit = dhi;
+    }
     a.ca = 1;
     launch_soft_agg(*pl, a, stream);
   };
@@ -498,10 +587,12 @@ int stereo_soft_backward(stereo_ctx* c, const float* left, const float* right, i
     const int dhi = std::min(pl->D, dlo + pl->nds);
     if (!saved && !whole) weights(dlo, dhi);
     TcwArgs tc{};
-    tc.wts = pl->wts; tc.pc = pl->pc; tc.arms = pl->arms; tc.gcax = pl->gcax;
-    tc.wts_bytes = (uint32_t)((size_t)pl->nw * pl->n * pl->XW * Y * 4);
+    const bool further = whole && dlo > 0;  // this slab's weights are in the rest
+    tc.wts = further ? pl->rest : pl->wts; tc.wlo = further ? pl->nds : dlo;
+    tc.wts_bytes = (uint32_t)(further ? pl->rest_bytes : (size_t)pl->nds * pl->n * pl->XW * Y * 4);
+    tc.pc = pl->pc; tc.arms = pl->arms; tc.gcax = pl->gcax;
     tc.X = X; tc.Y = Y; tc.XA = pl->XA; tc.XW = pl->XW; tc.arm_y = pl->p.arm_y; tc.npair = pl->n;
-    tc.dlo = dlo; tc.dhi = dhi; tc.wlo = whole ? 0 : dlo;
+    tc.dlo = dlo; tc.dhi = dhi;
     // disparity groups so that the grid fills the CUs about three blocks deep
     // (each group reloads the per-pixel constants: at 4 x 718x496, 4 groups
     // ran faster than 3 or 6)

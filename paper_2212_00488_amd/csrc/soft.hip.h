@@ -174,10 +174,11 @@ struct SoftArgs {
   const float* lam;         // device [2]: lambda_AD, lambda_census
   const float* inv_size;    // [n][Y][X]
   float2* part;             // [n][nchunk][Y][X] {sum e, sum d e}, or NULL
-  float* wts;               // [..][n][Y][X] e_d, plane 0 = disparity wlo, or NULL
-  int ca;                   // wts takes CA in place of e_d
+  float* wts;               // [..][n][Y][XW] e_d, plane 0 = disparity wlo, or NULL
+  float* wts2;              // the same, for the disparities from wsplit on
+  int ca;                   // wts and wts2 take CA in place of e_d
   int X, Y, XS, pads, XA, XW, arm_x, arm_y;
-  int nbands, dlo, dhi, wlo, nstrips, ngroups, npair;
+  int nbands, dlo, dhi, wlo, wsplit, nstrips, ngroups, npair;
   int csize, nchunk;        // d-chunk size; chunks = ceil((dhi - dlo) / csize), the last the remainder
   float fx;                 // fixed-point scale 2^k of the costs
   float zc;                 // 2^-k log2(e) / tau: CA_int * inv_size * zc = mean / tau in log2 units
@@ -395,7 +396,8 @@ __global__ void __launch_bounds__(kThreads) k_soft_agg(SoftArgs a) {
     uint32_t kpermM = 0x020c000cu;
     __asm__ volatile("" : "+v"(kpermM));
     // rows of the weight plane of d
-    float* wd = a.wts ? a.wts + (((size_t)(d - a.wlo) * a.npair + pair) * Y + ya + o0 + wave) * a.XW + x0
+    float* wd = a.wts ? (d < a.wsplit ? a.wts : a.wts2) +
+                            (((size_t)(d - a.wlo) * a.npair + pair) * Y + ya + o0 + wave) * a.XW + x0
                       : nullptr;
     if (x < X) {
       uint32_t wh[2][kWinGroup][2], wl[2][kWinGroup][2];

@@ -493,18 +493,19 @@ bool evict_one(stereo_ctx* c) {
   return true;
 }
 
-// make_plan, with idle plans given up while the scratch does not hold it.  A cap
-// that would not hold it with all of them gone is left as it is.
+// make_plan, with the soft head's optional planes given back, then idle plans
+// given up, while the scratch does not hold it.  A cap that would not hold it
+// with all of them gone is left as it is.
 int make_plan_evicting(stereo_ctx* c, const Plan& geo, hipStream_t s, Plan** out) {
   const size_t bytes = plan_bytes(geo).total;
-  size_t kept = c->used;
+  size_t kept = c->used - soft_optional_bytes(c);
   for (const Plan* pl : c->plans)
     if (evictable(c, pl)) kept -= pl->bytes;
   if (c->mem_cap && kept + bytes > c->mem_cap)
     return fail(c, STEREO_ENOMEM, "plan needs %zu bytes, cap %zu, in use %zu", bytes, c->mem_cap,
                 c->used);
   int rc = make_plan(c, geo, s, out);
-  while (rc == STEREO_ENOMEM && evict_one(c)) rc = make_plan(c, geo, s, out);
+  while (rc == STEREO_ENOMEM && (drop_soft_optional(c) || evict_one(c))) rc = make_plan(c, geo, s, out);
   return rc;
 }
 

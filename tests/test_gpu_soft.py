@@ -591,3 +591,104 @@ def test_cap_frees_idle_plans_before_smaller_slabs():
         for u, v in zip(got, ref[k]):
             assert np.array_equal(u, v)
     c.close()
+
+
+def test_weight_planes_of_all_disparities_only_for_a_backward():
+    """4 x 1920x1080, 128 disparities: a forward that saves nothing takes the
+    slab's planes only (at most 1 GiB beside the pixel planes); the first one that
+    saves its weights adds the planes of the other disparities."""
+    from paper_2212_00488_amd.binding import SOFT_F_SAVE_WEIGHTS
+    h = HeadCall(4, 1920, 1080, 256, 632)
+    c = Stereo(0)
+    h.forward(c)  # kernels, and the outputs' memory in torch's cache
+    c.close()
+    free0 = device_bytes_free()
+    c = Stereo(0)
+    h.forward(c)
+    plain = taken_by(c, free0)
+    h.forward(c, SOFT_F_SAVE_WEIGHTS)
+    saving = taken_by(c, free0)
+    c.close()
+    print(f"[soft] scratch without saving {plain}, with {saving}", flush=True)
+    plane = 4 * 540 * 960 * 4  # of one disparity
+    assert plain <= (1 << 30) + 60 * plane // 2, plain
+    assert saving >= plain + 32 * plane, (plain, saving)
+
+
+def test_optional_weight_planes_give_way():
+    """256 disparities (two slabs), two shapes under a cap that holds both plans
+    and the further weight planes of one: these go to the shape in use, the other
+    one's once it has not been used since; a pair of the integer path that needs
+    their room gets it; and the gradients are the same bits throughout."""
+    calls = [HeadCall(1, 1100, 400, 512, 640), HeadCall(1, 1090, 404, 512, 641)]
+    ref, base, full = [], [], []
+    for h in calls:
+        for _ in range(2):
+            free0 = device_bytes_free()
+            c = Stereo(0)
+            h.forward(c)
+            b = taken_by(c, free0)
+            r = h.step(c)
+            f = taken_by(c, free0)
+            c.close()
+        ref.append(r)
+        base.append(b)
+        full.append(f)
+    print(f"[soft] plan {base}, with the weights of all disparities {full}", flush=True)
+    rest = min(f - b for f, b in zip(full, base))
+    assert rest >= 40 << 20
+    free0 = device_bytes_free()
+    c = Stereo(0, mem_cap=sum(base) + rest + (16 << 20))
+    # (shape, who holds the further planes after the step)
+    for k, owner in ((0, 0), (1, 0), (1, 1), (0, 1), (1, 1), (0, 1), (0, 0)):
+        got = calls[k].step(c)
+        taken = taken_by(c, free0)
+        other = full[owner] + (base[1 - owner] if taken > full[owner] + (8 << 20) else 0)
+        print(f"[soft] shape {k}: scratch {taken}", flush=True)
+        assert abs(taken - other) <= 8 << 20, (k, owner, taken, base, full)
+        for u, v in zip(got, ref[k]):
+            assert np.array_equal(u, v)
+    # the integer path takes their room, not STEREO_ENOMEM
+    g = torch.Generator().manual_seed(9)
+    lt = torch.randint(0, 256, (992, 1436, 3), dtype=torch.uint8, generator=g).to(DEV)
+    big = c.disparity(lt, lt, 145)
+    torch.cuda.synchronize()
+    alone = Stereo(0)
+    assert torch.equal(big, alone.disparity(lt, lt, 145))
+    alone.close()
+    for u, v in zip(calls[0].step(c), ref[0]):
+        assert np.array_equal(u, v)
+    c.close()
+
+
+def test_training_step_captured_after_a_plain_forward():
+    """A plan whose calls saved nothing so far, then forward with saving and
+    backward captured in a graph (where nothing can be allocated): each replay
+    gives the eager gradients, with one slab and with two."""
+    from paper_2212_00488_amd.binding import SOFT_F_REUSE_FEATURES, SOFT_F_SAVE_WEIGHTS
+    for W, H, dmax, seed in ((96, 40, 32, 650), (290, 20, 270, 651)):
+        print(f"[soft] captured step {W}x{H} Dmax={dmax}", flush=True)
+        h = HeadCall(1, W, H, dmax, seed)
+        c, s = Stereo(0), torch.cuda.Stream()
+        ref = h.step(c, save=False)
+        with torch.cuda.stream(s):
+            h.forward(c)
+        torch.cuda.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=s):
+            d_hat, lse2 = h.forward(c, SOFT_F_SAVE_WEIGHTS)
+            out = (d_hat,) + h.backward(c, d_hat, lse2, SOFT_F_REUSE_FEATURES)
+        for k in range(3):
+            for t in out:
+                t.zero_()
+            torch.cuda.synchronize()
+            graph.replay()
+            torch.cuda.synchronize()
+            assert np.array_equal(out[0].cpu().numpy(), ref[0])
+            for t, r, nm in zip(out[1:], ref[1:], ("g_left", "g_right", "g_lambdas")):
+                t = t.cpu().numpy()
+                assert np.abs(t - r).max() <= 1e-5 * np.abs(r).max(), (k, nm)
+            h.step(c)  # eager work between the replays
+        del graph
+        torch.cuda.synchronize()
+        c.close()
