@@ -31,7 +31,7 @@ int best_chunk_size(int groups, int D, int rows, int num_cu, int cap);
 struct Tuned {
   int W, H, Dmax, npair;
   stereo_params p;
-  int csize;  // disparities per k_match d-chunk
+  int nchunk;  // d-chunks of k_match
 };
 }  // namespace stereo_host
 
@@ -47,7 +47,7 @@ struct stereo_ctx {
   std::string err;
   stereo_host::Plan* last = nullptr;  // plan of the last call that kept its intermediates
   uint64_t tick = 0;
-  std::vector<stereo_host::Tuned> tuned;  // d-chunk sizes chosen by stereo_autotune
+  std::vector<stereo_host::Tuned> tuned;  // d-chunk counts chosen by stereo_autotune
   // scratch of the L1 loss entry points, one block per stream
   std::vector<std::pair<hipStream_t, void*>> l1_blocks;
   // device address of this device's fixed scratch array (stereo_disparity_noalloc),

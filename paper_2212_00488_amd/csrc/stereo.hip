@@ -275,8 +275,9 @@ double match_time(const Plan& pl, const Bands& b, const MatchGrid& g, int nchunk
 // Launch geometry: bands keep the k_match LDS plane, the segment sums and the
 // key registers within bounds; d-chunks, and more bands than needed, raise
 // the workgroup count to fill the CUs.  nbase: 2 both bases a workgroup where
-// that is the better form, 1 one base.
-void plan_geometry(Plan& pl, int num_cu, int forced_csize, int nbase) {
+// that is the better form, 1 one base.  forced_nchunk: the number of chunks (at
+// least as many as the strips need), or 0 for the modelled one.
+void plan_geometry(Plan& pl, int num_cu, int forced_nchunk, int nbase) {
   const int arm = std::max(pl.p.arm_x, pl.p.arm_x_r), arm_y = pl.p.arm_y;
   // Both bases in one workgroup, with the fewest 128-column sub-passes that
   // leave their strips room for chunks of kMinChunk disparities, unless the
@@ -299,7 +300,7 @@ void plan_geometry(Plan& pl, int num_cu, int forced_csize, int nbase) {
     pl.ccap = cap_of(ns2);
   }
   // bands and d-chunks with the shortest modelled time (ties keep the fewer
-  // bands and the larger chunks), or the chunk size stereo_autotune chose
+  // bands and the larger chunks)
   double best_t = 1e300;
   constexpr int kMoreBands = 6;
   int nb = 1, best_nb = 1;
@@ -307,7 +308,7 @@ void plan_geometry(Plan& pl, int num_cu, int forced_csize, int nbase) {
     const Bands b = match_bands(pl.Y, arm_y, pl.ns, pl.nbase, nb);
     nb = pl.nbands = b.n;
     int n0 = (pl.D + pl.ccap - 1) / pl.ccap, n1 = std::min(pl.D, std::max(n0, 64));
-    if (forced_csize > 0) n0 = n1 = std::max(n0, (pl.D + forced_csize - 1) / forced_csize);
+    if (forced_nchunk > 0) n0 = n1 = std::max(n0, forced_nchunk);
     for (int n = n0; n <= n1; ++n) {
       const MatchGrid g = match_grid(pl, pl.npair, 0, pl.D, n);
       if (g.total > 16L * num_cu && best_t < 1e300) break;
@@ -333,11 +334,11 @@ void plan_geometry(Plan& pl, int num_cu, int forced_csize, int nbase) {
   pl.XA = (pl.X + kTX - 1) / kTX * kTX;
 }
 
-// The d-chunk size stereo_autotune chose for this shape and parameters, or 0.
-int tuned_csize(const stereo_ctx* c, int W, int H, int Dmax, int npair, const stereo_params& p) {
+// The number of d-chunks stereo_autotune chose for this shape and parameters, or 0.
+int tuned_nchunk(const stereo_ctx* c, int W, int H, int Dmax, int npair, const stereo_params& p) {
   for (const Tuned& t : c->tuned)
     if (t.W == W && t.H == H && t.Dmax == Dmax && t.npair == npair && same_params(t.p, p))
-      return t.csize;
+      return t.nchunk;
   return 0;
 }
 
@@ -387,7 +388,7 @@ int plan_setup(stereo_ctx* c, Plan& pl, int W, int H, int Dmax, const stereo_par
   build_tables(p, pl.lut_ad, pl.lut_mc);
   pl.cmax = pl.lut_ad[255] + pl.lut_mc[6];
   plan_geometry(pl, c->num_cu,
-                form.fewest_chunks ? pl.D : tuned_csize(c, W, H, Dmax, npair, p), form.nbase);
+                form.fewest_chunks ? 1 : tuned_nchunk(c, W, H, Dmax, npair, p), form.nbase);
   pl.nk = (int)(((size_t)pl.X * pl.Y + 63) & ~size_t(63));
   const PlanBytes b = plan_bytes(pl);
   if (b.pk >= (size_t(1) << 32) || b.arms >= (size_t(1) << 32))
@@ -581,13 +582,13 @@ int evict_shape(stereo_ctx* c, int W, int H, int Dmax, const stereo_params& p) {
 }
 
 void set_tuned(stereo_ctx* c, int W, int H, int Dmax, int npair, const stereo_params& p,
-               int csize) {
+               int nchunk) {
   for (Tuned& t : c->tuned)
     if (t.W == W && t.H == H && t.Dmax == Dmax && t.npair == npair && same_params(t.p, p)) {
-      t.csize = csize;
+      t.nchunk = nchunk;
       return;
     }
-  c->tuned.push_back(Tuned{W, H, Dmax, npair, p, csize});
+  c->tuned.push_back(Tuned{W, H, Dmax, npair, p, nchunk});
 }
 
 MatchArgs match_args(const Plan& pl, int npair, int dlo, int dhi, int nchunk) {
@@ -857,17 +858,20 @@ int stereo_autotune(stereo_ctx* c, const uint8_t* const* left, const uint8_t* co
   if (rc) return rc;
   p.flags &= ~(STEREO_F_KEEP_INTERMEDIATES | STEREO_F_STAGE_TIMING);
   HIP_TRY(c, hipSetDevice(c->device));
-  // the modelled default, then sizes ceil(D / k), k = 1 .. min(D, 32)
+  // the modelled default, then the sizes ceil(D / k), k = 1 .. min(D, 32), that the
+  // strips of both bases allow, each as the fewest chunks of that size
   Plan probe{};
   probe.W = W; probe.H = H; probe.Dmax = Dmax; probe.npair = m; probe.p = p;
   probe.X = full_res(p) ? W : (W + 1) / 2;
   probe.Y = full_res(p) ? H : (H + 1) / 2;
   probe.D = full_res(p) ? Dmax : (Dmax + 1) / 2;
   plan_geometry(probe, c->num_cu, 0, 2);
-  std::vector<int> cand{probe.csize};
+  std::vector<int> cand{probe.nchunk}, cand_size{probe.csize};
   for (int k = 1; k <= std::min(probe.D, 32); ++k) {
     const int cs = (probe.D + k - 1) / k;
-    if (std::find(cand.begin(), cand.end(), cs) == cand.end()) cand.push_back(cs);
+    if (cs > probe.ccap || std::find(cand_size.begin(), cand_size.end(), cs) != cand_size.end()) continue;
+    cand_size.push_back(cs);
+    cand.push_back((probe.D + cs - 1) / cs);
   }
   // scratch output maps for the trial runs
   int16_t* outs = nullptr;
@@ -879,7 +883,12 @@ int stereo_autotune(stereo_ctx* c, const uint8_t* const* left, const uint8_t* co
     pp.out[i] = outs + (size_t)i * W * H;
   }
   hipEvent_t e0 = nullptr, e1 = nullptr;
-  int best = probe.csize;
+  const int before = tuned_nchunk(c, W, H, Dmax, m, p);
+  // candidates that ran: where the scratch holds a smaller form only, several
+  // have the same launch, which is timed once
+  struct Trial { int nbase, ns, nbands, nchunk, csize; };
+  std::vector<Trial> ran;
+  int best = 0, best_size = 0;
   float best_ms = 1e30f;
   hipError_t he = hipEventCreate(&e0);
   if (he == hipSuccess) he = hipEventCreate(&e1);
@@ -888,7 +897,13 @@ int stereo_autotune(stereo_ctx* c, const uint8_t* const* left, const uint8_t* co
     rc = evict_shape(c, W, H, Dmax, p);
     Plan* pl = nullptr;
     if (!rc) rc = get_plan(c, W, H, Dmax, p, m, stream, stream, &pl);
-    if (!rc) rc = run(c, *pl, pp, m, false, false, stream);  // warm
+    if (rc) break;
+    const Trial now{pl->nbase, pl->ns, pl->nbands, pl->nchunk, pl->csize};
+    if (std::any_of(ran.begin(), ran.end(), [&](const Trial& t) {
+          return t.nbase == now.nbase && t.ns == now.ns && t.nbands == now.nbands && t.nchunk == now.nchunk;
+        }))
+      continue;
+    rc = run(c, *pl, pp, m, false, false, stream);  // warm
     constexpr int kReps = 5;
     if (!rc) he = hipEventRecord(e0, stream);
     for (int r = 0; r < kReps && !rc && he == hipSuccess; ++r) rc = run(c, *pl, pp, m, false, false, stream);
@@ -896,14 +911,17 @@ int stereo_autotune(stereo_ctx* c, const uint8_t* const* left, const uint8_t* co
     if (!rc && he == hipSuccess) he = hipEventSynchronize(e1);
     float ms = 0.f;
     if (!rc && he == hipSuccess) he = hipEventElapsedTime(&ms, e0, e1);
+    if (rc || he != hipSuccess) break;
     ms /= kReps;
-    if ((int)k < max_times) {
-      if (sizes) sizes[k] = cand[k];
-      if (times_ms) times_ms[k] = ms;
+    if ((int)ran.size() < max_times) {
+      if (sizes) sizes[ran.size()] = now.csize;
+      if (times_ms) times_ms[ran.size()] = ms;
     }
-    if (!rc && he == hipSuccess && ms < best_ms) {
+    ran.push_back(now);
+    if (ms < best_ms) {
       best_ms = ms;
       best = cand[k];
+      best_size = now.csize;
     }
   }
   if (e0) (void)hipEventDestroy(e0);
@@ -911,14 +929,17 @@ int stereo_autotune(stereo_ctx* c, const uint8_t* const* left, const uint8_t* co
   (void)hipDeviceSynchronize();
   (void)hipFree(outs);
   if (!rc && he != hipSuccess) rc = fail(c, STEREO_EHIP, "autotune: %s", hipGetErrorString(he));
-  set_tuned(c, W, H, Dmax, m, p, best);
+  // a call that failed leaves what was chosen before
+  set_tuned(c, W, H, Dmax, m, p, rc ? before : best);
+  const std::string err = c->err;
   const int rc2 = evict_shape(c, W, H, Dmax, p);
+  if (rc) c->err = err;
   if (rc) return rc;
   if (rc2) return rc2;
-  if (chosen) *chosen = best;
-  if (max_times > (int)cand.size()) {
-    if (sizes) sizes[cand.size()] = 0;
-    if (times_ms) times_ms[cand.size()] = -1.f;
+  if (chosen) *chosen = best_size;
+  if (max_times > (int)ran.size()) {
+    if (sizes) sizes[ran.size()] = 0;
+    if (times_ms) times_ms[ran.size()] = -1.f;
   }
   return 0;
 }

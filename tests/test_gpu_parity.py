@@ -671,3 +671,21 @@ def test_refused_shape_evicts_nothing(sm):
     torch.cuda.synchronize()
     assert_same("map", out.cpu().numpy(), exp)
     c.close()
+
+
+@pytest.mark.parametrize("W,H,dmax", [(300, 60, 145), (300, 200, 48), (40, 30, 12)])
+def test_autotune_times_each_launch_once(sm, W, H, dmax):
+    """The candidates are chunk sizes that a launch really has: at the default
+    caps at most 22 disparities (what the strips of both bases allow), each the
+    largest chunk of its chunk count, no chunk count twice."""
+    lt, rt = noise_pair(W, H, 830)
+    c = sm.Stereo(0)
+    chosen, cands = c.autotune([lt], [rt], dmax)
+    c.close()
+    D = (dmax + 1) // 2
+    say(f"{W}x{H} Dmax {dmax}: {cands}, chosen {chosen}")
+    assert chosen in cands and cands[chosen] == min(cands.values())
+    assert max(cands) <= 22
+    counts = [-(-D // s) for s in cands]
+    assert len(set(counts)) == len(counts), cands
+    assert all(-(-D // n) == s for n, s in zip(counts, cands)), cands
