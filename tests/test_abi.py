@@ -71,3 +71,22 @@ def test_intermediate_ids_match_header():
     for name, (which, _, _) in INTERMEDIATES.items():
         assert ids[name] == which, name
     assert ids["lut"] == I_LUT
+
+
+@pytest.mark.parametrize("raw", [True, False])
+def test_current_streams_handle_with_and_without_the_raw_call(monkeypatch, raw):
+    """The current stream's handle by torch's call for it, or from the Stream object
+    where torch has no such call; a given stream's own."""
+    torch = pytest.importorskip("torch")
+    from paper_2212_00488_amd import binding as b
+
+    class Stream:
+        cuda_stream = 0x1234
+
+    monkeypatch.setattr(torch.cuda, "current_device", lambda: 3)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda *a: Stream())
+    monkeypatch.setattr(torch._C, "_cuda_getCurrentRawStream", lambda d: 0x1000 + d, raising=False)
+    if not raw:
+        monkeypatch.delattr(torch._C, "_cuda_getCurrentRawStream")
+    assert b._stream_handle(None).value == (0x1003 if raw else 0x1234)
+    assert b._stream_handle(Stream()).value == 0x1234
