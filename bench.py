@@ -93,7 +93,7 @@ TRAFFIC_SOURCE_PARTS = (
     ("kernels.hip.h", None, "// ---------------------------------------------------------------- k_prep"),
     ("kernels.hip.h", "// ---------------------------------------------------------------- k_match",
      "// ----------------------------------------------------------------- k_wta"),
-    ("stereo.hip", "double match_makespan(", "// The number of d-chunks stereo_autotune chose"),
+    ("stereo.hip", "int match_kmax(", "// The number of d-chunks stereo_autotune chose"),
 )
 
 

@@ -23,10 +23,6 @@ bool drop_soft_optional(stereo_ctx* c);
 }  // namespace stereo_host
 
 namespace stereo_host {
-// d-chunk size (disparities, at most cap) for groups x D of work over band rows
-// of height rows, from the model of the per-XCD dispatch queues (stereo.hip).
-int best_chunk_size(int groups, int D, int rows, int num_cu, int cap);
-
 // A launch geometry chosen by stereo_autotune for one shape and parameter set.
 struct Tuned {
   int W, H, Dmax, npair;

@@ -28,39 +28,8 @@ constexpr int kWaves = 16;        // k_match workgroup = 16 waves
 constexpr int kThreads = kWaves * 64;
 constexpr int kLdsBytes = 163840; // LDS per workgroup on gfx950
 constexpr int kXcds = 8;          // accelerator complex dies, each with its own L2
-constexpr int kXcdQueues = 4;     // workgroup dispatch queues per XCD (position mod 4)
-
-// Position j of an XCD's workgroup sequence -> (local group, d-chunk), for
-// nloc groups of nchunk chunks each, nfull of them full-size and, when
-// nchunk > nfull, one shorter remainder chunk.  Workgroup j waits in the
-// XCD's dispatch queue j % kXcdQueues for a CU of that queue.  The remainder
-// chunks take the last positions of one queue, T-1, T-1-4, ... (T = nloc *
-// nchunk), so that the workgroups past the first round follow short ones
-// there; where that does not fit they simply come last.
-__device__ __forceinline__ void chunk_at(int j, int nloc, int nfull, int nchunk, int& local,
-                                         int& chunk) {
-  const int T = nloc * nchunk;
-  if (nchunk == nfull) {
-    local = j / nfull;
-    chunk = j - local * nfull;
-  } else if (kXcdQueues * (nloc - 1) > T - 1) {
-    local = j < nloc * nfull ? j / nfull : j - nloc * nfull;
-    chunk = j < nloc * nfull ? j - local * nfull : nfull;
-  } else {
-    const int q = T - 1 - j;  // remainder chunks at q = 0, 4, ..., 4 (nloc - 1)
-    if (q % kXcdQueues == 0 && q / kXcdQueues < nloc) {
-      local = nloc - 1 - q / kXcdQueues;
-      chunk = nfull;
-    } else {
-      const int i = j - max(0, nloc - (q / kXcdQueues + 1));  // full chunks before j
-      local = i / nfull;
-      chunk = i - local * nfull;
-    }
-  }
-}
 constexpr int kWinGroup = 2;      // k_match slot pairs whose window reads go together
 constexpr int kRowBatch = 2;      // k_match rows whose lookups and scans interleave
-
 
 __device__ __forceinline__ int iabs(int v) { return v < 0 ? -v : v; }
 __device__ __forceinline__ int clampi(int v, int lo, int hi) { return v < lo ? lo : (v > hi ? hi : v); }

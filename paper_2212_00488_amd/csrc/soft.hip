@@ -114,6 +114,74 @@ int soft_checks(stereo_ctx* c, int n, int W, int H, int Dmax, const stereo_soft_
   return 0;
 }
 
+// Modelled k_soft_agg time, in units of one disparity of one workgroup, for
+// d-chunks of cs disparities: each XCD's workgroups, in order of their positions
+// (chunk_at), go to dispatch queue (position % kXcdQueues), where each takes
+// the CU of that queue that frees first; a workgroup costs its disparities
+// plus ovh units of set-up and drain (arms, |S|, chunk sums).  The queue
+// structure (4 queues of 8 CUs per XCD, filled in turn) is what timings of such
+// placements showed on a kernel of this layout: a workgroup past the first round
+// waits for a CU of its own queue, not for the first CU to free.
+double agg_makespan(int groups, int D, int cs, int cus_per_xcd, double ovh) {
+  const int nfull = D / cs, rem = D - nfull * cs, nchunk = nfull + (rem > 0);
+  const int nloc = (groups + kXcds - 1) / kXcds, T = nloc * nchunk;
+  const int per_q = std::max(1, cus_per_xcd / kXcdQueues);
+  const bool stacked = nchunk != nfull && kXcdQueues * (nloc - 1) <= T - 1;
+  double worst = 0.0;
+  std::vector<double> cu((size_t)kXcdQueues * per_q);
+  for (int x = 0; x < kXcds && x < groups; ++x) {
+    std::fill(cu.begin(), cu.end(), 0.0);
+    for (int j = 0; j < T; ++j) {
+      int local, chunk;
+      const int q = T - 1 - j;
+      if (stacked && q % kXcdQueues == 0 && q / kXcdQueues < nloc) {
+        local = nloc - 1 - q / kXcdQueues;
+        chunk = nfull;
+      } else if (stacked) {
+        const int i = j - std::max(0, nloc - (q / kXcdQueues + 1));
+        local = i / nfull;
+        chunk = i - local * nfull;
+      } else {
+        local = j < nloc * nfull ? j / nfull : j - nloc * nfull;
+        chunk = j < nloc * nfull ? j - local * nfull : nfull;
+      }
+      if (local * kXcds + x >= groups) continue;  // padding workgroup
+      double* qb = cu.data() + (size_t)(j % kXcdQueues) * per_q;
+      *std::min_element(qb, qb + per_q) += ovh + (chunk < nfull ? cs : rem);
+    }
+    worst = std::max(worst, *std::max_element(cu.begin(), cu.end()));
+  }
+  return worst;
+}
+
+// Chunk size with the shortest modelled time among ceil(D / n), n = 1..64,
+// at most 16 workgroups per CU.  A workgroup's fixed cost (set-up, drain and
+// the first disparity's cold reads) is taken as one disparity over
+// kSetupRows band rows, a value fitted to an earlier kernel of this layout.  The
+// forward at every chunk size of nine shapes: the pick is the fastest at 320x240,
+// 640x480, 800x600, 1237x823 and 1436x992, 2% from it with 4 pairs of 1436x992 (15
+// disparities, 396 us; 10, 389), 6% at 2872x1984 (19, 727 us; 12, 686), and 10%
+// and 14% at 1920x1080 Dmax 256 (1 pair: 26, 244 us; 8, 222.  4 pairs: 32, 897 us;
+// 16, 783).
+constexpr double kSetupRows = 300.0;
+
+int best_chunk_size(int groups, int D, int rows, int num_cu) {
+  const int cus = std::max(1, num_cu / kXcds);
+  const double ovh = kSetupRows / std::max(1, rows);
+  int best = D;
+  double best_t = 1e300;
+  for (int n = 1; n <= std::min(D, 64); ++n) {
+    const int cs = (D + n - 1) / n;
+    if ((long)groups * ((D + cs - 1) / cs) > 16L * num_cu) break;
+    const double t = agg_makespan(groups, D, cs, cus, ovh);
+    if (t < best_t - 1e-9) {  // ties keep the larger chunks (fewer workgroups)
+      best_t = t;
+      best = cs;
+    }
+  }
+  return best;
+}
+
 // Shape and launch geometry of a plan (host side only).
 void soft_geometry(SoftPlan& pl, int num_cu) {
   const stereo_soft_params& p = pl.p;
@@ -145,7 +213,7 @@ void soft_geometry(SoftPlan& pl, int num_cu) {
   pl.pads = ((128 + D + 2) + 1) & ~1;
   pl.XS = (pl.pads + pl.XA + 128 + 2 + 1) & ~1;
   const int groups = pl.nstrips * pl.nbands * pl.n;
-  pl.csize = best_chunk_size(groups, D, pl.rows, num_cu, D);
+  pl.csize = best_chunk_size(groups, D, pl.rows, num_cu);
   pl.nchunk = (D + pl.csize - 1) / pl.csize;
 }
 
@@ -569,7 +637,7 @@ int stereo_soft_backward(stereo_ctx* c, const float* left, const float* right, i
   if (!saved) pl->wts_valid = false;  // the planes are overwritten below
   auto weights = [&](int dlo, int dhi) {
     SoftArgs a = soft_args(*pl, lambdas, dlo, dhi,
-                           best_chunk_size(groups, dhi - dlo, pl->rows, c->num_cu, dhi - dlo));
+                           best_chunk_size(groups, dhi - dlo, pl->rows, c->num_cu));
     if (whole) {
       all_weights(*pl, a);
     } else {
