@@ -146,8 +146,8 @@ int stereo_autotune(stereo_ctx* ctx, const uint8_t* const* left, const uint8_t* 
  *   Arguments, layouts and ownership as for stereo_disparity.  params->flags
  *   must not hold STEREO_F_KEEP_INTERMEDIATES or STEREO_F_STAGE_TIMING.
  *   Returns STEREO_EINVAL when the shape's scratch exceeds the array (the
- *   message gives both sizes; 1436x992 Dmax 145 needs about 46 MB,
- *   1920x1080 Dmax 256 about 37 MB), STEREO_EHIP when the array's address
+ *   message gives both sizes; 1436x992 Dmax 145 takes 46 MB, 1920x1080
+ *   Dmax 256 66 MB), STEREO_EHIP when the array's address
  *   could not be found on this device.
  * Every call on one device uses the same array and each call re-initialises
  * it: calls whose work overlaps on a device (two streams, two contexts or

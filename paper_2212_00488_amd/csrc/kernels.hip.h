@@ -223,10 +223,12 @@ __device__ __forceinline__ int arm_len(uint32_t p, int c, int delta, int cap, in
 // Two workgroups share a CU only while a wave holds at most 80 SGPRs; the
 // waves-per-EU bound keeps the compiler under that (above it the kernel took
 // a fifth longer).
-// Vector arithmetic bound: 2 instructions a step tested (228 a pixel at caps 21
-// and 31) of about 350; a wave is one row, so that row addresses are scalar, and
-// every step's read is one instruction (both together took 515).  16 images of
-// 960x540: 118 us before, 100 now; 2 of 718x496: 14.7 and 13.3.
+// Vector arithmetic first: 2 instructions a step tested (228 a pixel at caps 21
+// and 31) of about 350, nearly all of the kinds that take four clocks; they issue
+// in 78% of the SIMDs' cycles, and the LDS is active in 60%.  A wave is one row,
+// so that row addresses are scalar, and every step's read is one instruction
+// (both together took 515).  16 images of 960x540: 118 us before, 100 now; 2 of
+// 718x496: 14.7 and 13.3.
 // grid: (ceil(X/64), ceil(Y/kFeatRows), 2 * npair), block (64, kFeatRows).
 __global__ void __launch_bounds__(64 * kFeatRows) __attribute__((amdgpu_waves_per_eu(8)))
 k_feat(const uint8_t* __restrict__ half, int X, int Y, int delta, int arm_x_l, int arm_x_r,
@@ -551,9 +553,13 @@ __device__ __forceinline__ uint32_t add_diff(uint32_t hi, uint32_t lo, uint32_t 
 //                key = min(key, CA << dbits | d): the smallest d wins ties (Step5).
 // Two barriers a disparity: the plane is written between them and read after
 // the second, so one wave's window step overlaps another's next row pass.
-// Bound by VALU issue and the LDS together (counters at 8 x 960x540 half-res
-// pixels, D = 128: a VALU instruction in 66% of the SIMDs' issue slots, LDS
-// active 60% of the time).  Against one base a workgroup with the plane
+// Neither VALU issue nor the LDS is full: counters at 8 x 960x540 half-res
+// pixels, D = 128, show vector instructions in 57% of the SIMDs' cycles (3.4 clocks
+// each on average: measured alone, 32-bit adds, logic, shifts and moves of two
+// operands take 2, the DPP, SDWA and three-operand forms, bit counts and minima 4)
+// and the LDS active in 60%; a wave waits in 31% of its cycles, and 160 KB of LDS
+// leave four waves a SIMD.  51%, 53% and 37% at 718x496, D = 73; 70%, 63% and 25%
+// at 1436x992, D = 145 with arms 41 and 61.  Against one base a workgroup with the plane
 // written in the row pass and corrected by LDS atomics after a third barrier:
 // 1747 -> 1242 us there, 92.7 -> 77.8 us at 718x496 D = 73, 709 -> 539 us at
 // 1436x992 D = 145, 1159 -> 855 us at 1436x992 D = 145 with arms 41 and 61.

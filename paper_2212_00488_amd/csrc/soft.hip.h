@@ -17,9 +17,9 @@
 //             k_soft_merge  d_hat = sum d e_d / sum e_d, log2 sum e_d
 //             (with the weights saved, k_soft_agg also writes every e_d)
 //   backward  k_soft_bprep  per-pixel constants of dL/dCA
-//             k_soft_agg    the weights e_d again, where the forward did not
-//                           save them
-//             k_soft_tcolw  dL/dCA from the weights, and the transposed vertical
+//             k_soft_agg    the aggregate again, where the forward saved neither
+//                           it nor the weights
+//             k_soft_tcolw  dL/dCA from either, and the transposed vertical
 //                           window sums (integer difference arrays over bands
 //                           of output rows, LDS atomics)
 //             k_soft_tr     transposed horizontal window sums back to dL/dC
@@ -240,10 +240,13 @@ constexpr int kAggRows = (kLdsBytes - kAggRowBytes) / 256 - 1;
 // e = 2^{-CA mean / tau (log2 units)}; its sums e and d e per output pixel over
 // the chunk go to part, every e to wts (each where given).
 // A wave's segment has at most SEG rows (their sums stay in registers).
-// Vector arithmetic and LDS bound: the row sums in registers and two barriers
-// a disparity (one for the segments' totals, one for the plane) in place of
-// three and a second pass over the plane.  4 pairs of 718x496, 73 disparities:
-// 440 us before, 366 us now (24 of it from weight rows of whole 128-byte lines).
+// The row sums are in registers, with two barriers a disparity (one for the
+// segments' totals, one for the plane) in place of three and a second pass over
+// the plane.  4 pairs of 718x496, 73 disparities: 440 us before, 366 us now (24 of
+// it from weight rows of whole 128-byte lines).  Counters there: vector
+// instructions issue in 58% of the SIMDs' cycles at most (four clocks each; an
+// exponential 8, some of the others 2), the LDS is active in 22%, a wave waits in
+// 44% of its cycles: with four waves a SIMD it is the waiting that is left.
 // grid: ceil(groups / 8) * 8 * nchunk workgroups (1-D), block 1024.
 template <int KMAX, int SEG>
 __global__ void __launch_bounds__(kThreads) k_soft_agg(SoftArgs a) {
@@ -551,12 +554,14 @@ __global__ void __launch_bounds__(256) k_soft_bprep(const float* __restrict__ in
 // D the offsets of the waves above and the stores.  Between two barriers every
 // wave does B of one disparity, D and C of the two before it and A of the next,
 // on three difference arrays in turn: one barrier a disparity instead of three.
-// Bound by the 24 LDS atomics a thread and disparity and by the 16 waves that a
-// CU holds, and close to the memory rate (0.83 GB of planes, half as much again of
-// halo rows): 4 pairs of 718x496, 73 disparities, 264 us with three barriers, 246
-// with one, 217 with rows of whole 128-byte lines.  CA = true takes saved CA: at 4 pairs of 960x540 and 128 disparities,
-// where the backward computed CA again and summed its planes one by one,
-// forward and backward together took 3.61 ms and take 2.27 (this kernel 0.60).
+// Close to the memory rate (0.97 GB at 4.4 TB/s, halo rows included, where a copy
+// reaches 5.2 to 5.8); the LDS, with 24 atomics a thread and disparity, is active
+// in 21% of the cycles and vector instructions issue in 46% at most.  4 pairs of
+// 718x496, 73 disparities: 264 us with three barriers, 246 with one, 217 with rows
+// of whole 128-byte lines.  CA = true takes saved CA: at 4 pairs of 960x540 and
+// 128 disparities, where the backward computed CA again and summed its planes one
+// by one, forward and backward together took 3.60 ms and take 2.14 (this kernel
+// 0.60).
 // grid: strips * bands * n * ndg rounded up to 8 (1-D, xcd_item), block 1024;
 // disparity group g of ndg covers [dlo + g nd / ndg, dlo + (g + 1) nd / ndg).
 constexpr int kTcolBand = 128;
@@ -777,8 +782,9 @@ __global__ void __launch_bounds__(64 * kTcwWaves) k_soft_tcolw(TcwArgs a) {
 // values of a disparity go to an LDS row that ends with each entry's last one,
 // then to the strip's partial row, which k_soft_gright sums over the strips.
 // A block takes 4 rows of a strip.
-// Vector arithmetic bound (about 43 instructions a column and disparity, 16 of
-// them for the derivatives; three waves a SIMD).  4 pairs of 718x496, 73
+// Vector arithmetic first (about 43 instructions a column and disparity, 16 of
+// them for the derivatives: issued in up to 76% of the SIMDs' cycles; three waves a
+// SIMD, waiting in 40% of theirs).  4 pairs of 718x496, 73
 // disparities: 242 us as a scan and scatter of difference arrays in LDS, 197 now;
 // at 960x540 and 128 disparities 557 and 445.
 // grid: strips * ceil(Y / 4) * n rounded up to 8 (1-D, xcd_item), block 256.
