@@ -58,11 +58,12 @@ int common_checks(stereo_ctx* c, int W, int H, int Dmax, const stereo_params* pa
 // The cached plan of (W, H, Dmax, p, owner) holding at least npair pairs,
 // made when missing: least recently used plans are given up (except pinned ones)
 // while the memory cap or the device does not hold the preferred launch
-// geometry, and only then a smaller one is taken.  A new plan's set-up is
-// enqueued on stream s, the stream its work will run on.  Calls with different owners never share
+// geometry, and only then a smaller one is taken, if the caller has nothing left
+// to free itself (smaller).  A new plan's set-up is enqueued on stream s, the
+// stream its work will run on.  Calls with different owners never share
 // scratch, so their work may overlap on the device.
 int get_plan(stereo_ctx* c, int W, int H, int Dmax, const stereo_params& p, int npair,
-             const void* owner, hipStream_t s, Plan** out);
+             const void* owner, hipStream_t s, Plan** out, bool smaller = true);
 // Frees one plan of the context (the caller has synchronised its work).
 void drop_plan(stereo_ctx* c, Plan* pl);
 // Enqueues the whole path for npair (<= plan's) pairs on stream s.  Makes no

@@ -110,8 +110,9 @@ void free_exec(stereo_ctx* c, Exec* e) {
 
 // Builds the resident state of (W, H, Dmax) for batches of nb frames on
 // slot i: buffers, a plan of its own and a graph captured from the path's
-// launch sequence over the nb pairs on the slot's stream.
-int make_exec(stereo_server* s, int i, int W, int H, int Dmax, int nb, Exec** out) {
+// launch sequence over the nb pairs on the slot's stream.  smaller: a launch
+// geometry that needs less scratch than the preferred one will do.
+int make_exec(stereo_server* s, int i, int W, int H, int Dmax, int nb, bool smaller, Exec** out) {
   Slot& sl = s->slots[i];
   stereo_ctx* c = s->ctx;
   Exec* e = new Exec();
@@ -130,7 +131,7 @@ int make_exec(stereo_server* s, int i, int W, int H, int Dmax, int nb, Exec** ou
   }
   // the plan's owner key is unique per (slot, batch size): each Exec has its own
   const void* owner = reinterpret_cast<const char*>(&sl) + nb;
-  int rc = get_plan(c, W, H, Dmax, s->params, nb, owner, sl.stream, &e->plan);
+  int rc = get_plan(c, W, H, Dmax, s->params, nb, owner, sl.stream, &e->plan, smaller);
   if (rc) {
     e->plan = nullptr;
     free_exec(c, e);
@@ -195,17 +196,18 @@ int start(stereo_server* s, int i, std::vector<Request>& batch) {
   auto it = sl.execs.find(key);
   Exec* e = nullptr;
   if (it == sl.execs.end()) {
-    int rc = make_exec(s, i, r0.W, r0.H, r0.Dmax, nb, &e);
+    int rc = make_exec(s, i, r0.W, r0.H, r0.Dmax, nb, false, &e);
     // out of device memory: free the resident state (graphs, buffers, plans)
-    // of idle slots, this one first, and try again
+    // of idle slots, this one first, and try again; then a smaller launch form
     for (int k = 0; rc == STEREO_ENOMEM && k < (int)s->slots.size(); ++k) {
       Slot& q = s->slots[(i + k) % s->slots.size()];
       if (q.busy || q.execs.empty()) continue;
       (void)hipStreamSynchronize(q.stream);
       for (auto& kv : q.execs) free_exec(s->ctx, kv.second);
       q.execs.clear();
-      rc = make_exec(s, i, r0.W, r0.H, r0.Dmax, nb, &e);
+      rc = make_exec(s, i, r0.W, r0.H, r0.Dmax, nb, false, &e);
     }
+    if (rc == STEREO_ENOMEM) rc = make_exec(s, i, r0.W, r0.H, r0.Dmax, nb, true, &e);
     if (rc) return rc;
     sl.execs[key] = e;
   } else {

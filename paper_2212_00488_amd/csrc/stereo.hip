@@ -444,7 +444,7 @@ int make_plan_evicting(stereo_ctx* c, const Plan& geo, hipStream_t s, Plan** out
 }
 
 int get_plan(stereo_ctx* c, int W, int H, int Dmax, const stereo_params& p, int npair,
-             const void* owner, hipStream_t s, Plan** out) {
+             const void* owner, hipStream_t s, Plan** out, bool smaller) {
   for (Plan* pl : c->plans)
     if (pl->W == W && pl->H == H && pl->Dmax == Dmax && pl->npair >= npair && pl->owner == owner &&
         same_params(pl->p, p)) {
@@ -466,7 +466,7 @@ int get_plan(stereo_ctx* c, int W, int H, int Dmax, const stereo_params& p, int 
   int rc = plan_setup(c, geo, W, H, Dmax, p, npair, kForms[0]);
   if (rc) return rc;
   rc = make_plan_evicting(c, geo, s, &pl);
-  if (rc == STEREO_ENOMEM)
+  if (rc == STEREO_ENOMEM && smaller)
     for (const Plan& g : smaller_forms(c, geo)) {
       rc = make_plan_evicting(c, g, s, &pl);
       if (rc != STEREO_ENOMEM) break;

@@ -7,6 +7,7 @@ Dmax 145, 1920x1080 Dmax 256, 2872x1984 Dmax 290) and three smaller ones,
 one of them odd-sized."""
 
 import sys
+import time
 
 import numpy as np
 import pytest
@@ -153,3 +154,57 @@ def test_budget_holds_with_batches(pool):
         t = r["t_admit_ms"]
         live = [q for q in res if q["t_admit_ms"] <= t < q["t_done_ms"]]
         assert sum(volume(kinds[q["tag"]]) for q in live) <= budget
+
+
+def test_full_device_frees_idle_slots_before_a_smaller_launch_form():
+    """Two shapes in turn on one slot, with device memory for one shape's resident
+    state and half of the other's: the idle state is freed for the second shape's
+    preferred launch form (seen by the memory it takes, the same as alone), in
+    place of a form of fewer chunks beside it."""
+    shapes = [(4096, 3000, 512), (4000, 3072, 512)]
+    rng = np.random.default_rng(840)
+    frames = [tuple(rng.integers(0, 256, (h, w, 3), dtype=np.uint8) for _ in range(2))
+              for w, h, _ in shapes]
+    outs = [np.empty((h, w), np.int16) for w, h, _ in shapes]
+
+    def free():
+        torch.cuda.synchronize()
+        time.sleep(0.5)  # freed memory is cleared before it counts as free again
+        return torch.cuda.mem_get_info()[0]
+
+    def serve(srv, k):
+        outs[k].fill(-7)
+        srv.submit(*frames[k], shapes[k][2], outs[k], k)
+        res = srv.poll(timeout_ms=20000)
+        assert [(r["tag"], r["status"]) for r in res] == [(k, 0)], (res, srv.last_error())
+        return outs[k].copy()
+
+    ref, alone = [], []
+    for k in range(2):
+        for _ in range(2):  # the first time loads kernels
+            srv = Server(0, slots=1, max_batch=1)
+            free0 = free()
+            got = serve(srv, k)
+            taken = free0 - free()
+            srv.close()
+        ref.append(got)
+        alone.append(taken)
+    print(f"[serve] resident state of each shape alone: {alone}", flush=True)
+    filler = []
+    srv = Server(0, slots=1, max_batch=1)
+    try:
+        room = alone[0] + alone[1] - (80 << 20)
+        while (left := free() - room) > 0:
+            filler.append(torch.empty(min(left, 16 << 30), dtype=torch.uint8, device="cuda"))
+        free0 = free()
+        print(f"[serve] {free0} bytes left", flush=True)
+        for k in (0, 1, 0):
+            got = serve(srv, k)
+            taken = free0 - free()
+            print(f"[serve] shape {k}: {taken}", flush=True)
+            assert np.array_equal(got, ref[k])
+            assert abs(taken - alone[k]) <= 32 << 20, (k, taken, alone)
+    finally:
+        srv.close()
+        del filler
+        torch.cuda.empty_cache()
